@@ -1,6 +1,5 @@
-// Products built on the stored factor: solves with Sigma (forward and
-// backward tile substitution) and emulation draws Y = L Z (Sec. III.B), with
-// the Philox4x32-10 / Box-Muller normal generator.
+// Emulation draws Y = L Z from the stored factor (Sec. III.B), with the
+// Philox4x32-10 / Box-Muller normal generator.
 #include "common.h"
 #include "launch.h"
 
@@ -168,165 +167,6 @@ void launch_lower_apply(const Tiles &T, const float *Z, int64_t ldz, float *Y, i
 {
     dim3 grid(T.nt * (T.b / SB), (ndraws + SB - 1) / SB);
     lower_apply_kernel<<<grid, SNT, 0, st>>>(T, Z, ldz, Y, ldy, ndraws);
-}
-
-// ---------------------------------------------------------------- solve
-// Diagonal blocks: one wavefront per right-hand side, no barriers.  Lane l
-// keeps rows i = l (mod 64) of the block in registers.
-constexpr int MAXR = 2048 / 64;
-
-__global__ __launch_bounds__(64) void diag_forward_kernel(Tiles T, int K, double *B, int64_t ldb)
-{
-    const int b = T.b, lane = threadIdx.x;
-    const int vb = (int)min((int64_t)b, T.n - (int64_t)K * b);
-    double *y = B + (int64_t)K * b + (int64_t)blockIdx.x * ldb;
-    const double *L = (const double *)(T.slots + tile_index(K, K) * T.slot_bytes);
-    double v[MAXR];
-    const int nr = (vb + 63) / 64;
-#pragma unroll
-    for (int t = 0; t < MAXR; ++t) v[t] = (t < nr && lane + 64 * t < vb) ? y[lane + 64 * t] : 0.0;
-    for (int c = 0; c < vb; ++c) {
-        const int owner = c & 63, tc = c >> 6;
-        double xc = 0.0;
-#pragma unroll
-        for (int t = 0; t < MAXR; ++t)
-            if (t == tc) xc = v[t];
-        xc = __shfl(xc, owner, 64) / L[c + (int64_t)c * b];
-        const double *lc = L + (int64_t)c * b;
-#pragma unroll
-        for (int t = 0; t < MAXR; ++t) {
-            int i = lane + 64 * t;
-            if (t < nr && i > c && i < vb) v[t] -= lc[i] * xc;
-            if (t == tc && lane == owner) v[t] = xc;
-        }
-    }
-#pragma unroll
-    for (int t = 0; t < MAXR; ++t)
-        if (t < nr && lane + 64 * t < vb) y[lane + 64 * t] = v[t];
-}
-
-__global__ __launch_bounds__(64) void diag_backward_kernel(Tiles T, int K, double *B, int64_t ldb)
-{
-    const int b = T.b, lane = threadIdx.x;
-    const int vb = (int)min((int64_t)b, T.n - (int64_t)K * b);
-    double *y = B + (int64_t)K * b + (int64_t)blockIdx.x * ldb;
-    const double *L = (const double *)(T.slots + tile_index(K, K) * T.slot_bytes);
-    double x[MAXR];
-    const int nr = (vb + 63) / 64;
-#pragma unroll
-    for (int t = 0; t < MAXR; ++t) x[t] = 0.0;
-    // x_c = (y_c - sum_{i>c} L_ic x_i) / L_cc, c descending
-    for (int c = vb - 1; c >= 0; --c) {
-        const double *lc = L + (int64_t)c * b;
-        double s = 0.0;
-#pragma unroll
-        for (int t = 0; t < MAXR; ++t) {
-            int i = lane + 64 * t;
-            if (t < nr && i > c && i < vb) s += lc[i] * x[t];
-        }
-        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-        const double xc = (y[c] - s) / lc[c];
-        const int owner = c & 63, tc = c >> 6;
-#pragma unroll
-        for (int t = 0; t < MAXR; ++t)
-            if (t == tc && lane == owner) x[t] = xc;
-    }
-#pragma unroll
-    for (int t = 0; t < MAXR; ++t)
-        if (t < nr && lane + 64 * t < vb) y[lane + 64 * t] = x[t];
-}
-
-// B_I -= L_IK X_K for I > K: one thread per row (128 rows per block), 16
-// right-hand sides per pass, X_K staged in LDS 128 rows at a time.
-__global__ __launch_bounds__(128) void update_forward_kernel(Tiles T, int K, double *B, int64_t ldb, int nrhs)
-{
-    __shared__ double xs[128][17];
-    const int b = T.b, per = b / 128;
-    const int I = K + 1 + blockIdx.x / per;
-    const int r = (blockIdx.x % per) * 128 + threadIdx.x;
-    const int64_t gi = (int64_t)I * b + r;
-    const int vk = (int)min((int64_t)b, T.n - (int64_t)K * b);
-    const int cls = T.map[I + (int64_t)K * T.nt];
-    const int ts = T.tscale[I + (int64_t)K * T.nt];
-    const char *tile = T.slots + tile_index(I, K) * T.slot_bytes;
-    for (int j0 = 0; j0 < nrhs; j0 += 16) {
-        const int nj = min(16, nrhs - j0);
-        double acc[16];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) acc[j] = 0.0;
-        for (int c0 = 0; c0 < vk; c0 += 128) {
-            __syncthreads();
-            for (int e = threadIdx.x; e < 128 * 16; e += 128) {
-                int c = e % 128, j = e / 128;
-                xs[c][j] = (c0 + c < vk && j < nj) ? B[(int64_t)K * b + c0 + c + (int64_t)(j0 + j) * ldb] : 0.0;
-            }
-            __syncthreads();
-            if (gi < T.n) {
-                const int cmax = min(128, vk - c0);
-                for (int c = 0; c < cmax; ++c) {
-                    double l = load_stored(tile, cls, T.lo16, ts, (int64_t)r + (int64_t)(c0 + c) * b);
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) acc[j] += l * xs[c][j];
-                }
-            }
-        }
-        if (gi < T.n)
-            for (int j = 0; j < nj; ++j) B[gi + (int64_t)(j0 + j) * ldb] -= acc[j];
-    }
-}
-
-// B_J -= L_KJ^T X_K for J < K: a 64-column chunk of tile (K, J) per block,
-// staged 64 rows at a time through LDS.
-__global__ __launch_bounds__(256) void update_backward_kernel(Tiles T, int K, double *B, int64_t ldb, int nrhs)
-{
-    __shared__ double ls[64][65];  // ls[c][r]
-    __shared__ double xs[64][17];
-    const int b = T.b, per = b / 64;
-    const int J = blockIdx.x / per;
-    const int c0 = (blockIdx.x % per) * 64;
-    const int vk = (int)min((int64_t)b, T.n - (int64_t)K * b);
-    const int cls = T.map[K + (int64_t)J * T.nt];
-    const int ts = T.tscale[K + (int64_t)J * T.nt];
-    const char *tile = T.slots + tile_index(K, J) * T.slot_bytes;
-    const int col = threadIdx.x & 63, jg = threadIdx.x >> 6;  // 4 groups of 4 rhs
-    for (int j0 = 0; j0 < nrhs; j0 += 16) {
-        const int nj = min(16, nrhs - j0);
-        double acc[4] = {0.0, 0.0, 0.0, 0.0};
-        for (int r0 = 0; r0 < vk; r0 += 64) {
-            __syncthreads();
-            for (int e = threadIdx.x; e < 64 * 64; e += 256) {
-                int r = e & 63, c = e >> 6;
-                ls[c][r] = (r0 + r < vk) ? load_stored(tile, cls, T.lo16, ts, (int64_t)(r0 + r) + (int64_t)(c0 + c) * b) : 0.0;
-            }
-            for (int e = threadIdx.x; e < 64 * 16; e += 256) {
-                int r = e & 63, j = e >> 6;
-                xs[r][j] = (r0 + r < vk && j < nj) ? B[(int64_t)K * b + r0 + r + (int64_t)(j0 + j) * ldb] : 0.0;
-            }
-            __syncthreads();
-            for (int r = 0; r < 64; ++r) {
-                double l = ls[col][r];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) acc[q] += l * xs[r][jg * 4 + q];
-            }
-        }
-        const int64_t gj = (int64_t)J * b + c0 + col;
-        if (gj < T.n)
-            for (int q = 0; q < 4; ++q)
-                if (jg * 4 + q < nj) B[gj + (int64_t)(j0 + jg * 4 + q) * ldb] -= acc[q];
-    }
-}
-
-void launch_solve(const Tiles &T, double *B, int64_t ldb, int nrhs, hipStream_t st)
-{
-    const int nt = T.nt, b = T.b;
-    for (int K = 0; K < nt; ++K) {
-        diag_forward_kernel<<<nrhs, 64, 0, st>>>(T, K, B, ldb);
-        if (K + 1 < nt) update_forward_kernel<<<(nt - K - 1) * (b / 128), 128, 0, st>>>(T, K, B, ldb, nrhs);
-    }
-    for (int K = nt - 1; K >= 0; --K) {
-        diag_backward_kernel<<<nrhs, 64, 0, st>>>(T, K, B, ldb);
-        if (K > 0) update_backward_kernel<<<K * (b / 64), 256, 0, st>>>(T, K, B, ldb, nrhs);
-    }
 }
 
 }  // namespace mpc

@@ -90,8 +90,11 @@ int launch_cov_samples(const Tiles &T, const double *xi, int64_t ldxi, int64_t m
                        double *xp, int64_t mp, double *orig, hipStream_t st);
 int estimate_probes();
 
-// ---- solve, sample (k_apply.hip)
-void launch_solve(const Tiles &T, double *B, int64_t ldb, int nrhs, hipStream_t st);
+// ---- solve (k_solve.hip): ctl = solve_ctl_bytes() of scratch, cleared by the launch
+size_t solve_ctl_bytes();
+void launch_solve(const Tiles &T, double *B, int64_t ldb, int nrhs, int *ctl, hipStream_t st);
+
+// ---- sample (k_apply.hip)
 void launch_normal_draws(uint64_t seed, int64_t count, float *z, uint32_t *raw, hipStream_t st);
 void launch_normal_matrix(uint64_t seed, int64_t n, int ndraws, float *Z, int64_t ldz, hipStream_t st);
 // draws of columns d0 .. d0+nd-1 of the n x ndraws sequence into Z's columns 0 .. nd-1

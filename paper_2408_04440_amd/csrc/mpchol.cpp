@@ -74,6 +74,7 @@ struct mpchol_handle {
     double *d_fro2 = nullptr, *d_amax = nullptr;
     unsigned long long *d_info = nullptr;
     double *d_scalar = nullptr;
+    int *d_solve = nullptr;      // tickets and finished counts of the solves
     std::vector<uint8_t> h_map;
     std::vector<double> h_fro2, h_amax;
     double total_fro = 0;
@@ -217,7 +218,7 @@ static void release(mpchol_handle *h)
 {
     void *ptrs[] = {h->slots, h->orig, h->d_sigma, h->d_x, h->p64, h->p32, h->p32s, h->p16, h->p8, h->p8x, h->pmax, h->pscale,
                     h->poz, h->pexp, h->d_ozc,
-                    h->d_map, h->d_tscale, h->d_fro2, h->d_amax, h->d_info, h->d_scalar, h->d_items, h->d_qmask,
+                    h->d_map, h->d_tscale, h->d_fro2, h->d_amax, h->d_info, h->d_scalar, h->d_solve, h->d_items, h->d_qmask,
                     h->d_all_items, h->d_partial, h->d_tres2, h->d_params, h->d_feats, h->d_est, h->d_zbuf};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
@@ -328,6 +329,7 @@ int mpchol_create(mpchol_t *hp, int64_t n, int32_t tile, const mpchol_opts *o)
     A(dalloc(&h->d_amax, nt * nt * 8));
     A(dalloc(&h->d_info, 8));
     A(dalloc(&h->d_scalar, 64));
+    A(dalloc(&h->d_solve, solve_ctl_bytes()));
     A(dalloc(&h->d_qmask, nt * nt));
     A(dalloc(&h->d_all_items, h->ntile * 4));
     A(dalloc(&h->d_partial, h->ntile * (bb / (128 * 128)) * 8));
@@ -1101,7 +1103,7 @@ extern "C" int mpchol_solve(mpchol_t h, int32_t nrhs, double *B, int64_t ldb)
     if (h->state != S_FACTORED) return MPCHOL_EORDER;
     HIPCHK(hipSetDevice(h->dev));
     HIPCHK(hipEventRecord(h->ev[2], h->st));
-    launch_solve(h->tiles(), B, ldb, nrhs, h->st);
+    launch_solve(h->tiles(), B, ldb, nrhs, h->d_solve, h->st);
     HIPCHK(hipEventRecord(h->ev[3], h->st));
     HIPCHK(hipGetLastError());
     return MPCHOL_OK;
