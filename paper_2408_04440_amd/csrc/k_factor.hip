@@ -1,265 +1,569 @@
 // The factorization's tasks (Sec. V.A): POTRF of a diagonal tile, TRSM of the
 // panel below it, and the SYRK/GEMM trailing update grouped per precision
 // class, all for gfx950.
+#include <type_traits>
+
 #include "common.h"
 #include "gemm_core.h"
 #include "launch.h"
 
 namespace mpc {
 
-// ---------------------------------------------------------------- POTRF
-// Cholesky of the 64 x 64 block at (j0, j0) of an FP64 tile (column-major,
-// leading dimension b) by one wavefront, in four quarters of 16 columns: lane
-// r holds its row of the quarter in registers, first less the earlier
-// quarters' contribution, then right-looking over the quarter's columns with
-// each finished column broadcast through LDS (a[c][r] = L(j0 + r, j0 + c)).
-// A pivot that is not positive (or NaN) records its 1-based global column in
-// *info (minimum over failures); the computation then continues on NaNs and
-// still terminates.  Zeros are written above the diagonal.
+// ---------------------------------------------------------------- blocks of 64 in LDS
+// Shared by the diagonal tile's POTRF and the panel TRSM: four waves, each
+// owning 16 rows; 64 x 64 blocks in LDS column-major with leading dimension LD64.
+constexpr int LD64 = 66;
+
+// orders one wavefront's LDS accesses across lanes (the hardware executes a
+// wave's LDS instructions in order; this keeps the compiler from moving them)
 __device__ inline void wave_sync()
 {
-    // orders one wavefront's LDS accesses across lanes (the hardware executes a
-    // wave's LDS instructions in order; this keeps the compiler from moving them)
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__global__ __launch_bounds__(64) void potrf_block_kernel(double *tile, int b, int j0, int64_t col0, int64_t n,
+// Lane N of every row of 16 lanes, to the whole row (a DPP move).
+template <int N> __device__ inline double row_bcast(double v)
+{
+    return __longlong_as_double(__builtin_amdgcn_update_dpp(0ll, __double_as_longlong(v), 0x150 + N, 0xf, 0xf, true));
+}
+
+// f(integral_constant<int, I>) for I = 0 .. N - 1 (the DPP control is a constant).
+template <int I, int N, typename F> __device__ inline void static_for(F f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<I + 1, N>(f);
+    }
+}
+
+// t[j] -= m * (lane j of the row of 16's s) for j = C + 1 .. 15: one DPP
+// multiply-add each (5 cycles; the compiler makes a move and a multiply-add of
+// it, 12 cycles, and gathers the moves of many columns until they spill).  The
+// s_nops cover the wait states between a VALU write and a DPP read of it, s at
+// the start and the last t at the end, which the compiler does not see here.
+#define MPC_U(j) "\n\tv_fmac_f64_dpp %" #j ", -%[s], %[m] row_newbcast:" #j " row_mask:0xf bank_mask:0xf"
+#define MPC_FROM_15 MPC_U(15)
+#define MPC_FROM_14 MPC_U(14) MPC_FROM_15
+#define MPC_FROM_13 MPC_U(13) MPC_FROM_14
+#define MPC_FROM_12 MPC_U(12) MPC_FROM_13
+#define MPC_FROM_11 MPC_U(11) MPC_FROM_12
+#define MPC_FROM_10 MPC_U(10) MPC_FROM_11
+#define MPC_FROM_9 MPC_U(9) MPC_FROM_10
+#define MPC_FROM_8 MPC_U(8) MPC_FROM_9
+#define MPC_FROM_7 MPC_U(7) MPC_FROM_8
+#define MPC_FROM_6 MPC_U(6) MPC_FROM_7
+#define MPC_FROM_5 MPC_U(5) MPC_FROM_6
+#define MPC_FROM_4 MPC_U(4) MPC_FROM_5
+#define MPC_FROM_3 MPC_U(3) MPC_FROM_4
+#define MPC_FROM_2 MPC_U(2) MPC_FROM_3
+#define MPC_FROM_1 MPC_U(1) MPC_FROM_2
+#define MPC_ROW_ASM(body)                                                                                             \
+    asm("s_nop 1" body "\n\ts_nop 1"                                                                                  \
+        : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]), "+v"(t[4]), "+v"(t[5]), "+v"(t[6]), "+v"(t[7]),             \
+          "+v"(t[8]), "+v"(t[9]), "+v"(t[10]), "+v"(t[11]), "+v"(t[12]), "+v"(t[13]), "+v"(t[14]), "+v"(t[15])        \
+        : [s] "v"(s), [m] "v"(m))
+template <int C> __device__ inline void row_update(double (&t)[16], double s, double m)
+{
+    if constexpr (C == 0) MPC_ROW_ASM(MPC_FROM_1);
+    else if constexpr (C == 1) MPC_ROW_ASM(MPC_FROM_2);
+    else if constexpr (C == 2) MPC_ROW_ASM(MPC_FROM_3);
+    else if constexpr (C == 3) MPC_ROW_ASM(MPC_FROM_4);
+    else if constexpr (C == 4) MPC_ROW_ASM(MPC_FROM_5);
+    else if constexpr (C == 5) MPC_ROW_ASM(MPC_FROM_6);
+    else if constexpr (C == 6) MPC_ROW_ASM(MPC_FROM_7);
+    else if constexpr (C == 7) MPC_ROW_ASM(MPC_FROM_8);
+    else if constexpr (C == 8) MPC_ROW_ASM(MPC_FROM_9);
+    else if constexpr (C == 9) MPC_ROW_ASM(MPC_FROM_10);
+    else if constexpr (C == 10) MPC_ROW_ASM(MPC_FROM_11);
+    else if constexpr (C == 11) MPC_ROW_ASM(MPC_FROM_12);
+    else if constexpr (C == 12) MPC_ROW_ASM(MPC_FROM_13);
+    else if constexpr (C == 13) MPC_ROW_ASM(MPC_FROM_14);
+    else if constexpr (C == 14) MPC_ROW_ASM(MPC_FROM_15);
+}
+
+// x / d given r, 1 / d to at least half of its bits: one correction by the
+// exact remainder, which returns an exactly representable quotient exactly.
+__device__ inline double div_by(double x, double d, double r)
+{
+    const double q = x * r;
+    return __builtin_fma(__builtin_fma(-q, d, x), r, q);
+}
+
+// s = sqrt(d) and r = 1 / s to about 47 bits, for d in [2^-900, 2^900]: one
+// step of Goldschmidt's iteration from the hardware's estimate, the root then
+// corrected by its exact remainder (a perfect square gives its root exactly).
+__device__ inline void sqrt_rcp(double d, double &s, double &r)
+{
+    const double y = __builtin_amdgcn_rsq(d);
+    double g = d * y, h = 0.5 * y;
+    const double e = __builtin_fma(-h, g, 0.5);
+    g = __builtin_fma(g, e, g);
+    h = __builtin_fma(h, e, h);
+    s = __builtin_fma(__builtin_fma(-g, g, d), h, g);
+    r = h + h;
+}
+
+// acc[ct] += X(rows 16w.., k) Y(rows 16ct.., k)^T over 64 columns of the LDS
+// blocks.  Operands swapped: a lane holds row gi of its wave's 16 and
+// columns gg + 4v of each 16-column tile.
+__device__ inline void mma64(double4_t (&acc)[4], const double *X, const double *Y, int wave, int gi, int gg)
+{
+    struct Ops {
+        double x[2], y[2][4];
+    } u, w;
+    auto load = [&](int k, Ops &o) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int row = (k + 4 * s + gg) * LD64 + gi;
+            o.x[s] = X[row + wave * 16];
+#pragma unroll
+            for (int ct = 0; ct < 4; ++ct) o.y[s][ct] = Y[row + ct * 16];
+        }
+    };
+    auto mma = [&](const Ops &o) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int ct = 0; ct < 4; ++ct)
+                acc[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(o.y[s][ct], o.x[s], acc[ct], 0, 0, 0);
+    };
+    load(0, u);
+#pragma unroll 1
+    for (int k = 0; k < 64; k += 16) {  // the next eight columns are read while eight are multiplied
+        load(k + 8, w);
+        mma(u);
+        if (k < 48) load(k + 16, u);
+        mma(w);
+    }
+}
+
+// X = -acc L^-T for a wave's 16 rows: L the lower 64 x 64 block in LDS,
+// inv[c] = 1 / L(c, c), acc the negated 16 x 64 right-hand side.  Column panels of 16:
+// every lane gathers its row of the panel (the four lane groups hold the same
+// rows), substitutes column by column against broadcasts of the diagonal
+// block's rows from other lanes, and the panel's
+// product with the rest of L goes to the later panels' accumulators on the
+// MFMA.  put(p, t, v): lane (gi, gg) delivers X(gi, 16 p + 4 t + gg).
+template <typename Put>
+__device__ inline void wave_trsm64(double4_t (&acc)[4], const double *L, const double *inv, double *scratch, int gi,
+                                   int gg, Put put)
+{
+    // (the panels share one copy of the code, acc[0] always the current one: a
+    // diagonal workgroup runs it once, and four copies cost more in instruction
+    // fetches than the moves)
+#pragma unroll 1
+    for (int p = 0; p < 4; ++p) {
+        const double *Lp = L + 16 * p * LD64 + 16 * p + gi;
+        double x[16], ld[16];  // lane gi: its row, and row gi of the panel's 16 x 16 diagonal block
+        wave_sync();
+#pragma unroll
+        for (int v = 0; v < 4; ++v) scratch[gi * 17 + gg + 4 * v] = -acc[0][v];
+        const double rl = inv[16 * p + gi];
+#pragma unroll
+        for (int c = 0; c < 16; ++c) ld[c] = Lp[c * LD64];
+        wave_sync();
+#pragma unroll
+        for (int c = 0; c < 16; ++c) x[c] = scratch[gi * 17 + c];
+        static_for<0, 16>([&](auto C) {
+            constexpr int c = C;
+            x[c] = div_by(x[c], row_bcast<c>(ld[c]), row_bcast<c>(rl));
+            row_update<c>(x, ld[c], x[c]);
+        });
+        double a[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const double x0 = x[4 * t], x1 = x[4 * t + 1], x2 = x[4 * t + 2], x3 = x[4 * t + 3];
+            const double lo = gg & 1 ? x1 : x0, hi = gg & 1 ? x3 : x2;
+            a[t] = gg & 2 ? hi : lo;  // x[4 t + gg]
+            put(p, t, a[t]);
+        }
+#pragma unroll
+        for (int r = 1; r < 4; ++r) {  // the later panels' sums, moved up by one
+            acc[r - 1] = acc[r];
+            if (p + r < 4) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    acc[r - 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(Lp[(4 * t + gg) * LD64 + 16 * r], a[t], acc[r - 1],
+                                                                      0, 0, 0);
+            }
+        }
+    }
+}
+
+// Columns h .. h + 15 of the block S by one wave, right-looking in LDS, with the
+// library's square root and division: for pivots outside the range of sqrt_rcp,
+// among them zero, negative, infinite and NaN.
+__device__ __attribute__((noinline)) void panel_potrf16(double *S, int h, int lane, int64_t col0, int64_t n,
+                                                        unsigned long long *info)
+{
+#pragma unroll 1
+    for (int c = h; c < h + 16; ++c) {
+        wave_sync();
+        const double d = S[c * LD64 + c], x = S[c * LD64 + lane];
+        if (lane == 0 && !(d > 0.0) && col0 + c < n) atomicMin(info, (unsigned long long)(col0 + c + 1));
+        const double piv = sqrt(d), l = lane == c ? piv : x / piv;
+        wave_sync();
+        S[c * LD64 + lane] = lane >= c ? l : 0.0;
+        wave_sync();
+#pragma unroll 1
+        for (int j = c + 1; j < h + 16; ++j) S[j * LD64 + lane] -= l * S[c * LD64 + j];
+    }
+}
+
+// Cholesky of the lower 64 x 64 block S in LDS by four waves, in panels of 16
+// columns: one wave factors the panel, lane r holding row r, with the panel's
+// diagonal block held once more by every row of 16 lanes for the broadcasts; the
+// later tiles are updated on the MFMA.  Zeros go
+// above the diagonal.  A pivot that is not positive (or NaN) records its
+// 1-based global column col0 + c + 1 in *info (minimum over failures); the
+// computation then continues on NaNs and still terminates.
+__device__ inline void block_potrf64(double *S, int wave, int lane, int64_t col0, int64_t n, unsigned long long *info)
+{
+    const int gi = lane & 15, gg = lane >> 4;
+    for (int p = 0; p < 4; ++p) {
+        const int h = 16 * p;
+        if (wave == 0) {
+            double x[16], xd[16];  // row `lane`, and row h + gi: every 16 lanes hold the diagonal block to broadcast
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                xd[j] = S[(h + j) * LD64 + h + gi];
+                x[j] = S[(h + j) * LD64 + lane];
+            }
+            bool ordinary = true;  // every pivot in [2^-900, 2^900)
+            static_for<0, 16>([&](auto C) {
+                constexpr int c = C;
+                const double d = row_bcast<c>(xd[c]);
+                ordinary = ordinary && (uint32_t)(__double_as_longlong(d) >> 32) - 0x07B00000u < 0x78300000u - 0x07B00000u;
+                double piv, r;
+                sqrt_rcp(d, piv, r);
+                xd[c] = div_by(xd[c], piv, r);
+                if (gi == c) xd[c] = piv;
+                x[c] = div_by(x[c], piv, r);
+                if (lane == h + c) x[c] = piv;
+                row_update<c>(xd, xd[c], xd[c]);
+                row_update<c>(x, xd[c], x[c]);
+            });
+            if (__builtin_expect(__ballot(ordinary) == ~0ull, 1)) {
+#pragma unroll
+                for (int j = 0; j < 16; ++j) S[(h + j) * LD64 + lane] = lane >= h + j ? x[j] : 0.0;
+            } else {
+                panel_potrf16(S, h, lane, col0, n, info);
+            }
+        }
+        __syncthreads();
+        if (p == 3) break;
+        // lower tiles (rt, ct) of the trailing 64 - h - 16 columns, dealt to the waves
+        const int q = 3 - p;
+        for (int t = wave; t < q * (q + 1) / 2; t += 4) {
+            const int i = t < 1 ? 0 : t < 3 ? 1 : 2, j = t - i * (i + 1) / 2;
+            const int rt = p + 1 + i, ct = p + 1 + j;
+            double4_t a = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const double *col = S + (h + 4 * s + gg) * LD64 + gi;
+                a = __builtin_amdgcn_mfma_f64_16x16x4f64(col[ct * 16], col[rt * 16], a, 0, 0, 0);
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) S[(ct * 16 + gg + 4 * v) * LD64 + rt * 16 + gi] -= a[v];
+        }
+        __syncthreads();
+    }
+}
+
+// ---------------------------------------------------------------- POTRF of a diagonal tile
+// One launch for the whole b x b tile (b = 64 nb), blocks of 64.  What bounds it
+// is the chain of nb diagonal blocks; a launch each for a block's factor, the
+// rows below it and their update cost about 60 us a block, and 18 us now (of
+// 43,000 cycles 21,000 factor the block, 11,000 solve the one below it, 6,000
+// update the next; a 1024 tile: 0.96 -> 0.29 ms).  Every block has its workgroup, which sums its products with the blocks to its left as
+// these become known and waits for the rest of its turn in place:
+//   diagonal workgroup m: blocks (m, m-1) and (m, m) -- the solve of the first
+//       feeds the second without leaving the compute unit, so the chain crosses
+//       memory once per block;
+//   workgroup (i, m), i >= m + 2: block (i, m).
+// prog[i] counts the finished blocks of block row i (they finish in column
+// order; prog[i] = i + 1 once its diagonal block is factored).  Finished blocks
+// are written and read with device-scope accesses, and their stores have
+// completed before the count is raised.  Places are given out by a ticket
+// counter in column order, and every block depends on blocks with earlier
+// tickets only, so the earliest workgroup can always finish.  A wait that lasts
+// longer than WAIT_TICKS sets *info to 0, which the host reports as an error.
+constexpr long long WAIT_TICKS = 3000000000ll;  // 30 s of the 100 MHz counter
+
+__device__ inline double ld_dev(const double *p)
+{
+    return __longlong_as_double(
+        (long long)__hip_atomic_load((const unsigned long long *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+__device__ inline void st_dev(double *p, double v)
+{
+    __hip_atomic_store((unsigned long long *)p, (unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// One thread: until prog[i] >= vi and prog[m] >= vm; false if the wait ran out.
+__device__ inline bool wait_prog(const int *prog, int i, int vi, int m, int vm, unsigned long long *info)
+{
+    const long long t0 = wall_clock64();
+    for (unsigned k = 1;; ++k) {
+        const int a = __hip_atomic_load(prog + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int c = __hip_atomic_load(prog + m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (a >= vi && c >= vm) return true;
+        __builtin_amdgcn_s_sleep(1);
+        if ((k & 255) == 0 && (__hip_atomic_load(info, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0 ||
+                               wall_clock64() - t0 > WAIT_TICKS)) {
+            atomicMin(info, 0ull);
+            return false;
+        }
+    }
+}
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void potrf_tile_kernel(double *tile, int b, int64_t col0, int64_t n, int *ctl,
                                                          unsigned long long *info)
 {
     __builtin_amdgcn_s_setprio(3);  // the panel chain: issue ahead of update waves sharing the SIMD
-    __shared__ double a[64][65];
-    const int r = threadIdx.x;
-    double *base = tile + j0 + (int64_t)j0 * b;
-#pragma nounroll
-    for (int h = 0; h < 64; h += 16) {
-        double x[16];  // x[j] = A(j0 + r, j0 + h + j)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) x[j] = base[r + (int64_t)(h + j) * b];
-        for (int c = 0; c < h; ++c) {  // less L(r, 0:h) L(h+j, 0:h)^T
-            const double lrc = a[c][r];
-#pragma unroll
-            for (int j = 0; j < 16; ++j) x[j] -= lrc * a[c][h + j];
-        }
-#pragma unroll
-        for (int c = 0; c < 16; ++c) {
-            a[h + c][r] = x[c];
-            wave_sync();
-            const double d = a[h + c][h + c];
-            if (r == 0 && !(d > 0.0) && col0 + j0 + h + c < n)
-                atomicMin(info, (unsigned long long)(col0 + j0 + h + c + 1));
-            const double piv = sqrt(d);
-            x[c] = (r == h + c) ? piv : x[c] / piv;
-            wave_sync();
-            a[h + c][r] = x[c];
-            wave_sync();
-#pragma unroll
-            for (int j = c + 1; j < 16; ++j) x[j] -= x[c] * a[h + c][h + j];
-        }
-#pragma unroll
-        for (int j = 0; j < 16; ++j) base[r + (int64_t)(h + j) * b] = (r >= h + j) ? x[j] : 0.0;
-        wave_sync();
+    __shared__ double A[64 * LD64], Bs[64 * LD64];
+    __shared__ double inv[64], scratch[4][16 * 17];
+    __shared__ int s_word;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, gi = lane & 15, gg = lane >> 4;
+    const int nb = b / 64;
+    int *prog = ctl + 1;
+    if (tid == 0) s_word = atomicAdd(ctl, 1);
+    __syncthreads();
+    int m = 0, i = __builtin_amdgcn_readfirstlane(s_word);  // column order: diagonal m, then (i, m) for i = m + 2 .. nb - 1
+    for (;; ++m) {
+        const int cnt = 1 + max(0, nb - 2 - m);
+        if (i < cnt) break;
+        i -= cnt;
     }
+    const bool diag = i == 0;
+    i = diag ? m : m + 1 + i;
+    const int ca = diag ? m - 1 : m;  // column of the block solved here (none for m = 0 on the diagonal)
+    __syncthreads();
+
+    // block (r, c); within a block a uniform column base plus a lane's 32-bit byte offset
+    const int64_t cs = (int64_t)b * 8;
+    auto at = [&](int r, int c) { return (char *)tile + (int64_t)(64 * r) * 8 + 64 * c * cs; };
+    const uint32_t own8 = (wave * 16 + gi + gg * b) * 8, lin8 = (lane + wave * b) * 8;
+    // the blocks themselves start the sums, negated; the mirrored block above the diagonal becomes zero
+    double4_t acc1[4], acc2[4];
+#pragma unroll
+    for (int ct = 0; ct < 4; ++ct) acc1[ct] = acc2[ct] = (double4_t){0.0, 0.0, 0.0, 0.0};
+    if (ca >= 0) {
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc1[q / 4][q % 4] = -*(const double *)(at(i, ca) + 4 * q * cs + own8);
+    }
+    if (diag) {
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc2[q / 4][q % 4] = -*(const double *)(at(i, i) + 4 * q * cs + own8);
+    }
+    if (ca >= 0) {
+        char *up = at(ca, i);
+        for (int q = 0; q < 16; ++q) *(double *)(up + 4 * q * cs + lin8) = 0.0;
+    }
+
+    double ra[16], rb[16];
+    auto load = [&](int j) {
+        const char *pa = at(i, j), *pb = at(ca, j);
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            ra[q] = ld_dev((const double *)(pa + 4 * q * cs + lin8));
+            rb[q] = ld_dev((const double *)(pb + 4 * q * cs + lin8));
+        }
+    };
+    int have = 0;
+    for (int j = 0; j < ca; ++j) {
+        if (j >= have) {
+            if (tid == 0) {
+                int ok = wait_prog(prog, i, j + 1, ca, j + 1, info);
+                if (ok) ok = min(__hip_atomic_load(prog + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                                 __hip_atomic_load(prog + ca, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+                s_word = ok;
+            }
+            __syncthreads();
+            have = s_word;
+            if (have == 0) return;
+            load(j);
+        }
+        __syncthreads();  // the previous products have been read from LDS
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            A[(wave + 4 * q) * LD64 + lane] = ra[q];
+            Bs[(wave + 4 * q) * LD64 + lane] = rb[q];
+        }
+        __syncthreads();
+        if (j + 1 < ca && j + 1 < have) load(j + 1);
+        mma64(acc1, A, Bs, wave, gi, gg);
+        if (diag) mma64(acc2, A, A, wave, gi, gg);
+    }
+
+    if (ca >= 0) {
+        // L(ca, ca) into Bs, then this block's solve
+        if (tid == 0) s_word = wait_prog(prog, ca, ca + 1, ca, ca + 1, info);
+        __syncthreads();
+        if (!s_word) return;
+        const char *pl = at(ca, ca);
+        const double d = ld_dev((const double *)(pl + (uint32_t)((lane + lane * b) * 8)));
+#pragma unroll
+        for (int q = 0; q < 16; ++q) rb[q] = ld_dev((const double *)(pl + 4 * q * cs + lin8));
+#pragma unroll
+        for (int q = 0; q < 16; ++q) Bs[(wave + 4 * q) * LD64 + lane] = rb[q];
+        if (wave == 0) inv[lane] = 1.0 / d;
+        __syncthreads();
+        char *px = at(i, ca);
+        wave_trsm64(acc1, Bs, inv, scratch[wave], gi, gg, [&](int p, int t, double v) {
+            st_dev((double *)(px + (16 * p + 4 * t) * cs + own8), v);
+            if (diag) A[(16 * p + 4 * t + gg) * LD64 + wave * 16 + gi] = v;
+        });
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's stores have completed
+        __syncthreads();
+        if (tid == 0) __hip_atomic_store(prog + i, ca + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (!diag) return;
+    if (ca >= 0) mma64(acc2, A, A, wave, gi, gg);
+    // the diagonal block: Bs is free, every wave is past its solve
+#pragma unroll
+    for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) Bs[(ct * 16 + gg + 4 * v) * LD64 + wave * 16 + gi] = -acc2[ct][v];
+    __syncthreads();
+    block_potrf64(Bs, wave, lane, col0 + 64 * (int64_t)m, n, info);
+    char *pd = at(m, m);
+#pragma unroll
+    for (int q = 0; q < 16; ++q) st_dev((double *)(pd + 4 * q * cs + lin8), Bs[(wave + 4 * q) * LD64 + lane]);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) __hip_atomic_store(prog + m, m + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Words of control memory per diagonal tile: the ticket and the block rows'
+// counts; all zero before the tile's launch.
+int potrf_ctl_words(int b) { return 1 + b / 64; }
+
+void launch_potrf_tile(const Tiles &T, int k, int *ctl, unsigned long long *info, hipStream_t st)
+{
+    const int b = T.b, nb = b / 64;
+    double *tile = (double *)(T.slots + tile_index(k, k) * T.slot_bytes);
+    const int off = (nb - 1) * (nb - 2) / 2;  // blocks two or more below the diagonal
+    potrf_tile_kernel<<<nb + off, 256, 0, st>>>(tile, b, (int64_t)k * b, T.n, ctl + (int64_t)k * potrf_ctl_words(b), info);
 }
 
 // ---------------------------------------------------------------- TRSM
-// X = W L^-T for strips of 64 rows (X L^T = W, L lower nL x nL, FP64), four
-// waves per strip, each owning 16 rows.  Column blocks of 32: the block's
-// right-hand side W - X_left L_row^T is formed with FP64 MFMA from the
-// already solved columns -- each wave reads its own rows of X and the L rows
-// straight into registers, the next 48 columns of K in flight while the
-// current ones are multiplied, with no barrier inside the K loop -- then
-// solved by forward substitution against the 32 x 32 diagonal block, one row
-// per lane in registers.
-// mode 0: the panel of step k -- item I = k+1+blockIdx.y, W = tile (I,k) in
-//         its work precision (FP64, or FP32 for lower classes), X = p64[I];
-//         the strip's largest |X| is folded into pmax[I] (atomic max of the
-//         FP64 bits, which order like the values; the caller zeroes pmax),
-//         and the first column holding an Inf or NaN into P.info (every
-//         off-diagonal factor tile passes here, so a non-finite value is
-//         reported even where a low-precision code would saturate it);
-// mode 1: one FP64 strip set in place (W = X = xin, leading dimension ldin).
-// nL is a multiple of 32.
-__global__ __launch_bounds__(256) void trsm_kernel(Tiles T, Panel P, int k, const double *__restrict__ L, int64_t ldl,
-                                                   int nL, double *xin, int64_t ldin, int mode)
+// The panel of step k: X = W L^-T for 64-row strips of the tiles I > k, W the
+// work tile (FP64, or FP32 for lower classes), X = p64[I].  Four waves, each
+// its own 16 rows from end to end: column blocks of 64, whose product with the
+// solved columns runs on the FP64 MFMA straight from registers (X and L, three
+// chunks of 16 columns in flight, no barrier), then the substitution of
+// wave_trsm64; the waves only share the diagonal block in LDS.  What bounds a
+// strip is its b / 64 column blocks in sequence, what bounds many strips the
+// MFMA (248 strips of 512 columns: 0.33 -> 0.15 ms, where the products alone take
+// 0.055 ms on their compute unit).  The strip's largest |X| is folded into pmax[I] (atomic max of the FP64
+// bits, which order like the values; the caller zeroes pmax), and the first
+// column holding an Inf or NaN into P.info (every off-diagonal factor tile
+// passes here, so a non-finite value is reported even where a low-precision
+// code would saturate it).
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void trsm_kernel(Tiles T, Panel P, int k, const double *__restrict__ L)
 {
     __builtin_amdgcn_s_setprio(3);  // the panel chain: issue ahead of update waves sharing the SIMD
-    __shared__ double ts[32][64 + 1];  // right-hand side / solution: ts[c][row]
-    __shared__ double lb[32][33];      // diagonal block: lb[cc][c] = L(cb + c, cb + cc)
-    const void *W;
-    bool wf32 = false;
-    int64_t ldw, ldx;
-    double *X;
-    if (mode == 0) {
-        const int I = k + 1 + blockIdx.y;
-        wf32 = T.map[I + (int64_t)k * T.nt] != P64;
-        W = T.slots + tile_index(I, k) * T.slot_bytes;
-        ldw = T.b;
-        X = P.p64 + (int64_t)I * T.b * T.b;
-        ldx = T.b;
-    } else {
-        W = xin;
-        ldw = ldin;
-        X = xin;
-        ldx = ldin;
-    }
+    __shared__ double Ls[64 * LD64];
+    __shared__ double inv[64], scratch[4][16 * 17];
+    const int b = T.b, I = k + 1 + blockIdx.y;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, gi = lane & 15, gg = lane >> 4;
+    const bool wf32 = T.map[I + (int64_t)k * T.nt] != P64;
+    // addresses: a uniform column base plus a lane's 32-bit byte offset
     const int row0 = blockIdx.x * 64;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int gi = lane & 15, gg = lane >> 4;
-    double *Xs = X + row0;
-    double xmax = 0.0;     // wave 0: largest |X| written
-    int bad = 0x7FFFFFFF;  // wave 0: first column (in the tile) of a non-finite X written
-
-    for (int cb = 0; cb < nL; cb += 32) {
-        // this column block's right-hand side and diagonal block, read before
-        // the K loop so that their latency overlaps its first loads
-        double wv[4][2], lv[4];
+    const char *W = T.slots + tile_index(I, k) * T.slot_bytes + (int64_t)row0 * (wf32 ? 4 : 8);
+    char *X = (char *)(P.p64 + (int64_t)I * b * b + row0);
+    const char *Lc = (const char *)L;
+    const uint32_t own = wave * 16 + gi + gg * b;  // row gi of the wave, column gg
+    const uint32_t own8 = own * 8, own4 = own * 4, lop8 = (gi + gg * b) * 8, dia8 = (lane + wave * b) * 8;
+    const int64_t cs = (int64_t)b * 8;  // bytes from column to column
+    double xmax = 0.0;     // largest |X| of this lane's row
+    int bad = 0x7FFFFFFF;  // first column (in the tile) of a non-finite X
+    double lv[16], dv;     // the next diagonal block and its diagonal, read ahead
+    auto load_diag = [&](int cb) {
+        dv = *(const double *)(Lc + (int64_t)cb * 8 + cb * cs + (lane + lane * b) * 8);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int r = wave * 16 + acc_row<double>(gg, v);
-            const int64_t o0 = (int64_t)(row0 + r) + (int64_t)(cb + gi) * ldw;
-            const int64_t o1 = o0 + 16 * ldw;
-            wv[v][0] = wf32 ? (double)((const float *)W)[o0] : ((const double *)W)[o0];
-            wv[v][1] = wf32 ? (double)((const float *)W)[o1] : ((const double *)W)[o1];
+        for (int q = 0; q < 16; ++q) lv[q] = *(const double *)(Lc + (int64_t)cb * 8 + (cb + 4 * q) * cs + dia8);
+    };
+    load_diag(0);
+    for (int cb = 0; cb < b; cb += 64) {
+#pragma unroll
+        for (int q = 0; q < 16; ++q) Ls[(wave + 4 * q) * LD64 + lane] = lv[q];
+        if (wave == 0) inv[lane] = 1.0 / dv;
+        // right-hand side, read ahead of the products
+        double4_t w[4], acc[4];
+        if (wf32) {
+#pragma unroll
+            for (int q = 0; q < 16; ++q)
+                w[q / 4][q % 4] = (double)*(const float *)(W + (cb + 4 * q) * (cs / 2) + own4);
+        } else {
+#pragma unroll
+            for (int q = 0; q < 16; ++q) w[q / 4][q % 4] = *(const double *)(W + (cb + 4 * q) * cs + own8);
         }
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int e = tid + 256 * q, c = e & 31, cc = e >> 5;
-            lv[q] = L[(cb + c) + (int64_t)(cb + cc) * ldl];
-        }
-        double4_t acc0 = {0.0, 0.0, 0.0, 0.0}, acc1 = {0.0, 0.0, 0.0, 0.0};
-        // MFMA k-step kk (4 columns of K): a = X(row0 + 16 wave + gi, kk + gg),
-        // b_n = L(cb + 16 n + gi, kk + gg); chunks of four k-steps
-        const double *xa = Xs + wave * 16 + gi + (int64_t)gg * ldx;
-        const double *lp = L + (cb + gi) + (int64_t)gg * ldl;
-        double a0[4], b0[4][2], a1[4], b1[4][2], a2[4], b2[4][2], a3[4], b3[4][2];
-        // offsets within one tile (below b * b), kept in 32 bits
-        const int ldx32 = (int)ldx, ldl32 = (int)ldl;
-        auto load = [&](int kc, double(&a)[4], double(&bv)[4][2]) {
+        for (int ct = 0; ct < 4; ++ct) acc[ct] = (double4_t){0.0, 0.0, 0.0, 0.0};
+        // MFMA step s of a chunk: columns 8 kc + 4 s + gg of X and L
+        struct Chunk {
+            double a[2], l[2][4];
+        } c0, c1, c2, c3;
+        auto load = [&](int kc, Chunk &c) {
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const int kk = kc * 16 + 4 * s;
-                a[s] = xa[kk * ldx32];
-                bv[s][0] = lp[kk * ldl32];
-                bv[s][1] = lp[16 + kk * ldl32];
+            for (int s = 0; s < 2; ++s) {
+                const int64_t o = (kc * 8 + 4 * s) * cs;
+                c.a[s] = *(const double *)(X + o + own8);
+#pragma unroll
+                for (int ct = 0; ct < 4; ++ct)
+                    c.l[s][ct] = *(const double *)(Lc + o + (int64_t)(cb + ct * 16) * 8 + lop8);
             }
         };
-        auto mma = [&](const double(&a)[4], const double(&bv)[4][2]) {
+        auto mma = [&](const Chunk &c) {
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], bv[s][0], acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], bv[s][1], acc1, 0, 0, 0);
-            }
+            for (int s = 0; s < 2; ++s)
+#pragma unroll
+                for (int ct = 0; ct < 4; ++ct)
+                    acc[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(c.l[s][ct], c.a[s], acc[ct], 0, 0, 0);
         };
-        // three chunks in flight (a chunk is 512 cycles of MFMA work, well
-        // short of a load's latency); nc is even
-        const int nc = cb / 16;
-        if (nc > 0) {
-            load(0, a0, b0);
-            load(1, a1, b1);
-            if (nc > 2) load(2, a2, b2);
-            for (int kc = 0; kc < nc; kc += 4) {
-                if (kc + 3 < nc) load(kc + 3, a3, b3);
-                mma(a0, b0);
-                if (kc + 4 < nc) load(kc + 4, a0, b0);
-                mma(a1, b1);
-                if (kc + 2 >= nc) break;
-                if (kc + 5 < nc) load(kc + 5, a1, b1);
-                mma(a2, b2);
-                if (kc + 6 < nc) load(kc + 6, a2, b2);
-                mma(a3, b3);
+        if (cb > 0) {
+            const int nc = cb / 8;  // a multiple of eight
+            load(0, c0);
+            load(1, c1);
+            load(2, c2);
+            for (int kc = 0;; kc += 4) {
+                load(kc + 3, c3);
+                mma(c0);
+                if (kc + 4 >= nc) break;
+                load(kc + 4, c0);
+                mma(c1);
+                load(kc + 5, c1);
+                mma(c2);
+                load(kc + 6, c2);
+                mma(c3);
             }
+            mma(c1);
+            mma(c2);
+            mma(c3);
         }
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int r = wave * 16 + acc_row<double>(gg, v);
-            ts[gi][r] = wv[v][0] - acc0[v];
-            ts[16 + gi][r] = wv[v][1] - acc1[v];
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int e = tid + 256 * q, c = e & 31, cc = e >> 5;
-            lb[cc][c] = lv[q];
-        }
-        __syncthreads();
-        if (wave == 0) {
-            double t[32];
-#pragma unroll
-            for (int c = 0; c < 32; ++c) t[c] = ts[c][lane];
-            // column by column: once x_c is final it is divided out and
-            // subtracted from every later column of the row -- each x_j still
-            // receives its terms in increasing c, then its division, but the
-            // updates of different j are independent of each other
-#pragma unroll
-            for (int c = 0; c < 32; ++c) {
-                t[c] = t[c] / lb[c][c];
-#pragma unroll
-                for (int j = c + 1; j < 32; ++j) t[j] -= t[c] * lb[c][j];
-            }
-#pragma unroll
-            for (int c = 0; c < 32; ++c) {
-                Xs[lane + (int64_t)(cb + c) * ldx] = t[c];
-                xmax = fmax(xmax, fabs(t[c]));
-                if (!(fabs(t[c]) <= 1.7976931348623157e308)) bad = min(bad, cb + c);
-            }
-        }
-        __syncthreads();  // the solved columns are read back by the next column block
+        for (int ct = 0; ct < 4; ++ct) acc[ct] -= w[ct];
+        __syncthreads();  // the diagonal block is in LDS
+        if (cb + 64 < b) load_diag(cb + 64);
+        wave_trsm64(acc, Ls, inv, scratch[wave], gi, gg, [&](int p, int t, double v) {
+            const int c = cb + 16 * p + 4 * t;
+            *(double *)(X + c * cs + own8) = v;
+            xmax = fmax(xmax, fabs(v));
+            if (!(fabs(v) <= 1.7976931348623157e308)) bad = min(bad, c + gg);
+        });
+        __syncthreads();  // the diagonal block has been read; the next one reads these columns through other lanes
     }
-    if (mode == 0 && wave == 0) {
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) xmax = fmax(xmax, __shfl_xor(xmax, off));
-        if (lane == 0) atomicMax(P.pmax + k + 1 + blockIdx.y, (unsigned long long)__double_as_longlong(xmax));
+    for (int off = 32; off > 0; off >>= 1) xmax = fmax(xmax, __shfl_xor(xmax, off));
+    if (lane == 0) atomicMax(P.pmax + I, (unsigned long long)__double_as_longlong(xmax));
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) bad = min(bad, __shfl_xor(bad, off));
-        if (lane == 0 && bad != 0x7FFFFFFF && P.info)
-            atomicMin(P.info, (unsigned long long)((int64_t)k * T.b + bad + 1));
-    }
-}
-
-// ---------------------------------------------------------------- SYRK inside a diagonal tile
-// C -= X X^T on the lower 64 x 64 blocks of an M x M FP64 block (K = 64).
-__global__ __launch_bounds__(256) void syrk_tile_kernel(const double *X, double *Cm, int b, int nblk)
-{
-    __builtin_amdgcn_s_setprio(3);  // the panel chain: issue ahead of update waves sharing the SIMD
-    extern __shared__ __align__(16) char smem_raw[];
-    // block (bi, bj), bi >= bj, from the linear index
-    int t = blockIdx.x;
-    int bi = (int)((sqrt(8.0 * t + 1.0) - 1.0) * 0.5);
-    while ((bi + 1) * (bi + 2) / 2 <= t) ++bi;
-    while (bi * (bi + 1) / 2 > t) --bi;
-    int bj = t - bi * (bi + 1) / 2;
-    double4_t acc[2][2];
-    for (int m = 0; m < 2; ++m)
-        for (int nn = 0; nn < 2; ++nn) acc[m][nn] = (double4_t){0.0, 0.0, 0.0, 0.0};
-    cm_block<double, 64, 64, 16>(X + bi * 64, b, X + bj * 64, b, 64, acc, (double *)smem_raw);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = wave & 1, wn = wave >> 1, gi = lane & 15, gg = lane >> 4;
-    double *C = Cm + bi * 64 + (int64_t)bj * 64 * b;
-    for (int m = 0; m < 2; ++m)
-        for (int nn = 0; nn < 2; ++nn)
-            for (int v = 0; v < 4; ++v) {
-                int r = wm * 32 + m * 16 + acc_row<double>(gg, v), c = wn * 32 + nn * 16 + gi;
-                C[r + (int64_t)c * b] -= acc[m][nn][v];
-            }
-}
-
-void launch_potrf_tile(const Tiles &T, int k, unsigned long long *info, hipStream_t st)
-{
-    const int b = T.b;
-    double *tile = (double *)(T.slots + tile_index(k, k) * T.slot_bytes);
-    Panel none{};
-    for (int j0 = 0; j0 < b; j0 += 64) {
-        potrf_block_kernel<<<1, 64, 0, st>>>(tile, b, j0, (int64_t)k * b, T.n, info);
-        const int M = b - j0 - 64;
-        if (M <= 0) break;
-        double *xin = tile + (j0 + 64) + (int64_t)j0 * b;
-        trsm_kernel<<<dim3(M / 64, 1), 256, 0, st>>>(T, none, k, tile + j0 + (int64_t)j0 * b, b, 64, xin, b, 1);
-        const int nblk = M / 64;
-        syrk_tile_kernel<<<nblk * (nblk + 1) / 2, 256, CMShape<double, 64, 64, 16>::SMEM, st>>>(
-            xin, tile + (j0 + 64) + (int64_t)(j0 + 64) * b, b, nblk);
-    }
-    launch_zero_upper_diag(T, k, st);
+    for (int off = 32; off > 0; off >>= 1) bad = min(bad, __shfl_xor(bad, off));
+    if (lane == 0 && bad != 0x7FFFFFFF) atomicMin(P.info, (unsigned long long)((int64_t)k * T.b + bad + 1));
 }
 
 void launch_trsm_panel(const Tiles &T, const Panel &P, int k, hipStream_t st)
@@ -267,7 +571,7 @@ void launch_trsm_panel(const Tiles &T, const Panel &P, int k, hipStream_t st)
     const int np = T.nt - k - 1;
     if (np <= 0) return;
     const double *L = (const double *)(T.slots + tile_index(k, k) * T.slot_bytes);
-    trsm_kernel<<<dim3(T.b / 64, np), 256, 0, st>>>(T, P, k, L, T.b, T.b, nullptr, 0, 0);
+    trsm_kernel<<<dim3(T.b / 64, np), 256, 0, st>>>(T, P, k, L);
 }
 
 // ---------------------------------------------------------------- grouped trailing update

@@ -225,12 +225,6 @@ __global__ __launch_bounds__(256) void get_factor_kernel(Tiles T, double *L, int
     }
 }
 
-__global__ __launch_bounds__(256) void zero_upper_kernel(double *tile, int b)
-{
-    const int c = blockIdx.x;
-    for (int r = threadIdx.x; r < c; r += 256) tile[r + (int64_t)c * b] = 0.0;
-}
-
 // ---------------------------------------------------------------- launchers
 static inline int64_t ntiles(const Tiles &T) { return (int64_t)T.nt * (T.nt + 1) / 2; }
 
@@ -264,12 +258,6 @@ void launch_logdet(const Tiles &T, double *out, hipStream_t st) { logdet_kernel<
 void launch_get_factor(const Tiles &T, double *L, int64_t ldl, hipStream_t st)
 {
     get_factor_kernel<<<dim3((unsigned)((T.n + 255) / 256), (unsigned)std::min<int64_t>(T.n, 4096)), 256, 0, st>>>(T, L, ldl);
-}
-
-void launch_zero_upper_diag(const Tiles &T, int k, hipStream_t st)
-{
-    double *tile = (double *)(T.slots + tile_index(k, k) * T.slot_bytes);
-    zero_upper_kernel<<<T.b, 256, 0, st>>>(tile, T.b);
 }
 
 }  // namespace mpc

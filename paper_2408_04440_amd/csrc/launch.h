@@ -53,10 +53,11 @@ void launch_copy_matrix(const Tiles &T, const double *A, int64_t lda, double *or
 void launch_convert(const Tiles &T, const Panel &P, int k, const uint8_t *qmask, hipStream_t st);
 void launch_logdet(const Tiles &T, double *out, hipStream_t st);
 void launch_get_factor(const Tiles &T, double *L, int64_t ldl, hipStream_t st);
-void launch_zero_upper_diag(const Tiles &T, int k, hipStream_t st);
 
 // ---- factorization (k_factor.hip)
-void launch_potrf_tile(const Tiles &T, int k, unsigned long long *info, hipStream_t st);
+// ctl: nt * potrf_ctl_words(b) words, all zero before the first tile of a factorization
+int potrf_ctl_words(int b);
+void launch_potrf_tile(const Tiles &T, int k, int *ctl, unsigned long long *info, hipStream_t st);
 void launch_trsm_panel(const Tiles &T, const Panel &P, int k, hipStream_t st);
 // grouped update A_IJ -= sum_h L_I,k_h L_J,k_h^T of class q over `nitems` packed (I << 16 | J)
 // items from the npan panels Ps[0..npan-1] (npan <= 2 for FP64 and FP32-MFMA, <= 4 otherwise);

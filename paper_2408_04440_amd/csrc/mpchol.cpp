@@ -75,6 +75,7 @@ struct mpchol_handle {
     unsigned long long *d_info = nullptr;
     double *d_scalar = nullptr;
     int *d_solve = nullptr;      // tickets and finished counts of the solves
+    int *d_potrf = nullptr;      // the same of the diagonal tiles' factorizations
     std::vector<uint8_t> h_map;
     std::vector<double> h_fro2, h_amax;
     double total_fro = 0;
@@ -218,7 +219,7 @@ static void release(mpchol_handle *h)
 {
     void *ptrs[] = {h->slots, h->orig, h->d_sigma, h->d_x, h->p64, h->p32, h->p32s, h->p16, h->p8, h->p8x, h->pmax, h->pscale,
                     h->poz, h->pexp, h->d_ozc,
-                    h->d_map, h->d_tscale, h->d_fro2, h->d_amax, h->d_info, h->d_scalar, h->d_solve, h->d_items, h->d_qmask,
+                    h->d_map, h->d_tscale, h->d_fro2, h->d_amax, h->d_info, h->d_scalar, h->d_solve, h->d_potrf, h->d_items, h->d_qmask,
                     h->d_all_items, h->d_partial, h->d_tres2, h->d_params, h->d_feats, h->d_est, h->d_zbuf};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
@@ -330,6 +331,7 @@ int mpchol_create(mpchol_t *hp, int64_t n, int32_t tile, const mpchol_opts *o)
     A(dalloc(&h->d_info, 8));
     A(dalloc(&h->d_scalar, 64));
     A(dalloc(&h->d_solve, solve_ctl_bytes()));
+    A(dalloc(&h->d_potrf, nt * potrf_ctl_words(tile) * sizeof(int)));
     A(dalloc(&h->d_qmask, nt * nt));
     A(dalloc(&h->d_all_items, h->ntile * 4));
     A(dalloc(&h->d_partial, h->ntile * (bb / (128 * 128)) * 8));
@@ -797,13 +799,13 @@ static int update_list(mpchol_handle *h, const Tiles &T, const Panel *P, int p, 
 static int panel_pair(mpchol_handle *h, const Tiles &T, const Panel *P, int c, hipStream_t st)
 {
     const int nt = h->nt;
-    launch_potrf_tile(T, c, h->d_info, st);
+    launch_potrf_tile(T, c, h->d_potrf, h->d_info, st);
     if (c + 1 >= nt) return MPCHOL_OK;
     int rc = panel_step(h, T, P[c % NSET], c, st);
     if (rc) return rc;
     rc = update_list(h, T, P, c / 2, 0, st);
     if (rc) return rc;
-    launch_potrf_tile(T, c + 1, h->d_info, st);
+    launch_potrf_tile(T, c + 1, h->d_potrf, h->d_info, st);
     if (c + 2 < nt) rc = panel_step(h, T, P[(c + 1) % NSET], c + 1, st);
     return rc;
 }
@@ -826,6 +828,7 @@ static int run_factor(mpchol_handle *h, int64_t *info)
     h->gev_class.clear();
     h->gev_flops.clear();
     HIPCHK(hipMemsetAsync(h->d_info, 0xFF, 8, A));
+    HIPCHK(hipMemsetAsync(h->d_potrf, 0, (size_t)nt * potrf_ctl_words(h->b) * sizeof(int), A));
     HIPCHK(hipEventRecord(h->ev[0], A));
     int rc = panel_pair(h, T, P, 0, A);
     if (rc) return rc;
@@ -846,6 +849,11 @@ static int run_factor(mpchol_handle *h, int64_t *info)
     HIPCHK(hipMemcpyAsync(&hinfo, h->d_info, 8, hipMemcpyDeviceToHost, A));
     HIPCHK(hipStreamSynchronize(A));
     HIPCHK(hipGetLastError());
+    if (hinfo == 0) {  // a wait inside a diagonal tile ran out
+        snprintf(g_last_error, sizeof(g_last_error), "mpchol_factor: a diagonal tile's workgroups stopped waiting");
+        h->state = S_FAILED;
+        return MPCHOL_EHIP;
+    }
     float ms = 0;
     HIPCHK(hipEventElapsedTime(&ms, h->ev[0], h->ev[1]));
     h->stats.t_factor_ms = ms;

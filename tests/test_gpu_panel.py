@@ -1,0 +1,45 @@
+"""The diagonal tile's POTRF and the panel TRSM at every number of 64-blocks a
+tile can have at its ends (2 and 32 per tile, and odd counts of 128), and for
+pivots outside the range of the in-kernel square root."""
+import numpy as np
+import pytest
+
+import synth
+from _gpu import M, factor_dense
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("tile,n,exp2", [
+    (128, 128, 0), (128, 129, 0), (384, 1000, 0), (640, 640, 0), (2048, 2048, 0), (1152, 2400, 0),
+    (128, 300, -910), (256, 600, 920), (384, 500, -901), (128, 300, -899), (128, 300, 899)])
+def test_factor_of_scaled_integers_is_exact(tile, n, exp2):
+    """A = S S^T, S = 2^(exp2 // 2) L0 with a small integer L0: the factor is S
+    bit for bit, whichever way a pivot is taken."""
+    mod = M()
+    L0 = synth.int_lower(n, 5) * 2.0 ** (exp2 // 2)
+    h = mod.mpchol_create(n, tile)
+    try:
+        mod.mpchol_set_matrix(h, L0 @ L0.T)
+        mod.mpchol_precision_map(h, mod.RULE_FP64)
+        assert mod.mpchol_factor(h) == 0
+        assert np.array_equal(factor_dense(h, n), L0)
+    finally:
+        mod.mpchol_destroy(h)
+
+
+@pytest.mark.parametrize("tile,n,col,val", [(256, 600, 70, -1.0), (256, 600, 255, 0.0), (512, 512, 511, -2.0),
+                                            (128, 300, 299, float("nan"))])
+def test_bad_pivot_column(tile, n, col, val):
+    """A diagonal entry lowered so that exactly its pivot fails: info is its 1-based column."""
+    mod = M()
+    L0 = synth.int_lower(n, 6)
+    A = L0 @ L0.T
+    A[col, col] = A[col, col] - L0[col, col] ** 2 + val
+    h = mod.mpchol_create(n, tile)
+    try:
+        mod.mpchol_set_matrix(h, A)
+        mod.mpchol_precision_map(h, mod.RULE_FP64)
+        assert mod.mpchol_factor(h) == col + 1
+    finally:
+        mod.mpchol_destroy(h)
