@@ -83,6 +83,9 @@ template <int C> __device__ inline void row_update(double (&t)[16], double s, do
     else if constexpr (C == 14) MPC_ROW_ASM(MPC_FROM_15);
 }
 
+// All of this wave's global stores have completed.
+__device__ inline void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // x / d given r, 1 / d to at least half of its bits: one correction by the
 // exact remainder, which returns an exactly representable quotient exactly.
 __device__ inline double div_by(double x, double d, double r)
@@ -105,10 +108,11 @@ __device__ inline void sqrt_rcp(double d, double &s, double &r)
     r = h + h;
 }
 
-// acc[ct] += X(rows 16w.., k) Y(rows 16ct.., k)^T over 64 columns of the LDS
-// blocks.  Operands swapped: a lane holds row gi of its wave's 16 and
+// acc[ct] += X(rows 16w.., k) Y(rows 16ct.., k)^T over columns k0 .. k1 - 1 (a
+// multiple of 16) of the LDS blocks.  Operands swapped: a lane holds row gi of its wave's 16 and
 // columns gg + 4v of each 16-column tile.
-__device__ inline void mma64(double4_t (&acc)[4], const double *X, const double *Y, int wave, int gi, int gg)
+__device__ inline void mma64(double4_t (&acc)[4], const double *X, const double *Y, int wave, int gi, int gg,
+                             int k0 = 0, int k1 = 64)
 {
     struct Ops {
         double x[2], y[2][4];
@@ -129,65 +133,61 @@ __device__ inline void mma64(double4_t (&acc)[4], const double *X, const double 
             for (int ct = 0; ct < 4; ++ct)
                 acc[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(o.y[s][ct], o.x[s], acc[ct], 0, 0, 0);
     };
-    load(0, u);
+    load(k0, u);
 #pragma unroll 1
-    for (int k = 0; k < 64; k += 16) {  // the next eight columns are read while eight are multiplied
+    for (int k = k0; k < k1; k += 16) {  // the next eight columns are read while eight are multiplied
         load(k + 8, w);
         mma(u);
-        if (k < 48) load(k + 16, u);
+        if (k + 16 < k1) load(k + 16, u);
         mma(w);
     }
 }
 
-// X = -acc L^-T for a wave's 16 rows: L the lower 64 x 64 block in LDS,
-// inv[c] = 1 / L(c, c), acc the negated 16 x 64 right-hand side.  Column panels of 16:
-// every lane gathers its row of the panel (the four lane groups hold the same
-// rows), substitutes column by column against broadcasts of the diagonal
-// block's rows from other lanes, and the panel's
-// product with the rest of L goes to the later panels' accumulators on the
-// MFMA.  put(p, t, v): lane (gi, gg) delivers X(gi, 16 p + 4 t + gg).
+// Panel p of X = -acc L^-T for a wave's 16 rows: L the lower 64 x 64 block in
+// LDS (its columns 16 p .. 16 p + 15 are read), rl = 1 / L(16 p + gi, 16 p + gi),
+// acc the negated 16 x 64 right-hand side, acc[0] the current 16 columns: the
+// later panels' sums move up by one, so that the four panels share one copy of
+// the code (a diagonal workgroup runs it once, and four copies cost more in
+// instruction fetches than the moves).  Every lane gathers its row of the panel
+// (the four lane groups hold the same rows) and substitutes column by column
+// against broadcasts of the diagonal block's rows from other lanes; the
+// panel's product with the rest of L goes to the later sums on the MFMA.
+// put(t, v): lane (gi, gg) delivers X(gi, 16 p + 4 t + gg).
 template <typename Put>
-__device__ inline void wave_trsm64(double4_t (&acc)[4], const double *L, const double *inv, double *scratch, int gi,
+__device__ inline void wave_trsm16(double4_t (&acc)[4], int p, const double *L, double rl, double *scratch, int gi,
                                    int gg, Put put)
 {
-    // (the panels share one copy of the code, acc[0] always the current one: a
-    // diagonal workgroup runs it once, and four copies cost more in instruction
-    // fetches than the moves)
-#pragma unroll 1
-    for (int p = 0; p < 4; ++p) {
-        const double *Lp = L + 16 * p * LD64 + 16 * p + gi;
-        double x[16], ld[16];  // lane gi: its row, and row gi of the panel's 16 x 16 diagonal block
-        wave_sync();
+    const double *Lp = L + 16 * p * LD64 + 16 * p + gi;
+    double x[16], ld[16];  // lane gi: its row, and row gi of the panel's 16 x 16 diagonal block
+    wave_sync();
 #pragma unroll
-        for (int v = 0; v < 4; ++v) scratch[gi * 17 + gg + 4 * v] = -acc[0][v];
-        const double rl = inv[16 * p + gi];
+    for (int v = 0; v < 4; ++v) scratch[gi * 17 + gg + 4 * v] = -acc[0][v];
 #pragma unroll
-        for (int c = 0; c < 16; ++c) ld[c] = Lp[c * LD64];
-        wave_sync();
+    for (int c = 0; c < 16; ++c) ld[c] = Lp[c * LD64];
+    wave_sync();
 #pragma unroll
-        for (int c = 0; c < 16; ++c) x[c] = scratch[gi * 17 + c];
-        static_for<0, 16>([&](auto C) {
-            constexpr int c = C;
-            x[c] = div_by(x[c], row_bcast<c>(ld[c]), row_bcast<c>(rl));
-            row_update<c>(x, ld[c], x[c]);
-        });
-        double a[4];
+    for (int c = 0; c < 16; ++c) x[c] = scratch[gi * 17 + c];
+    static_for<0, 16>([&](auto C) {
+        constexpr int c = C;
+        x[c] = div_by(x[c], row_bcast<c>(ld[c]), row_bcast<c>(rl));
+        row_update<c>(x, ld[c], x[c]);
+    });
+    double a[4];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const double x0 = x[4 * t], x1 = x[4 * t + 1], x2 = x[4 * t + 2], x3 = x[4 * t + 3];
-            const double lo = gg & 1 ? x1 : x0, hi = gg & 1 ? x3 : x2;
-            a[t] = gg & 2 ? hi : lo;  // x[4 t + gg]
-            put(p, t, a[t]);
-        }
+    for (int t = 0; t < 4; ++t) {
+        const double x0 = x[4 * t], x1 = x[4 * t + 1], x2 = x[4 * t + 2], x3 = x[4 * t + 3];
+        const double lo = gg & 1 ? x1 : x0, hi = gg & 1 ? x3 : x2;
+        a[t] = gg & 2 ? hi : lo;  // x[4 t + gg]
+        put(t, a[t]);
+    }
 #pragma unroll
-        for (int r = 1; r < 4; ++r) {  // the later panels' sums, moved up by one
-            acc[r - 1] = acc[r];
-            if (p + r < 4) {
+    for (int r = 1; r < 4; ++r) {
+        acc[r - 1] = acc[r];
+        if (p + r < 4) {
 #pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    acc[r - 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(Lp[(4 * t + gg) * LD64 + 16 * r], a[t], acc[r - 1],
-                                                                      0, 0, 0);
-            }
+            for (int t = 0; t < 4; ++t)
+                acc[r - 1] =
+                    __builtin_amdgcn_mfma_f64_16x16x4f64(Lp[(4 * t + gg) * LD64 + 16 * r], a[t], acc[r - 1], 0, 0, 0);
         }
     }
 }
@@ -216,12 +216,16 @@ __device__ __attribute__((noinline)) void panel_potrf16(double *S, int h, int la
 // columns: one wave factors the panel, lane r holding row r, with the panel's
 // diagonal block held once more by every row of 16 lanes for the broadcasts; the
 // later tiles are updated on the MFMA.  Zeros go
-// above the diagonal.  A pivot that is not positive (or NaN) records its
+// above the diagonal.  out(p) runs in every thread once panel p is in LDS,
+// done(p) in every thread after a barrier behind it.  A pivot that is not positive (or NaN) records its
 // 1-based global column col0 + c + 1 in *info (minimum over failures); the
 // computation then continues on NaNs and still terminates.
-__device__ inline void block_potrf64(double *S, int wave, int lane, int64_t col0, int64_t n, unsigned long long *info)
+template <typename Out, typename Done>
+__device__ inline void block_potrf64(double *S, int wave, int lane, int64_t col0, int64_t n, unsigned long long *info,
+                                     Out out, Done done)
 {
     const int gi = lane & 15, gg = lane >> 4;
+#pragma unroll 1
     for (int p = 0; p < 4; ++p) {
         const int h = 16 * p;
         if (wave == 0) {
@@ -253,7 +257,7 @@ __device__ inline void block_potrf64(double *S, int wave, int lane, int64_t col0
             }
         }
         __syncthreads();
-        if (p == 3) break;
+        out(p);
         // lower tiles (rt, ct) of the trailing 64 - h - 16 columns, dealt to the waves
         const int q = 3 - p;
         for (int t = wave; t < q * (q + 1) / 2; t += 4) {
@@ -268,7 +272,9 @@ __device__ inline void block_potrf64(double *S, int wave, int lane, int64_t col0
 #pragma unroll
             for (int v = 0; v < 4; ++v) S[(ct * 16 + gg + 4 * v) * LD64 + rt * 16 + gi] -= a[v];
         }
+        stores_done();
         __syncthreads();
+        done(p);
     }
 }
 
@@ -283,8 +289,9 @@ __device__ inline void block_potrf64(double *S, int wave, int lane, int64_t col0
 //       feeds the second without leaving the compute unit, so the chain crosses
 //       memory once per block;
 //   workgroup (i, m), i >= m + 2: block (i, m).
-// prog[i] counts the finished blocks of block row i (they finish in column
-// order; prog[i] = i + 1 once its diagonal block is factored).  Finished blocks
+// prog[i] counts the finished 16-column panels of block row i: blocks finish in
+// column order, four panels at a time, a diagonal block panel by panel, so that
+// the rows below solve against a panel while the next one is factored.  Finished blocks
 // are written and read with device-scope accesses, and their stores have
 // completed before the count is raised.  Places are given out by a ticket
 // counter in column order, and every block depends on blocks with earlier
@@ -320,16 +327,18 @@ __device__ inline bool wait_prog(const int *prog, int i, int vi, int m, int vm, 
     }
 }
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void potrf_tile_kernel(double *tile, int b, int64_t col0, int64_t n, int *ctl,
-                                                         unsigned long long *info)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void potrf_tile_kernel(
+    double *tile, int b, int64_t col0, int64_t n, int *ctl, unsigned long long *info, unsigned long long *pmax, int npmax)
 {
     __builtin_amdgcn_s_setprio(3);  // the panel chain: issue ahead of update waves sharing the SIMD
     __shared__ double A[64 * LD64], Bs[64 * LD64];
-    __shared__ double inv[64], scratch[4][16 * 17];
+    __shared__ double scratch[4][16 * 17];
     __shared__ int s_word;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, gi = lane & 15, gg = lane >> 4;
     const int nb = b / 64;
     int *prog = ctl + 1;
+    if (blockIdx.x == 0)  // the panel's maxima, which its TRSM collects after this launch
+        for (int q = tid; q < npmax; q += 256) pmax[q] = 0;
     if (tid == 0) s_word = atomicAdd(ctl, 1);
     __syncthreads();
     int m = 0, i = __builtin_amdgcn_readfirstlane(s_word);  // column order: diagonal m, then (i, m) for i = m + 2 .. nb - 1
@@ -377,9 +386,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
     for (int j = 0; j < ca; ++j) {
         if (j >= have) {
             if (tid == 0) {
-                int ok = wait_prog(prog, i, j + 1, ca, j + 1, info);
+                int ok = wait_prog(prog, i, 4 * j + 4, ca, 4 * j + 4, info);
                 if (ok) ok = min(__hip_atomic_load(prog + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
-                                 __hip_atomic_load(prog + ca, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+                                 __hip_atomic_load(prog + ca, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) / 4;
                 s_word = ok;
             }
             __syncthreads();
@@ -400,54 +409,66 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
     }
 
     if (ca >= 0) {
-        // L(ca, ca) into Bs, then this block's solve
-        if (tid == 0) s_word = wait_prog(prog, ca, ca + 1, ca, ca + 1, info);
-        __syncthreads();
-        if (!s_word) return;
         const char *pl = at(ca, ca);
-        const double d = ld_dev((const double *)(pl + (uint32_t)((lane + lane * b) * 8)));
-#pragma unroll
-        for (int q = 0; q < 16; ++q) rb[q] = ld_dev((const double *)(pl + 4 * q * cs + lin8));
-#pragma unroll
-        for (int q = 0; q < 16; ++q) Bs[(wave + 4 * q) * LD64 + lane] = rb[q];
-        if (wave == 0) inv[lane] = 1.0 / d;
-        __syncthreads();
         char *px = at(i, ca);
-        wave_trsm64(acc1, Bs, inv, scratch[wave], gi, gg, [&](int p, int t, double v) {
-            st_dev((double *)(px + (16 * p + 4 * t) * cs + own8), v);
-            if (diag) A[(16 * p + 4 * t + gg) * LD64 + wave * 16 + gi] = v;
-        });
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's stores have completed
+        __syncthreads();  // the last products have been read from LDS
+#pragma unroll 1
+        for (int p = 0; p < 4; ++p) {  // panel p of L(ca, ca) into Bs, then this block's panel
+            if (tid == 0) s_word = wait_prog(prog, ca, 4 * ca + p + 1, ca, 4 * ca + p + 1, info);
+            __syncthreads();
+            if (!s_word) return;
+            const double d = ld_dev((const double *)(pl + 16 * p * (8 + cs) + (uint32_t)((gi + gi * b) * 8)));
+            double l[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) l[q] = ld_dev((const double *)(pl + (16 * p + 4 * q) * cs + lin8));
+#pragma unroll
+            for (int q = 0; q < 4; ++q) Bs[(16 * p + wave + 4 * q) * LD64 + lane] = l[q];
+            const double rl = 1.0 / d;
+            __syncthreads();
+            wave_trsm16(acc1, p, Bs, rl, scratch[wave], gi, gg, [&](int t, double v) {
+                st_dev((double *)(px + (16 * p + 4 * t) * cs + own8), v);
+                if (diag) A[(16 * p + 4 * t + gg) * LD64 + wave * 16 + gi] = v;
+            });
+            if (diag) {
+                __syncthreads();
+                mma64(acc2, A, A, wave, gi, gg, 16 * p, 16 * p + 16);
+            }
+        }
+        stores_done();
         __syncthreads();
-        if (tid == 0) __hip_atomic_store(prog + i, ca + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) __hip_atomic_store(prog + i, 4 * ca + 4, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (!diag) return;
-    if (ca >= 0) mma64(acc2, A, A, wave, gi, gg);
     // the diagonal block: Bs is free, every wave is past its solve
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
         for (int v = 0; v < 4; ++v) Bs[(ct * 16 + gg + 4 * v) * LD64 + wave * 16 + gi] = -acc2[ct][v];
     __syncthreads();
-    block_potrf64(Bs, wave, lane, col0 + 64 * (int64_t)m, n, info);
     char *pd = at(m, m);
+    block_potrf64(
+        Bs, wave, lane, col0 + 64 * (int64_t)m, n, info,
+        [&](int p) {
 #pragma unroll
-    for (int q = 0; q < 16; ++q) st_dev((double *)(pd + 4 * q * cs + lin8), Bs[(wave + 4 * q) * LD64 + lane]);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (tid == 0) __hip_atomic_store(prog + m, m + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int q = 0; q < 4; ++q)
+                st_dev((double *)(pd + (16 * p + 4 * q) * cs + lin8), Bs[(16 * p + wave + 4 * q) * LD64 + lane]);
+        },
+        [&](int p) {
+            if (tid == 0) __hip_atomic_store(prog + m, 4 * m + p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        });
 }
 
 // Words of control memory per diagonal tile: the ticket and the block rows'
 // counts; all zero before the tile's launch.
 int potrf_ctl_words(int b) { return 1 + b / 64; }
 
-void launch_potrf_tile(const Tiles &T, int k, int *ctl, unsigned long long *info, hipStream_t st)
+void launch_potrf_tile(const Tiles &T, const Panel &P, int k, int *ctl, hipStream_t st)
 {
     const int b = T.b, nb = b / 64;
     double *tile = (double *)(T.slots + tile_index(k, k) * T.slot_bytes);
     const int off = (nb - 1) * (nb - 2) / 2;  // blocks two or more below the diagonal
-    potrf_tile_kernel<<<nb + off, 256, 0, st>>>(tile, b, (int64_t)k * b, T.n, ctl + (int64_t)k * potrf_ctl_words(b), info);
+    potrf_tile_kernel<<<nb + off, 256, 0, st>>>(tile, b, (int64_t)k * b, T.n,
+                                                ctl + (int64_t)k * potrf_ctl_words(b), P.info, P.pmax, T.nt);
 }
 
 // ---------------------------------------------------------------- TRSM
@@ -456,15 +477,17 @@ void launch_potrf_tile(const Tiles &T, int k, int *ctl, unsigned long long *info
 // its own 16 rows from end to end: column blocks of 64, whose product with the
 // solved columns runs on the FP64 MFMA straight from registers (X and L, three
 // chunks of 16 columns in flight, no barrier), then the substitution of
-// wave_trsm64; the waves only share the diagonal block in LDS.  What bounds a
+// wave_trsm16; the waves only share the diagonal block in LDS.  What bounds a
 // strip is its b / 64 column blocks in sequence, what bounds many strips the
 // MFMA (248 strips of 512 columns: 0.33 -> 0.15 ms, where the products alone take
 // 0.055 ms on their compute unit).  The strip's largest |X| is folded into pmax[I] (atomic max of the FP64
-// bits, which order like the values; the caller zeroes pmax), and the first
+// bits, which order like the values; the tile's POTRF zeroes pmax), and the first
 // column holding an Inf or NaN into P.info (every off-diagonal factor tile
 // passes here, so a non-finite value is reported even where a low-precision
-// code would saturate it).
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void trsm_kernel(Tiles T, Panel P, int k, const double *__restrict__ L)
+// code would saturate it).  An FP64 tile whose only consumers are FP64 updates
+// is stored from here as well and needs no conversion.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void trsm_kernel(Tiles T, Panel P, int k, const double *__restrict__ L,
+                                                                                            const uint8_t *qmask)
 {
     __builtin_amdgcn_s_setprio(3);  // the panel chain: issue ahead of update waves sharing the SIMD
     __shared__ double Ls[64 * LD64];
@@ -472,9 +495,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void t
     const int b = T.b, I = k + 1 + blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, gi = lane & 15, gg = lane >> 4;
     const bool wf32 = T.map[I + (int64_t)k * T.nt] != P64;
+    const bool direct = panel_direct(T.map[I + (int64_t)k * T.nt], qmask[I]);  // the stored tile and its only copy are X
     // addresses: a uniform column base plus a lane's 32-bit byte offset
     const int row0 = blockIdx.x * 64;
-    const char *W = T.slots + tile_index(I, k) * T.slot_bytes + (int64_t)row0 * (wf32 ? 4 : 8);
+    char *W = T.slots + tile_index(I, k) * T.slot_bytes + (int64_t)row0 * (wf32 ? 4 : 8);
     char *X = (char *)(P.p64 + (int64_t)I * b * b + row0);
     const char *Lc = (const char *)L;
     const uint32_t own = wave * 16 + gi + gg * b;  // row gi of the wave, column gg
@@ -550,12 +574,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void t
         for (int ct = 0; ct < 4; ++ct) acc[ct] -= w[ct];
         __syncthreads();  // the diagonal block is in LDS
         if (cb + 64 < b) load_diag(cb + 64);
-        wave_trsm64(acc, Ls, inv, scratch[wave], gi, gg, [&](int p, int t, double v) {
-            const int c = cb + 16 * p + 4 * t;
-            *(double *)(X + c * cs + own8) = v;
-            xmax = fmax(xmax, fabs(v));
-            if (!(fabs(v) <= 1.7976931348623157e308)) bad = min(bad, c + gg);
-        });
+#pragma unroll 1
+        for (int p = 0; p < 4; ++p)
+            wave_trsm16(acc, p, Ls, inv[16 * p + gi], scratch[wave], gi, gg, [&](int t, double v) {
+                const int c = cb + 16 * p + 4 * t;
+                *(double *)(X + c * cs + own8) = v;
+                if (direct) *(double *)(W + c * cs + own8) = v;
+                xmax = fmax(xmax, fabs(v));
+                if (!(fabs(v) <= 1.7976931348623157e308)) bad = min(bad, c + gg);
+            });
         __syncthreads();  // the diagonal block has been read; the next one reads these columns through other lanes
     }
 #pragma unroll
@@ -566,12 +593,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void t
     if (lane == 0 && bad != 0x7FFFFFFF) atomicMin(P.info, (unsigned long long)((int64_t)k * T.b + bad + 1));
 }
 
-void launch_trsm_panel(const Tiles &T, const Panel &P, int k, hipStream_t st)
+void launch_trsm_panel(const Tiles &T, const Panel &P, int k, const uint8_t *qmask, hipStream_t st)
 {
     const int np = T.nt - k - 1;
     if (np <= 0) return;
     const double *L = (const double *)(T.slots + tile_index(k, k) * T.slot_bytes);
-    trsm_kernel<<<dim3(T.b / 64, np), 256, 0, st>>>(T, P, k, L);
+    trsm_kernel<<<dim3(T.b / 64, np), 256, 0, st>>>(T, P, k, L, qmask);
 }
 
 // ---------------------------------------------------------------- grouped trailing update
@@ -580,10 +607,10 @@ void launch_trsm_panel(const Tiles &T, const Panel &P, int k, hipStream_t st)
 // A_IJ -= L_Ik L_Jk^T + L_I,k+1 L_J,k+1^T with K = 2b in one accumulation.  Blocks are
 // renumbered XCD-aware so the blocks of one item share an L2; an item with
 // I == J (SYRK, always FP64) computes its lower blocks only.
-// The FP64 block keeps to 64 registers so that two blocks share a compute
+// The 128 x 128 FP64 block keeps to 64 registers so that two blocks share a compute
 // unit (eight waves per SIMD).
 template <typename T, int BM, int BN, int BK, int WM, int WN>
-__global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 8 : 1)))
+__global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 && BM == 128 ? 8 : 1)))
 void update_cm_kernel(Tiles Tt, const T *panel0, const T *panel1, const int32_t *items)
 {
     typedef CMShape<T, BM, BN, BK, WM, WN> S;
@@ -847,7 +874,14 @@ void launch_update(const Tiles &T, const Panel *const *Ps, int npan, int q, cons
     const Panel &P = *Ps[0];
     const Panel *P2 = npan > 1 ? Ps[1] : nullptr;  // the FP64 / FP32-MFMA updates take one pair at most
     switch (q) {
-    case P64: launch_cm<double, 128, 128, 16, 4, 4>(T, P.p64, P2 ? P2->p64 : nullptr, items, nitems, st); break;
+    case P64:
+        // a grid of 128 x 128 blocks that does not fill the 512 places on the GPU is
+        // bound by one block's time: blocks of 64 x 64 take a quarter of it
+        if ((int64_t)nitems * (T.b / 128) * (T.b / 128) < 512)
+            launch_cm<double, 64, 64, 16, 2, 2>(T, P.p64, P2 ? P2->p64 : nullptr, items, nitems, st);
+        else
+            launch_cm<double, 128, 128, 16, 4, 4>(T, P.p64, P2 ? P2->p64 : nullptr, items, nitems, st);
+        break;
     case P32:
         if (T.lo32) {
             PanelSet<uint16_t> ps{};

@@ -109,6 +109,7 @@ __global__ __launch_bounds__(256) void convert_kernel(Tiles T, Panel P, int k, c
     const int cls = T.map[I + (int64_t)k * T.nt];
     const int lo16 = T.lo16;
     const uint8_t mask = qmask[I];
+    if (panel_direct(cls, mask)) return;
     double *x64 = P.p64 + (int64_t)I * bb;
     char *slot = T.slots + tile_index(I, k) * T.slot_bytes;
 

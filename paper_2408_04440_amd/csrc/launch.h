@@ -57,8 +57,10 @@ void launch_get_factor(const Tiles &T, double *L, int64_t ldl, hipStream_t st);
 // ---- factorization (k_factor.hip)
 // ctl: nt * potrf_ctl_words(b) words, all zero before the first tile of a factorization
 int potrf_ctl_words(int b);
-void launch_potrf_tile(const Tiles &T, int k, int *ctl, unsigned long long *info, hipStream_t st);
-void launch_trsm_panel(const Tiles &T, const Panel &P, int k, hipStream_t st);
+void launch_potrf_tile(const Tiles &T, const Panel &P, int k, int *ctl, hipStream_t st);  // also zeroes P.pmax
+void launch_trsm_panel(const Tiles &T, const Panel &P, int k, const uint8_t *qmask, hipStream_t st);
+// a panel tile of FP64 class with FP64 consumers only: its TRSM stores it, the conversion skips it
+__host__ __device__ inline bool panel_direct(int cls, int qmask) { return cls == 0 && qmask == 1; }
 // grouped update A_IJ -= sum_h L_I,k_h L_J,k_h^T of class q over `nitems` packed (I << 16 | J)
 // items from the npan panels Ps[0..npan-1] (npan <= 2 for FP64 and FP32-MFMA, <= 4 otherwise);
 // small: block shapes that fit beside running update blocks.

@@ -90,6 +90,7 @@ struct mpchol_handle {
     std::vector<int64_t> item_off;
     std::vector<int32_t> item_syrk;  // per (pair, class, part): how many of its items are SYRK (I == J)
     uint8_t *d_qmask = nullptr;
+    std::vector<uint8_t> convert_col;  // per column: some panel tile needs the conversion
     int32_t *d_all_items = nullptr;  // every lower tile, for the residual
     double *d_partial = nullptr, *d_tres2 = nullptr;
     // backward-error estimator scratch
@@ -595,12 +596,14 @@ static void build_schedule_counts(mpchol_handle *h, std::vector<int32_t> &items,
     }
     h->item_off[(size_t)npair * NQ * 3] = (int64_t)items.size();
     qmask.assign((size_t)nt * nt, 0);
+    h->convert_col.assign(nt, 0);
     for (int k = 0; k < nt; ++k)
         for (int I = k + 1; I < nt; ++I) {
             uint8_t msk = 1;  // SYRK(I,I) reads the FP64 copy
             for (int J = k + 1; J < I; ++J) msk |= (uint8_t)(1u << update_class(h, I, J, int8_ok));
             for (int J = I + 1; J < nt; ++J) msk |= (uint8_t)(1u << update_class(h, J, I, int8_ok));
             qmask[I + (size_t)k * nt] = msk;
+            if (!panel_direct(h->h_map[I + (size_t)k * nt], msk)) h->convert_col[k] = 1;
         }
 }
 
@@ -728,10 +731,10 @@ extern "C" int mpchol_precision_map(mpchol_t h, int32_t rule, double eps, const 
 // sender-side conversion.
 static int panel_step(mpchol_handle *h, const Tiles &T, const Panel &P, int k, hipStream_t st)
 {
-    HIPCHK(hipMemsetAsync(P.pmax, 0, (size_t)h->nt * 8, st));
-    launch_trsm_panel(T, P, k, st);
-    launch_convert(T, P, k, h->d_qmask + (size_t)k * h->nt, st);
-    if (h->d_ozc) launch_ozaki_convert(T, P, k, h->d_qmask + (size_t)k * h->nt, h->d_ozc, st);
+    const uint8_t *qmask = h->d_qmask + (size_t)k * h->nt;
+    launch_trsm_panel(T, P, k, qmask, st);
+    if (h->convert_col[k]) launch_convert(T, P, k, qmask, st);
+    if (h->d_ozc) launch_ozaki_convert(T, P, k, qmask, h->d_ozc, st);
     return MPCHOL_OK;
 }
 
@@ -799,13 +802,13 @@ static int update_list(mpchol_handle *h, const Tiles &T, const Panel *P, int p, 
 static int panel_pair(mpchol_handle *h, const Tiles &T, const Panel *P, int c, hipStream_t st)
 {
     const int nt = h->nt;
-    launch_potrf_tile(T, c, h->d_potrf, h->d_info, st);
+    launch_potrf_tile(T, P[c % NSET], c, h->d_potrf, st);
     if (c + 1 >= nt) return MPCHOL_OK;
     int rc = panel_step(h, T, P[c % NSET], c, st);
     if (rc) return rc;
     rc = update_list(h, T, P, c / 2, 0, st);
     if (rc) return rc;
-    launch_potrf_tile(T, c + 1, h->d_potrf, h->d_info, st);
+    launch_potrf_tile(T, P[(c + 1) % NSET], c + 1, h->d_potrf, st);
     if (c + 2 < nt) rc = panel_step(h, T, P[(c + 1) % NSET], c + 1, st);
     return rc;
 }
