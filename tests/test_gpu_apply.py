@@ -185,3 +185,32 @@ def test_sample_is_philox_then_product(orc):
     log(f"  sample variance ratio mean={ratio.mean():.4f} min={ratio.min():.3f} max={ratio.max():.3f}")
     assert abs(ratio.mean() - 1.0) < 0.03
     assert ratio.min() > 0.7 and ratio.max() < 1.3
+
+
+@pytest.mark.parametrize("n,tile,nd,pad", [(130, 128, 1, 0), (600, 128, 16, 3), (600, 256, 17, 0), (1000, 512, 64, 0),
+                                           (1000, 128, 65, 1), (3000, 1024, 129, 0), (9000, 256, 1900, 0)])
+def test_sample_z_block_shapes(orc, n, tile, nd, pad):
+    """Every block shape of the draws at its edges (16, 64 and 128 draws a block,
+    strips of 32 and 128 rows, ragged rows and draws), Y against FP64 products
+    with the GPU's own factor: n u (FP32) bounds the sum of n terms entry by
+    entry, relative to |L| |z|."""
+    torch = torch_cuda()
+    mod = M()
+    h = mod.mpchol_create(n, tile)
+    try:
+        sigma, x = synth.workload(int(np.ceil(np.sqrt(n))))
+        mod.mpchol_set_generator(h, sigma[:n], x[:n], 5.0, 1e-8)
+        mod.mpchol_precision_map(h, mod.RULE_NORM, 1e-6)
+        assert mod.mpchol_factor(h) == 0
+        L = torch.zeros((n, n), dtype=torch.float64, device="cuda")
+        mod.mpchol_get_factor(h, L.T, n)
+        Z = torch.randn((nd, n + pad), generator=torch.Generator("cuda").manual_seed(7), device="cuda")
+        Y = torch.full((nd, n + pad), 7.0, device="cuda")
+        mod.mpchol_sample_z(h, Z.T, Y.T, n)
+        torch.cuda.synchronize()
+    finally:
+        mod.mpchol_destroy(h)
+    assert torch.all(Y[:, n:] == 7.0)
+    Zd = Z[:, :n].double().contiguous()
+    want, size = Zd @ L, Zd.abs() @ L.abs()  # L holds the factor's columns as rows
+    assert torch.all((Y[:, :n] - want).abs() <= n * 2.0 ** -24 * size + 1e-30)
