@@ -2,6 +2,8 @@
 // for every lower tile, in FP64 with each stored tile exactly widened to FP64
 // on its way into LDS; per-block sums of R^2 are reduced per tile in a fixed
 // order.
+#include <mutex>
+
 #include "common.h"
 #include "gemm_core.h"
 #include "launch.h"
@@ -18,6 +20,40 @@ __device__ inline double source_at(const Tiles &T, const Source &S, int I, int J
     return v;
 }
 
+// Consecutive workgroups go to the XCDs in turn: the blocks of one item follow
+// each other on one XCD and share its L2, and every XCD takes the items in order
+// (longest first, so that the short ones fill the end).
+__device__ inline bool residual_place(int per, int nitems, int &item, int &rem)
+{
+    const int xcd = blockIdx.x % 8, idx = blockIdx.x / 8;
+    item = idx / per * 8 + xcd;
+    rem = idx % per;
+    return item < nitems;
+}
+
+// The weighted squared residual of one entry.
+__device__ inline double residual2(const Tiles &T, const Source &S, int I, int J, int r, int c, double product)
+{
+    const int64_t i = (int64_t)I * T.b + r, j = (int64_t)J * T.b + c;
+    if (i >= T.n || j >= T.n || i < j) return 0.0;
+    const double res = source_at(T, S, I, J, r, c) - product;
+    return ((i == j) ? 1.0 : (I == J ? 2.0 : 1.0)) * res * res;
+}
+
+// Fixed-order sum of s2 over the workgroup into *out; red: NTH doubles of LDS
+// that no wave reads any more.
+template <int NTH> __device__ inline void residual_sum(double s2, double *red, double *out)
+{
+    const int tid = threadIdx.x;
+    red[tid] = s2;
+    __syncthreads();
+    for (int w = NTH / 2; w > 0; w >>= 1) {
+        if (tid < w) red[tid] += red[tid + w];
+        __syncthreads();
+    }
+    if (tid == 0) *out = red[0];
+}
+
 // 128 x 128 output block per workgroup, 8 waves of 64 x 32 (two blocks share
 // a compute unit: 144 KiB of LDS for the two, at most 128 registers a lane),
 // K staged 16 columns at a time through LDS.
@@ -27,11 +63,12 @@ static_assert(RNT <= 2 * RK * RLD, "the reduction reuses the A staging buffers")
 
 __global__ __launch_bounds__(RNT) __attribute__((amdgpu_waves_per_eu(4))) void residual_kernel(Tiles T, Source S,
                                                                                               const int32_t *items,
-                                                                                              double *partial)
+                                                                                              int nitems, double *partial)
 {
     __shared__ double As[2][RK][RLD], Bs[2][RK][RLD];
     const int b = T.b, nsub = b / RB;
-    const int item = blockIdx.x / (nsub * nsub), rem = blockIdx.x % (nsub * nsub);
+    int item, rem;
+    if (!residual_place(nsub * nsub, nitems, item, rem)) return;
     const int tm = rem % nsub, tn = rem / nsub;
     const int32_t it = items[item];
     const int I = it >> 16, J = it & 0xFFFF;
@@ -129,25 +166,59 @@ __global__ __launch_bounds__(RNT) __attribute__((amdgpu_waves_per_eu(4))) void r
 #pragma unroll
             for (int n = 0; n < RNB; ++n)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    int r = tm * RB + wm * WTM + m * 16 + acc_row<double>(gg, v), c = tn * RB + wn * WTN + n * 16 + gi;
-                    int64_t i = (int64_t)I * b + r, j = (int64_t)J * b + c;
-                    if (i >= T.n || j >= T.n || i < j) continue;
-                    double res = source_at(T, S, I, J, r, c) - acc[m][n][v];
-                    double w = (i == j) ? 1.0 : (I == J ? 2.0 : 1.0);
-                    s2 += w * res * res;
-                }
+                for (int v = 0; v < 4; ++v)
+                    s2 += residual2(T, S, I, J, tm * RB + wm * WTM + m * 16 + acc_row<double>(gg, v),
+                                    tn * RB + wn * WTN + n * 16 + gi, acc[m][n][v]);
     }
     // every wave is past the K loop's last barrier: the A staging buffers
     // are free for the reduction
-    double *red = &As[0][0][0];
-    red[tid] = s2;
-    __syncthreads();
-    for (int w = RNT / 2; w > 0; w >>= 1) {
-        if (tid < w) red[tid] += red[tid + w];
-        __syncthreads();
+    residual_sum<RNT>(s2, &As[0][0][0], partial + (int64_t)item * nsub * nsub + rem);
+}
+
+// A factor whose tiles are all FP64: the update's core, two K slices in flight
+// and 16-byte loads, over the tiles of the two block rows (N = 32,400, tile 1024:
+// 51 -> 63 TFLOP/s; with the kernel above's classes in the same loop, or sixteen
+// waves of 32 x 32 in 64 registers beside the sum below, the registers no longer
+// hold it: 29 and 21).  On small orders the last blocks bound it (N = 8,100:
+// 5.3 -> 3.7 ms, 48 TFLOP/s).
+constexpr int SWM = 2, SWN = 4;
+typedef CMShape<double, RB, RB, RK, SWM, SWN> RS;
+
+__global__ __launch_bounds__(RS::NTH) __attribute__((amdgpu_waves_per_eu(4))) void residual64_kernel(
+    Tiles T, Source S, const int32_t *items, int nitems, double *partial)
+{
+    extern __shared__ __align__(16) char smem_raw[];
+    const int b = T.b, nsub = b / RB;
+    int item, rem;
+    if (!residual_place(nsub * nsub, nitems, item, rem)) return;
+    const int tm = rem % nsub, tn = rem / nsub;
+    const int32_t it = items[item];
+    const int I = it >> 16, J = it & 0xFFFF;
+    double4_t acc[RS::MB][RS::NB];
+#pragma unroll
+    for (int m = 0; m < RS::MB; ++m)
+#pragma unroll
+        for (int n = 0; n < RS::NB; ++n) acc[m][n] = (double4_t){0.0, 0.0, 0.0, 0.0};
+    const bool skip = (I == J && tn > tm);
+    double s2 = 0.0;
+    if (!skip) {
+#pragma unroll 1
+        for (int K = 0; K <= J; ++K)
+            cm_block_deep<double, RB, RB, RK, SWM, SWN, true>(
+                (const double *)(T.slots + tile_index(I, K) * T.slot_bytes) + tm * RB, b,
+                (const double *)(T.slots + tile_index(J, K) * T.slot_bytes) + tn * RB, b, b, acc, (double *)smem_raw);
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        const int wm = wave % SWM, wn = wave / SWM, gi = lane & 15, gg = lane >> 4;
+#pragma unroll
+        for (int m = 0; m < RS::MB; ++m)
+#pragma unroll
+            for (int n = 0; n < RS::NB; ++n)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)  // swapped operands: lane gi owns row gi
+                    s2 += residual2(T, S, I, J, tm * RB + wm * (RB / SWM) + m * 16 + gi,
+                                    tn * RB + wn * (RB / SWN) + n * 16 + acc_row<double>(gg, v), acc[m][n][v]);
     }
-    if (tid == 0) partial[blockIdx.x] = red[0];
+    residual_sum<RS::NTH>(s2, (double *)smem_raw, partial + (int64_t)item * nsub * nsub + rem);
 }
 
 __global__ void residual_reduce_kernel(const int32_t *items, int nitems, int per_item, const double *partial, int nt,
@@ -161,12 +232,22 @@ __global__ void residual_reduce_kernel(const int32_t *items, int nitems, int per
     tile_res2[(it >> 16) + (int64_t)(it & 0xFFFF) * nt] = s;
 }
 
-// items: every lower tile as (I << 16 | J); scratch: partial sums
-void launch_residual_items(const Tiles &T, const Source &S, const int32_t *items, int nitems, double *partial,
-                           double *tile_res2, hipStream_t st)
+// items: every lower tile as (I << 16 | J), longest products first; scratch: partial sums
+void launch_residual_items(const Tiles &T, const Source &S, bool all64, const int32_t *items, int nitems,
+                           double *partial, double *tile_res2, hipStream_t st)
 {
     const int nsub = T.b / RB;
-    residual_kernel<<<(unsigned)((int64_t)nitems * nsub * nsub), RNT, 0, st>>>(T, S, items, partial);
+    const unsigned grid = (unsigned)((int64_t)(nitems + 7) / 8 * 8 * nsub * nsub);
+    if (all64) {
+        static std::once_flag attr;
+        std::call_once(attr, [] {
+            (void)hipFuncSetAttribute((const void *)residual64_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                      (int)RS::SMEM);
+        });
+        residual64_kernel<<<grid, RS::NTH, RS::SMEM, st>>>(T, S, items, nitems, partial);
+    } else {
+        residual_kernel<<<grid, RNT, 0, st>>>(T, S, items, nitems, partial);
+    }
     residual_reduce_kernel<<<(nitems + 255) / 256, 256, 0, st>>>(items, nitems, nsub * nsub, partial, T.nt, tile_res2);
 }
 

@@ -47,7 +47,8 @@ struct Panel {
 };
 
 // ---- tiles (k_tiles.hip)
-void launch_norms(const Tiles &T, const Source &S, double *fro2, double *amax, hipStream_t st);
+// partial: scratch of nt (nt + 1) / 2 * (b / 128)^2 doubles
+void launch_norms(const Tiles &T, const Source &S, double *partial, double *fro2, double *amax, hipStream_t st);
 void launch_load(const Tiles &T, const Source &S, hipStream_t st);
 void launch_copy_matrix(const Tiles &T, const double *A, int64_t lda, double *orig, hipStream_t st);
 void launch_convert(const Tiles &T, const Panel &P, int k, const uint8_t *qmask, hipStream_t st);
@@ -76,10 +77,11 @@ void launch_ozaki_convert(const Tiles &T, const Panel &P, int k, const uint8_t *
 void launch_ozaki_update(const Tiles &T, const Panel &P, const Panel *P2, const int32_t *items, int nitems,
                          const OzakiConst *K, hipStream_t st);
 
-// ---- residual (k_residual.hip): items = every lower tile as (I << 16 | J);
+// ---- residual (k_residual.hip): items = every lower tile as (I << 16 | J), the
+// longest products (largest J) first; all64: every tile of the map is FP64;
 // partial = scratch of nitems * (b/128)^2 doubles; tile_res2 = nt*nt output
-void launch_residual_items(const Tiles &T, const Source &S, const int32_t *items, int nitems, double *partial,
-                           double *tile_res2, hipStream_t st);
+void launch_residual_items(const Tiles &T, const Source &S, bool all64, const int32_t *items, int nitems,
+                           double *partial, double *tile_res2, hipStream_t st);
 
 // ---- backward-error estimate (k_estimate.hip): scratch 3*nt*b*probes doubles,
 // zbuf n*probes floats; *out = sum over the probes of ||(Sigma - L L^T) v||^2

@@ -355,8 +355,9 @@ int mpchol_create(mpchol_t *hp, int64_t n, int32_t tile, const mpchol_opts *o)
     if (rc == MPCHOL_OK) {
         std::vector<int32_t> all;
         all.reserve(h->ntile);
-        for (int I = 0; I < nt; ++I)
-            for (int J = 0; J <= I; ++J) all.push_back((I << 16) | J);
+        // the residual's products of tile (I, J) run over J + 1 tiles: longest first
+        for (int J = (int)nt - 1; J >= 0; --J)
+            for (int I = J; I < nt; ++I) all.push_back((I << 16) | J);
         H(hipMemcpy(h->d_all_items, all.data(), all.size() * 4, hipMemcpyHostToDevice), "hipMemcpy(items)");
         H(hipMemset(h->d_tscale, 0, nt * nt * 4), "hipMemset(tscale)");
         H(hipMemset(h->d_map, 0, nt * nt), "hipMemset(map)");
@@ -683,7 +684,7 @@ static int compute_norms(mpchol_handle *h)
     const int nt = h->nt;
     HIPCHK(hipMemsetAsync(h->d_fro2, 0, (size_t)nt * nt * 8, h->st));
     HIPCHK(hipMemsetAsync(h->d_amax, 0, (size_t)nt * nt * 8, h->st));
-    launch_norms(h->tiles(), h->source(), h->d_fro2, h->d_amax, h->st);
+    launch_norms(h->tiles(), h->source(), h->d_partial, h->d_fro2, h->d_amax, h->st);
     h->h_fro2.assign((size_t)nt * nt, 0.0);
     h->h_amax.assign((size_t)nt * nt, 0.0);
     HIPCHK(hipMemcpyAsync(h->h_fro2.data(), h->d_fro2, (size_t)nt * nt * 8, hipMemcpyDeviceToHost, h->st));
@@ -977,7 +978,8 @@ static int residual_of(mpchol_handle *h, const Source &S, double total_fro, doub
 {
     const int nt = h->nt;
     HIPCHK(hipEventRecord(h->ev[2], h->st));
-    launch_residual_items(h->tiles(), S, h->d_all_items, (int)h->ntile, h->d_partial, h->d_tres2, h->st);
+    const bool all64 = std::all_of(h->h_map.begin(), h->h_map.end(), [](uint8_t c) { return c == P64; });
+    launch_residual_items(h->tiles(), S, all64, h->d_all_items, (int)h->ntile, h->d_partial, h->d_tres2, h->st);
     std::vector<double> r((size_t)nt * nt, 0.0);
     HIPCHK(hipMemsetAsync(h->d_scalar, 0, 8, h->st));
     HIPCHK(hipMemcpyAsync(r.data(), h->d_tres2, r.size() * 8, hipMemcpyDeviceToHost, h->st));
@@ -1076,7 +1078,7 @@ extern "C" int mpchol_backward_error_matrix(mpchol_t h, const double *A, int64_t
     if (!rc && hipMemsetAsync(fro2, 0, (size_t)nt * nt * 8, h->st) != hipSuccess) rc = MPCHOL_EHIP;
     std::vector<double> f2((size_t)nt * nt, 0.0);
     if (!rc) {
-        launch_norms(h->tiles(), S, fro2, amax, h->st);
+        launch_norms(h->tiles(), S, h->d_partial, fro2, amax, h->st);
         if (hipMemcpyAsync(f2.data(), fro2, f2.size() * 8, hipMemcpyDeviceToHost, h->st) != hipSuccess ||
             hipStreamSynchronize(h->st) != hipSuccess || hipGetLastError() != hipSuccess)
             rc = MPCHOL_EHIP;

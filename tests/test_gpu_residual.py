@@ -125,3 +125,35 @@ def test_residual_same_factor_mixed(orc, L, tile, rho, eps):
     w2 = same_factor_residuals(be_m, tr_m, be_o, tr_o, A, tile)
     log(f"  same factor L={L} eps={eps} hist={hist}: be_gpu={be:.6e} be_oracle={be_o:.6e} "
         f"worst tile {w:.2e}/{w2:.2e} of the tolerance")
+
+
+@pytest.mark.parametrize("n,tile,src", [(100, 128, 0), (700, 256, 0), (900, 384, 1), (2000, 768, 0), (1300, 640, 1)])
+def test_norms_and_residual_tile_sizes(n, tile, src):
+    """Norms and load over every way a tile's columns are dealt to blocks (the
+    norm rule's classes and the total norm), and the all-FP64 residual of a
+    perturbed matrix: 100 n u covers sums of up to n^2 squares taken pairwise."""
+    torch = torch_cuda()
+    mod = M()
+    sigma, x = synth.workload(int(np.ceil(np.sqrt(n))))
+    sigma, x = sigma[:n], x[:n]
+    A = sigma[:, None] * sigma[None, :] * np.exp(-np.abs(x[:, None] - x[None, :]) / 5.0) + 1e-8 * np.eye(n)
+    h = mod.mpchol_create(n, tile)
+    try:
+        if src:
+            mod.mpchol_set_matrix(h, A)
+        else:
+            mod.mpchol_set_generator(h, sigma, x, 5.0, 1e-8)
+        mod.mpchol_precision_map(h, mod.RULE_FP64)
+        total = mod.mpchol_get_stats(h)["total_fro"]
+        assert abs(total - np.linalg.norm(A)) <= 100 * n * 2.0 ** -53 * total
+        assert mod.mpchol_factor(h) == 0
+        E = 1e-3 * np.diag(sigma) @ np.cos(np.add.outer(np.arange(n), np.arange(n))) @ np.diag(sigma)
+        be, tr = mod.mpchol_backward_error_matrix(h, A + E, tiles=True)
+    finally:
+        mod.mpchol_destroy(h)
+    nt = -(-n // tile)
+    for I in range(nt):
+        for J in range(I + 1):
+            e = E[I * tile:(I + 1) * tile, J * tile:(J + 1) * tile]
+            assert abs(tr[I, J] - np.sum(e * e)) <= 1e-9 * np.sum(E * E)
+    assert abs(be - np.linalg.norm(E) / np.linalg.norm(A + E)) <= 1e-9 * be
