@@ -42,6 +42,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -52,8 +53,6 @@
 namespace mpc {
 namespace sht {
 
-constexpr int NTH = 512;   // threads of an FFT workgroup
-constexpr int MAXV = 8;    // complex values per thread and pass: nseq * n <= NTH * MAXV
 constexpr int MAXP = 16;   // passes of a plan
 constexpr int MAXN = 4096; // longest transform
 constexpr int MAXL = 1024; // band limit (2^-l of the edge value stays a normal double)
@@ -63,9 +62,12 @@ struct Plan {
     int r[MAXP];
 };
 
-// GEMM block shape (FP64 MFMA, operands swapped so that column-major stores coalesce)
-constexpr int GBM = 64, GBN = 128, GBK = 16, GWM = 2, GWN = 2;
-typedef CMShape<double, GBM, GBN, GBK, GWM, GWN> GS;
+// GEMM block: 64 rows by 64 columns, K slices of 16, four waves (three workgroups
+// share a compute unit; with 128 columns two do: L = 360, 512 fields 0.72 against
+// 0.68 ms, L = 720, 64 fields 0.64 against 0.60).  Up to SMALL_T fields (two
+// columns each) take blocks of 16 columns, which move and multiply a quarter of it.
+constexpr int GBM = 64, GBN = 64, GBK = 16, GNT = 256;
+constexpr int SMALL_T = 8;
 
 __device__ inline double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
 __device__ inline double2 csub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
@@ -82,161 +84,246 @@ __device__ inline double2 ipow(double2 a, int e)
     }
 }
 
-// R-point DFT in place: V[q] = sum_r v[r] w^{q r}, w = e^{-2 pi i / R} (forward)
-// or its conjugate (inverse); tw holds e^{-2 pi i k / n} for the transform length n.
-template <int R>
-__device__ inline void dft_small(double2 (&v)[R], const double2 *tw, int n, bool inv)
+// cos and sin of 2 pi k / R
+template <int R> struct Root;
+template <> struct Root<6> {
+    static constexpr double c[6] = {1.0, 0.5, -0.5, -1.0, -0.5, 0.5};
+    static constexpr double s[6] = {0.0, 0.8660254037844386, 0.8660254037844386, 0.0, -0.8660254037844386, -0.8660254037844386};
+};
+template <> struct Root<8> {
+    static constexpr double c[8] = {1.0, 0.7071067811865476, 0.0, -0.7071067811865476, -1.0, -0.7071067811865476, 0.0, 0.7071067811865476};
+    static constexpr double s[8] = {0.0, 0.7071067811865476, 1.0, 0.7071067811865476, 0.0, -0.7071067811865476, -1.0, -0.7071067811865476};
+};
+template <> struct Root<9> {
+    static constexpr double c[9] = {1.0, 0.766044443118978, 0.17364817766693036, -0.5, -0.9396926207859084, -0.9396926207859084, -0.5, 0.17364817766693036, 0.766044443118978};
+    static constexpr double s[9] = {0.0, 0.6427876096865394, 0.984807753012208, 0.8660254037844386, 0.3420201433256687, -0.3420201433256687, -0.8660254037844386, -0.984807753012208, -0.6427876096865394};
+};
+template <> struct Root<10> {
+    static constexpr double c[10] = {1.0, 0.8090169943749475, 0.30901699437494745, -0.30901699437494745, -0.8090169943749475, -1.0, -0.8090169943749475, -0.30901699437494745, 0.30901699437494745, 0.8090169943749475};
+    static constexpr double s[10] = {0.0, 0.5877852522924731, 0.9510565162951535, 0.9510565162951535, 0.5877852522924731, 0.0, -0.5877852522924731, -0.9510565162951535, -0.9510565162951535, -0.5877852522924731};
+};
+template <> struct Root<12> {
+    static constexpr double c[12] = {1.0, 0.8660254037844386, 0.5, 0.0, -0.5, -0.8660254037844386, -1.0, -0.8660254037844386, -0.5, 0.0, 0.5, 0.8660254037844386};
+    static constexpr double s[12] = {0.0, 0.5, 0.8660254037844386, 1.0, 0.8660254037844386, 0.5, 0.0, -0.5, -0.8660254037844386, -1.0, -0.8660254037844386, -0.5};
+};
+
+template <int I, int N, typename F> __device__ inline void static_for(F f)
 {
-    if constexpr (R == 2) {
-        double2 a = v[0], b = v[1];
-        v[0] = cadd(a, b);
-        v[1] = csub(a, b);
-    } else if constexpr (R == 4) {
-        double2 s02 = cadd(v[0], v[2]), d02 = csub(v[0], v[2]);
-        double2 s13 = cadd(v[1], v[3]), d13 = csub(v[1], v[3]);
-        // w = -i forward, +i inverse
-        double2 wd = inv ? make_double2(-d13.y, d13.x) : make_double2(d13.y, -d13.x);
-        v[0] = cadd(s02, s13);
-        v[2] = csub(s02, s13);
-        v[1] = cadd(d02, wd);
-        v[3] = csub(d02, wd);
-    } else {
-        double2 in[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) in[r] = v[r];
-        const int st = n / R;
-#pragma unroll
-        for (int q = 0; q < R; ++q) {
-            double2 acc = in[0];
-#pragma unroll
-            for (int r = 1; r < R; ++r) {
-                double2 w = tw[((q * r) % R) * st];
-                if (inv) w.y = -w.y;
-                acc = cadd(acc, cmul(in[r], w));
-            }
-            v[q] = acc;
-        }
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<I + 1, N>(f);
     }
 }
 
-// One Stockham pass of radix R over nseq sequences of length n held
-// contiguously in LDS (in place: every butterfly reads its inputs before a
-// barrier and writes its outputs after it).  Ns = product of earlier radices.
-template <int R>
-__device__ inline void fft_pass(double2 *buf, int nseq, int n, int Ns, const double2 *tw, bool inv)
+// R-point DFT in place in registers: V[q] = sum_r v[r] e^{-2 pi i q r / R}.
+// Composite R = R1 R2: R2 transforms of length R1, the roots of R, R1 of length R2.
+template <int R> __device__ inline void dft(double2 (&v)[R]);
+template <int R1, int R2> __device__ inline void dft_composite(double2 (&v)[R1 * R2])
 {
-    constexpr int MB = (MAXV + R - 1) / R;
-    const int nb = n / R, total = nseq * nb;
+    constexpr int R = R1 * R2;
+    double2 y[R2][R1];
+    static_for<0, R2>([&](auto N2) {
+        constexpr int n2 = N2;
+#pragma unroll
+        for (int n1 = 0; n1 < R1; ++n1) y[n2][n1] = v[R2 * n1 + n2];
+        dft<R1>(y[n2]);
+        static_for<1, R1>([&](auto K1) {
+            constexpr int e = n2 * K1;
+            if constexpr (e > 0) y[n2][K1] = cmul(y[n2][K1], make_double2(Root<R>::c[e], -Root<R>::s[e]));
+        });
+    });
+#pragma unroll
+    for (int k1 = 0; k1 < R1; ++k1) {
+        double2 z[R2];
+#pragma unroll
+        for (int n2 = 0; n2 < R2; ++n2) z[n2] = y[n2][k1];
+        dft<R2>(z);
+#pragma unroll
+        for (int k2 = 0; k2 < R2; ++k2) v[k1 + R1 * k2] = z[k2];
+    }
+}
+template <int R> __device__ inline void dft(double2 (&v)[R])
+{
+    if constexpr (R == 2) {
+        const double2 a = v[0], b = v[1];
+        v[0] = cadd(a, b);
+        v[1] = csub(a, b);
+    } else if constexpr (R == 3) {
+        const double2 t = cadd(v[1], v[2]), d = cscale(csub(v[1], v[2]), Root<6>::s[1]);
+        const double2 u = make_double2(v[0].x - 0.5 * t.x, v[0].y - 0.5 * t.y);
+        v[0] = cadd(v[0], t);
+        v[1] = make_double2(u.x + d.y, u.y - d.x);
+        v[2] = make_double2(u.x - d.y, u.y + d.x);
+    } else if constexpr (R == 4) {
+        const double2 s02 = cadd(v[0], v[2]), d02 = csub(v[0], v[2]), s13 = cadd(v[1], v[3]), d13 = csub(v[1], v[3]);
+        v[0] = cadd(s02, s13);
+        v[2] = csub(s02, s13);
+        v[1] = make_double2(d02.x + d13.y, d02.y - d13.x);
+        v[3] = make_double2(d02.x - d13.y, d02.y + d13.x);
+    } else if constexpr (R == 5) {
+        constexpr double c1 = Root<10>::c[2], c2 = Root<10>::c[4], s1 = Root<10>::s[2], s2 = Root<10>::s[4];
+        const double2 t1 = cadd(v[1], v[4]), t2 = cadd(v[2], v[3]), t3 = csub(v[1], v[4]), t4 = csub(v[2], v[3]);
+        const double2 a1 = make_double2(v[0].x + c1 * t1.x + c2 * t2.x, v[0].y + c1 * t1.y + c2 * t2.y);
+        const double2 a2 = make_double2(v[0].x + c2 * t1.x + c1 * t2.x, v[0].y + c2 * t1.y + c1 * t2.y);
+        const double2 b1 = make_double2(s1 * t3.x + s2 * t4.x, s1 * t3.y + s2 * t4.y);
+        const double2 b2 = make_double2(s2 * t3.x - s1 * t4.x, s2 * t3.y - s1 * t4.y);
+        v[0] = cadd(v[0], cadd(t1, t2));
+        v[1] = make_double2(a1.x + b1.y, a1.y - b1.x);
+        v[4] = make_double2(a1.x - b1.y, a1.y + b1.x);
+        v[2] = make_double2(a2.x + b2.y, a2.y - b2.x);
+        v[3] = make_double2(a2.x - b2.y, a2.y + b2.x);
+    } else if constexpr (R == 6) dft_composite<2, 3>(v);
+    else if constexpr (R == 8) dft_composite<4, 2>(v);
+    else if constexpr (R == 9) dft_composite<3, 3>(v);
+    else if constexpr (R == 10) dft_composite<2, 5>(v);
+    else if constexpr (R == 12) dft_composite<4, 3>(v);
+}
+
+// Element i of a sequence in LDS: one place in 17 is skipped, so that the writes
+// of a pass, R elements apart, spread over the banks for even R too.
+__host__ __device__ inline int skew(int i) { return i + (i >> 4); }
+__host__ __device__ inline int seq_len(int n) { return skew(n) + 1; }
+
+// One Stockham pass of radix R over nseq sequences of length n (in place in LDS:
+// every butterfly reads its inputs before a barrier and writes its outputs after
+// it).  Ns = product of earlier radices; load(s)(i) and store(s)(i, v) take
+// and give element i of sequence s, in LDS or in memory.
+// butterflies of a pass per thread: one, of the smallest radices two
+__host__ __device__ constexpr int butterflies(int R) { return R <= 3 ? 2 : 1; }
+
+template <int R, typename Load, typename Store>
+__device__ inline void fft_pass(int nseq, int n, int Ns, const double2 *tw, Load load, Store store)
+{
+    constexpr int MB = butterflies(R);
+    // the length anew in every pass: otherwise the indices of all radices are
+    // computed ahead of the loop over the passes, and spilled
+    asm volatile("" : "+s"(n));
+    const int nb = n / R;
     double2 v[MB][R];
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
-        const int idx = threadIdx.x + i * NTH;
-        if (idx < total) {
-            const int s = idx / nb, j = idx - s * nb;
-            const double2 *src = buf + s * n + j;
+        const int idx = threadIdx.x + i * blockDim.x, s = idx / nb, j = idx - s * nb;
+        if (s < nseq) {
+            auto from = load(s);
 #pragma unroll
-            for (int r = 0; r < R; ++r) v[i][r] = src[r * nb];
+            for (int r = 0; r < R; ++r) v[i][r] = from(j + r * nb);
         }
     }
     __syncthreads();
-    const int stride = n / (Ns * R);
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
-        const int idx = threadIdx.x + i * NTH;
-        if (idx < total) {
-            const int s = idx / nb, j = idx - s * nb;
-            const int k = j % Ns, step = k * stride;
+        const int idx = threadIdx.x + i * blockDim.x, s = idx / nb, j = idx - s * nb;
+        if (s < nseq) {
+            const int jn = j / Ns, k = j - jn * Ns;
+            if (Ns > 1) {
+                const int step = k * (n / (Ns * R));
 #pragma unroll
-            for (int r = 1; r < R; ++r) {
-                double2 w = tw[r * step];
-                if (inv) w.y = -w.y;
-                v[i][r] = cmul(v[i][r], w);
+                for (int r = 1; r < R; ++r) v[i][r] = cmul(v[i][r], tw[r * step]);
             }
-            dft_small<R>(v[i], tw, n, inv);
-            double2 *dst = buf + s * n + (j / Ns) * Ns * R + k;
+            if constexpr (R > 1) dft<R>(v[i]);
+            auto to = store(s);
 #pragma unroll
-            for (int q = 0; q < R; ++q) dst[q * Ns] = v[i][q];
+            for (int q = 0; q < R; ++q) to(jn * Ns * R + k + q * Ns, v[i][q]);
         }
     }
     __syncthreads();
 }
 
-// X[k] = sum_j x[j] e^{-+2 pi i jk/n} for nseq sequences in LDS (no scaling).
-__device__ inline void fft_run(double2 *buf, int nseq, const Plan &P, const double2 *tw, bool inv)
+template <typename Load, typename Store>
+__device__ inline void fft_step(int R, int nseq, int n, int Ns, const double2 *tw, Load load, Store store)
 {
-    int Ns = 1;
-    for (int p = 0; p < P.np; ++p) {
-        const int R = P.r[p];
-        if (R == 4) fft_pass<4>(buf, nseq, P.n, Ns, tw, inv);
-        else if (R == 2) fft_pass<2>(buf, nseq, P.n, Ns, tw, inv);
-        else if (R == 3) fft_pass<3>(buf, nseq, P.n, Ns, tw, inv);
-        else fft_pass<5>(buf, nseq, P.n, Ns, tw, inv);
-        Ns *= R;
+    switch (R) {
+    case 2: fft_pass<2>(nseq, n, Ns, tw, load, store); break;
+    case 3: fft_pass<3>(nseq, n, Ns, tw, load, store); break;
+    case 4: fft_pass<4>(nseq, n, Ns, tw, load, store); break;
+    case 5: fft_pass<5>(nseq, n, Ns, tw, load, store); break;
+    case 6: fft_pass<6>(nseq, n, Ns, tw, load, store); break;
+    case 8: fft_pass<8>(nseq, n, Ns, tw, load, store); break;
+    case 9: fft_pass<9>(nseq, n, Ns, tw, load, store); break;
+    case 10: fft_pass<10>(nseq, n, Ns, tw, load, store); break;
+    case 12: fft_pass<12>(nseq, n, Ns, tw, load, store); break;
+    default: fft_pass<1>(nseq, n, Ns, tw, load, store); break;
     }
 }
 
-__device__ inline void load_twiddles(double2 *tws, const double2 *twg, int n)
+constexpr int MAXSEQ = 8;  // sequences of an FFT workgroup
+
+// The two rows of a sequence and its place in the blocks of the contraction.
+struct Seq {
+    int64_t z0, z1;  // first elements of rows j' and N_theta - 1 - j' of the field (equal at the equator)
+    int64_t o;       // row j', column 2t of a block; < 0: no such sequence (z0 and z1 then the first row)
+};
+__device__ inline Seq sequence(int64_t g, int64_t nsq, int T, int ntheta, int n, int64_t ld)
 {
-    for (int i = threadIdx.x; i < n; i += NTH) tws[i] = twg[i];
+    Seq q{0, 0, -1};
+    if (g < nsq) {
+        const int jp = (int)(g / T), t = (int)(g - (int64_t)jp * T), js = ntheta - 1 - jp;
+        q.z0 = ((int64_t)t * ntheta + jp) * n;
+        q.z1 = ((int64_t)t * ntheta + js) * n;
+        q.o = jp * ld + 2 * t;
+    }
+    return q;
 }
 
 // ------------------------------------------------------------------ longitude
 __host__ __device__ inline int lstart(int m, int p) { return ((m & 1) == p) ? m : m + 1; }
 
 // Forward: sequence g = j' T + t (j' < H = ceil(N_theta / 2)) packs rows j' and
-// N_theta - 1 - j' of field t (the second row zero at the equator of an odd
-// grid); with A, B their spectra times 2 pi / N_phi, block (m, q) of Gb gets
+// N_theta - 1 - j' of field t (the equator of an odd grid twice, and only its
+// first spectrum used); with A, B their spectra times 2 pi / N_phi, block (m, q) of Gb gets
 // row j', columns 2t, 2t + 1: A + B (q = 0) and A - B (q = 1), m = 0..L-1.
-__global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(4, 8))) void phi_forward_kernel(
-    const double *__restrict__ Z, int T, int ntheta, int L, Plan P, const double2 *__restrict__ twg, double *Gb,
-    int64_t blk, int64_t ld, int nseq)
+// Bound by LDS traffic more than by its bytes: the first pass reads the fields
+// themselves, radices up to 12 leave three passes for N_phi = 720, and their
+// roots are constants (five passes with looked-up roots before: L = 360, 512
+// fields 1.03 -> 0.57 ms, 3.7 TB/s).  Workgroups that fill the same lines share an
+// XCD.
+template <int MAXT>
+__global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(MAXT == 512 ? 3 : 4))) void phi_forward_kernel(const double *__restrict__ Z, int T, int ntheta, int L, Plan P,
+                                                          const double2 *__restrict__ twg, double *Gb, int64_t blk,
+                                                          int64_t ld, int nseq)
 {
     extern __shared__ __align__(16) char smem_raw[];
-    const int n = P.n;
-    const int H = (ntheta + 1) / 2;
-    const int64_t nsq = (int64_t)H * T;
+    __shared__ Seq seq[MAXSEQ];
+    const int n = P.n, sl = seq_len(n);
     double2 *tws = (double2 *)smem_raw;
     double2 *buf = tws + n;
-    load_twiddles(tws, twg, n);
-    const int64_t g0 = (int64_t)blockIdx.x * nseq;
-    double2 vin[MAXV];
-#pragma unroll
-    for (int i = 0; i < MAXV; ++i) {
-        const int idx = threadIdx.x + i * NTH;
-        vin[i] = make_double2(0.0, 0.0);
-        if (idx < nseq * n) {
-            const int s = idx / n, k = idx - s * n;
-            const int64_t g = g0 + s;
-            if (g < nsq) {
-                const int jp = (int)(g / T), t = (int)(g - (int64_t)jp * T);
-                const int js = ntheta - 1 - jp;
-                const double *zt = Z + (int64_t)t * ntheta * n;
-                vin[i].x = zt[(int64_t)jp * n + k];
-                if (js != jp) vin[i].y = zt[(int64_t)js * n + k];
-            }
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < MAXV; ++i) {
-        const int idx = threadIdx.x + i * NTH;
-        if (idx < nseq * n) buf[idx] = vin[i];
-    }
+    const int64_t g0 = xcd_remap(blockIdx.x, gridDim.x) * nseq;
+    if (threadIdx.x < nseq)
+        seq[threadIdx.x] = sequence(g0 + threadIdx.x, (int64_t)((ntheta + 1) / 2) * T, T, ntheta, n, ld);
+    for (int i = threadIdx.x; i < n; i += blockDim.x) tws[i] = twg[i];
     __syncthreads();
-    fft_run(buf, nseq, P, tws, false);
+    int Ns = 1;
+    for (int p = 0; p < P.np; ++p) {
+        auto store = [&](int s) {
+            return [b = buf + s * sl](int i, double2 v) { b[skew(i)] = v; };
+        };
+        if (p == 0)
+            fft_step(P.r[0], nseq, n, 1, tws,
+                     [&](int s) {
+                         return [z0 = Z + seq[s].z0, z1 = Z + seq[s].z1](int i) { return make_double2(z0[i], z1[i]); };
+                     },
+                     store);
+        else
+            fft_step(P.r[p], nseq, n, Ns, tws,
+                     [&](int s) { return [b = buf + s * sl](int i) { return b[skew(i)]; }; }, store);
+        Ns *= P.r[p];
+    }
     const double sc = M_PI / n;  // (2 pi / n) / 2 of the two-row separation
-    for (int idx = threadIdx.x; idx < nseq * L; idx += NTH) {
-        const int s = idx % nseq, m = idx / nseq;
-        const int64_t g = g0 + s;
-        if (g >= nsq) continue;
-        const int jp = (int)(g / T), t = (int)(g - (int64_t)jp * T);
-        const double2 X = buf[s * n + m], Y = buf[s * n + (n - m) % n];
+    for (int idx = threadIdx.x; idx < nseq * L; idx += blockDim.x) {
+        const int m = idx / nseq, s = idx - m * nseq;
+        const Seq &q = seq[s];
+        if (q.o < 0) continue;
+        const double2 X = buf[s * sl + skew(m)], Y = buf[s * sl + skew(m ? n - m : 0)];
         // A = (X + conj Y) / 2, B = (X - conj Y) / 2i, both times 2 pi / n
         const double2 a = make_double2(sc * (X.x + Y.x), sc * (X.y - Y.y));
         const double2 b = make_double2(sc * (X.y + Y.y), -sc * (X.x - Y.x));
         double2 gs = cadd(a, b), ga = csub(a, b);
-        if (ntheta - 1 - jp == jp) ga = make_double2(0.0, 0.0);
-        *(double2 *)(Gb + (2 * m) * blk + jp * ld + 2 * t) = gs;
-        *(double2 *)(Gb + (2 * m + 1) * blk + jp * ld + 2 * t) = ga;
+        if (q.z1 == q.z0) {  // the equator: its row alone
+            gs = a;
+            ga = make_double2(0.0, 0.0);
+        }
+        *(double2 *)(Gb + (2 * m) * blk + q.o) = gs;
+        *(double2 *)(Gb + (2 * m + 1) * blk + q.o) = ga;
     }
 }
 
@@ -244,53 +331,67 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
 // the results of the even (l + m even) and odd blocks of order m,
 // G_m = i^{m mod 2 - m} (E + O) on row j' and i^{m mod 2 - m} (E - O) on its
 // mirror; Z = (1 / 2 pi) sum_{|m| < L} G_m e^{i m phi}, G_{-m} = conj(G_m), both
-// rows from one inverse FFT (their spectra are Hermitian).
-__global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(4, 8))) void phi_inverse_kernel(
-    const double *__restrict__ Ob, int64_t blk, int64_t ld, int T, int ntheta, int L, Plan P,
-    const double2 *__restrict__ twg, double *__restrict__ Z, int nseq)
+// rows from one inverse FFT (their spectra are Hermitian): the forward transform
+// with real and imaginary parts exchanged on the way in and out.  The last pass
+// writes the fields (L = 720, 64 fields: 0.72 -> 0.43 ms).
+template <int MAXT>
+__global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(MAXT == 512 ? 3 : 4))) void phi_inverse_kernel(const double *__restrict__ Ob, int64_t blk, int64_t ld, int T,
+                                                          int ntheta, int L, Plan P, const double2 *__restrict__ twg,
+                                                          double *__restrict__ Z, int nseq)
 {
     extern __shared__ __align__(16) char smem_raw[];
-    const int n = P.n;
-    const int H = (ntheta + 1) / 2;
-    const int64_t nsq = (int64_t)H * T;
+    __shared__ Seq seq[MAXSEQ];
+    const int n = P.n, sl = seq_len(n);
     double2 *tws = (double2 *)smem_raw;
     double2 *buf = tws + n;
-    load_twiddles(tws, twg, n);
-    for (int idx = threadIdx.x; idx < nseq * n; idx += NTH) buf[idx] = make_double2(0.0, 0.0);
+    const int64_t g0 = xcd_remap(blockIdx.x, gridDim.x) * nseq;
+    if (threadIdx.x < nseq)
+        seq[threadIdx.x] = sequence(g0 + threadIdx.x, (int64_t)((ntheta + 1) / 2) * T, T, ntheta, n, ld);
+    for (int i = threadIdx.x; i < n; i += blockDim.x) tws[i] = twg[i];
+    const int gap = n - 2 * L + 1;  // orders L .. n - L
+    for (int idx = threadIdx.x; idx < nseq * gap; idx += blockDim.x) {
+        const int s = idx / gap;
+        buf[s * sl + skew(L + idx - s * gap)] = make_double2(0.0, 0.0);
+    }
     __syncthreads();
-    const int64_t g0 = (int64_t)blockIdx.x * nseq;
     const double sc = 1.0 / (2.0 * M_PI);
-    for (int idx = threadIdx.x; idx < nseq * L; idx += NTH) {
-        const int s = idx % nseq, m = idx / nseq;
-        const int64_t g = g0 + s;
-        if (g >= nsq) continue;
-        const int jp = (int)(g / T), t = (int)(g - (int64_t)jp * T);
-        const int p0 = m & 1;  // degree parity of the block with l + m even
-        const double2 E = *(const double2 *)(Ob + (2 * m + p0) * blk + jp * ld + 2 * t);
-        const double2 O = *(const double2 *)(Ob + (2 * m + (p0 ^ 1)) * blk + jp * ld + 2 * t);
-        const int e = ((m & 1) - m) & 3;
-        const double2 ga = cscale(ipow(cadd(E, O), e), sc);
-        double2 gb = cscale(ipow(csub(E, O), e), sc);
-        if (ntheta - 1 - jp == jp) gb = make_double2(0.0, 0.0);
+    for (int idx = threadIdx.x; idx < nseq * L; idx += blockDim.x) {
+        const int m = idx / nseq, s = idx - m * nseq;
+        const Seq &q = seq[s];
+        double2 ga = make_double2(0.0, 0.0), gb = ga;
+        if (q.o >= 0) {
+            const int p0 = m & 1;  // degree parity of the block with l + m even
+            const double2 E = *(const double2 *)(Ob + (2 * m + p0) * blk + q.o);
+            const double2 O = *(const double2 *)(Ob + (2 * m + (p0 ^ 1)) * blk + q.o);
+            const int e = ((m & 1) - m) & 3;
+            ga = cscale(ipow(cadd(E, O), e), sc);
+            if (q.z1 != q.z0) gb = cscale(ipow(csub(E, O), e), sc);
+        }
+        double2 *bs = buf + s * sl;  // parts exchanged
         if (m == 0) {  // G_0 of a real field is real
-            buf[s * n] = make_double2(ga.x, gb.x);
+            bs[0] = make_double2(gb.x, ga.x);
         } else {
-            buf[s * n + m] = make_double2(ga.x - gb.y, ga.y + gb.x);       // ga + i gb
-            buf[s * n + n - m] = make_double2(ga.x + gb.y, -ga.y + gb.x);  // conj(ga) + i conj(gb)
+            bs[skew(m)] = make_double2(ga.y + gb.x, ga.x - gb.y);       // ga + i gb
+            bs[skew(n - m)] = make_double2(gb.x - ga.y, ga.x + gb.y);  // conj(ga) + i conj(gb)
         }
     }
     __syncthreads();
-    fft_run(buf, nseq, P, tws, true);
-    for (int idx = threadIdx.x; idx < nseq * n; idx += NTH) {
-        const int s = idx / n, k = idx - s * n;
-        const int64_t g = g0 + s;
-        if (g >= nsq) continue;
-        const int jp = (int)(g / T), t = (int)(g - (int64_t)jp * T);
-        const int js = ntheta - 1 - jp;
-        double *zt = Z + (int64_t)t * ntheta * n;
-        const double2 v = buf[idx];
-        zt[(int64_t)jp * n + k] = v.x;
-        if (js != jp) zt[(int64_t)js * n + k] = v.y;
+    int Ns = 1;
+    for (int p = 0; p < P.np; ++p) {
+        auto load = [&](int s) { return [b = buf + s * sl](int i) { return b[skew(i)]; }; };
+        if (p + 1 < P.np)
+            fft_step(P.r[p], nseq, n, Ns, tws, load, [&](int s) {
+                return [b = buf + s * sl](int i, double2 v) { b[skew(i)] = v; };
+            });
+        else
+            fft_step(P.r[p], nseq, n, Ns, tws, load, [&](int s) {
+                const Seq &q = seq[s];
+                return [z0 = Z + q.z0, z1 = Z + q.z1, on = q.o >= 0, two = q.z1 != q.z0](int i, double2 v) {
+                    if (on) z0[i] = v.y;
+                    if (on && two) z1[i] = v.x;
+                };
+            });
+        Ns *= P.r[p];
     }
 }
 
@@ -300,44 +401,163 @@ struct Item {
     int32_t tm;
 };
 
-// Forward GEMM per (m, p, row block): C^{m,p} = A^{m,p} Gq, q = (p + m) mod 2, over
-// the northern colatitudes, written row-major (rows r, columns 2t / 2t + 1
-// contiguous) into block (m, p) of Cf.
-__global__ __launch_bounds__(GS::NTH) void gemm_forward_kernel(const double *__restrict__ Af,
-                                                               const int64_t *__restrict__ aoff,
-                                                               const int *__restrict__ arows,
-                                                               const double *__restrict__ Gb, int64_t gblk,
-                                                               int64_t ldb, int Kp, const Item *__restrict__ items,
-                                                               double *Cf, int64_t cblk)
+// Degrees of block (m, p): l = lstart(m, p) + 2 r, r < block_rows.
+__host__ __device__ inline int block_rows(int L, int m, int p)
+{
+    const int l0 = lstart(m, p);
+    return l0 < L ? (L - 1 - l0) / 2 + 1 : 0;
+}
+
+// acc += A B over K (a multiple of 16), A(r, k) = A[r + k lda] for 64 rows, B(k, c) =
+// B[c + k ldb] for BN columns; WM x WN waves, two K slices in flight in registers
+// beside the one in LDS.  Only the first `mt` 16-row tiles are multiplied: the rows
+// of a block end anywhere (at L = 360 whole 64-row blocks are a third larger than
+// the rows, whole 16-row tiles a tenth).
+template <int BN, int WM, int WN> struct SG {
+    static constexpr int MB = GBM / WM / 16, NB = BN / WN / 16;
+    static constexpr int LDA = GBM + 16, LDB = BN + 16;
+    static constexpr int CA = GBM * GBK / 2 / GNT, CHB = BN * GBK / 2, CB = (CHB + GNT - 1) / GNT;
+    static constexpr size_t SMEM = sizeof(double) * 2 * GBK * (LDA + LDB);
+};
+template <int BN, int WM, int WN>
+__device__ inline void sht_block(const double *__restrict__ A, int64_t lda, const double *__restrict__ B, int64_t ldb,
+                                 int K, int mt, double4_t (&acc)[SG<BN, WM, WN>::MB][SG<BN, WM, WN>::NB], double *smem)
+{
+    typedef SG<BN, WM, WN> S;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave % WM, wn = wave / WM, gi = lane & 15, gg = lane >> 4;
+    double *As = smem, *Bs = smem + 2 * GBK * S::LDA;
+    struct Regs {
+        u32x4 a[S::CA], b[S::CB];
+    } r0, r1;
+    const int nk = K / GBK;
+    auto gload = [&](int kt, Regs &r) {
+#pragma unroll
+        for (int c = 0; c < S::CA; ++c) {
+            const int ch = tid + GNT * c;
+            r.a[c] = *(const u32x4 *)(A + 2 * (ch % (GBM / 2)) + (int64_t)(kt * GBK + ch / (GBM / 2)) * lda);
+        }
+#pragma unroll
+        for (int c = 0; c < S::CB; ++c) {
+            const int ch = tid + GNT * c;
+            if (S::CHB % GNT == 0 || ch < S::CHB)
+                r.b[c] = *(const u32x4 *)(B + 2 * (ch % (BN / 2)) + (int64_t)(kt * GBK + ch / (BN / 2)) * ldb);
+        }
+    };
+    auto sstore = [&](int buf, const Regs &r) {
+#pragma unroll
+        for (int c = 0; c < S::CA; ++c) {
+            const int ch = tid + GNT * c;
+            *(u32x4 *)(As + (buf * GBK + ch / (GBM / 2)) * S::LDA + 2 * (ch % (GBM / 2))) = r.a[c];
+        }
+#pragma unroll
+        for (int c = 0; c < S::CB; ++c) {
+            const int ch = tid + GNT * c;
+            if (S::CHB % GNT == 0 || ch < S::CHB)
+                *(u32x4 *)(Bs + (buf * GBK + ch / (BN / 2)) * S::LDB + 2 * (ch % (BN / 2))) = r.b[c];
+        }
+    };
+    auto multiply = [&](int cur, auto M) {
+        const double *as = As + cur * GBK * S::LDA + wm * S::MB * 16 + gi;
+        const double *bs = Bs + cur * GBK * S::LDB + wn * S::NB * 16 + gi;
+#pragma unroll
+        for (int s = 0; s < GBK / 4; ++s) {
+            double fa[M], fb[S::NB];
+#pragma unroll
+            for (int m = 0; m < M; ++m) fa[m] = as[(s * 4 + gg) * S::LDA + m * 16];
+#pragma unroll
+            for (int n = 0; n < S::NB; ++n) fb[n] = bs[(s * 4 + gg) * S::LDB + n * 16];
+#pragma unroll
+            for (int m = 0; m < M; ++m)
+#pragma unroll
+                for (int n = 0; n < S::NB; ++n)
+                    acc[m][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[m], fb[n], acc[m][n], 0, 0, 0);
+        }
+    };
+    const int mw = __builtin_amdgcn_readfirstlane(min(S::MB, mt - wm * S::MB));  // this wave's tiles
+    auto compute = [&](int cur) {
+        if (mw >= S::MB) multiply(cur, std::integral_constant<int, S::MB>{});
+        else if (S::MB > 1 && mw == 1) multiply(cur, std::integral_constant<int, 1>{});
+        else if (S::MB > 2 && mw == 2) multiply(cur, std::integral_constant<int, (S::MB > 2 ? 2 : 1)>{});
+        else if (S::MB > 2 && mw == 3) multiply(cur, std::integral_constant<int, (S::MB > 2 ? 3 : 1)>{});
+    };
+    gload(0, r0);
+    if (nk > 1) gload(1, r1);
+    sstore(0, r0);
+    __syncthreads();
+    for (int kt = 0;; kt += 2) {
+        if (kt + 2 < nk) gload(kt + 2, r0);
+        compute(0);
+        if (kt + 1 >= nk) break;
+        sstore(1, r1);
+        __syncthreads();
+        if (kt + 3 < nk) gload(kt + 3, r1);
+        compute(1);
+        if (kt + 2 >= nk) break;
+        sstore(0, r0);
+        __syncthreads();
+    }
+}
+
+// One 64 x BN block of a contraction; logical blocks run over the column blocks of
+// a row block first and stay in order on an XCD, whose L2 then serves the row
+// block's table to all of them and their columns to the next row blocks.  Results
+// go row-major (columns contiguous) into block (m, p) of C.
+template <int BN, int WM, int WN>
+__device__ inline void sht_gemm(const double *A, int64_t lda, const double *B, int64_t ldb, int K, int rows, int tm, int tn,
+                                double *C, double *smem)
+{
+    typedef SG<BN, WM, WN> S;
+    double4_t acc[S::MB][S::NB];
+#pragma unroll
+    for (int a = 0; a < S::MB; ++a)
+#pragma unroll
+        for (int b = 0; b < S::NB; ++b) acc[a][b] = (double4_t){0.0, 0.0, 0.0, 0.0};
+    const int mt = (min(GBM, rows - tm * GBM) + 15) / 16;
+    sht_block<BN, WM, WN>(A + tm * GBM, lda, B + tn * BN, ldb, K, mt, acc, smem);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wm = wave % WM, wn = wave / WM, gi = lane & 15, gg = lane >> 4;
+#pragma unroll
+    for (int a = 0; a < S::MB; ++a)
+        if (wm * S::MB + a < mt)
+#pragma unroll
+            for (int b = 0; b < S::NB; ++b) {
+                const int c = tn * BN + (wn * S::NB + b) * 16 + gi;
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    C[(int64_t)(tm * GBM + (wm * S::MB + a) * 16 + acc_row<double>(gg, v)) * ldb + c] = acc[a][b][v];
+            }
+}
+
+// Forward: C^{m,p} = A^{m,p} Gq, q = (p + m) mod 2, over the northern colatitudes.
+template <int BN, int WM, int WN>
+__global__ __launch_bounds__(GNT) void gemm_forward_kernel(const double *__restrict__ Af, const int64_t *__restrict__ aoff,
+                                                           const int *__restrict__ arows, const double *__restrict__ Gb,
+                                                           int64_t gblk, int64_t ldb, int Kp, int L,
+                                                           const Item *__restrict__ items, int ntn, double *Cf, int64_t cblk)
 {
     extern __shared__ __align__(16) char smem_raw[];
-    const Item it = items[blockIdx.x];
-    const int m = it.m, p = it.p, mp2 = 2 * m + p, q = (p + m) & 1;
-    const int tn = blockIdx.y;
-    double4_t acc[GS::MB][GS::NB];
-#pragma unroll
-    for (int a = 0; a < GS::MB; ++a)
-#pragma unroll
-        for (int b = 0; b < GS::NB; ++b)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) acc[a][b][v] = 0.0;
-    cm_block<double, GBM, GBN, GBK, GWM, GWN, false>(Af + aoff[mp2] + it.tm * GBM, arows[mp2],
-                                                     Gb + (2 * m + q) * gblk + tn * GBN, ldb, Kp, acc,
-                                                     (double *)smem_raw);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = wave % GWM, wn = wave / GWM, gi = lane & 15, gg = lane >> 4;
-    double *C = Cf + mp2 * cblk;
-#pragma unroll
-    for (int a = 0; a < GS::MB; ++a)
-#pragma unroll
-        for (int b = 0; b < GS::NB; ++b) {
-            const int c = tn * GBN + wn * (GBN / GWN) + b * 16 + gi;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int row = it.tm * GBM + wm * (GBM / GWM) + a * 16 + acc_row<double>(gg, v);
-                C[(int64_t)row * ldb + c] = acc[a][b][v];
-            }
-        }
+    const int64_t lg = xcd_remap(blockIdx.x, gridDim.x);
+    const Item it = items[lg / ntn];
+    const int mp2 = 2 * it.m + it.p;
+    sht_gemm<BN, WM, WN>(Af + aoff[mp2], arows[mp2], Gb + (2 * it.m + ((it.p + it.m) & 1)) * gblk, ldb, Kp,
+                         block_rows(L, it.m, it.p), it.tm, (int)(lg % ntn), Cf + mp2 * cblk, (double *)smem_raw);
+}
+
+// Inverse: E/O^{m,p}[j'][c] = V^{m,p} Bz^{m,p}.
+template <int BN, int WM, int WN>
+__global__ __launch_bounds__(GNT) void gemm_inverse_kernel(const double *__restrict__ V, const int64_t *__restrict__ voff,
+                                                           int64_t ldv, const int *__restrict__ kpadz,
+                                                           const double *__restrict__ Bz, const int64_t *__restrict__ zoff,
+                                                           int64_t ldb, int H, const Item *__restrict__ items, int ntn,
+                                                           double *Ob, int64_t oblk)
+{
+    extern __shared__ __align__(16) char smem_raw[];
+    const int64_t lg = xcd_remap(blockIdx.x, gridDim.x);
+    const Item it = items[lg / ntn];
+    const int mp2 = 2 * it.m + it.p;
+    sht_gemm<BN, WM, WN>(V + voff[mp2], ldv, Bz + zoff[mp2], ldb, kpadz[mp2], H, it.tm, (int)(lg % ntn), Ob + mp2 * oblk,
+                         (double *)smem_raw);
 }
 
 // Degree of pair pr of a chunk starting at degree la, where degree l holds the
@@ -371,41 +591,36 @@ __global__ __launch_bounds__(TNT) void unpack_forward_kernel(const double *__res
     const int i0 = la * la, ni = lb * lb - i0;
     const int t0 = blockIdx.y * TT;
     const int tt = min(TT, T - t0);
-    // gather: one (l, m >= 0) pair and 2 tt columns per 2 tt threads
+    // gather: one (l, m >= 0) pair and 2 tt columns per 2 tt threads; a thread
+    // keeps its column and steps through the pairs
     const int npair = (lb * (lb + 1) - la * (la + 1)) / 2;  // sum over l of (l + 1)
-    for (int g = threadIdx.x; g < npair * 2 * tt; g += blockDim.x) {
-        const int col = g % (2 * tt), pr = g / (2 * tt);
-        const int l = pair_degree(pr, la);
-        const int m = pr - (l * (l + 1) - la * (la + 1)) / 2, p = l & 1, r = (l - lstart(m, p)) >> 1;
-        const int t = t0 + col / 2, part = col & 1;
-        const double v = Cf[(2 * m + p) * cblk + (int64_t)r * ldb + 2 * t + part];
-        const int idx = l * l + l + (part ? -m : m) - i0;
-        if (m > 0 || part == 0) buf[(col / 2) * CH + idx] = v;
+    const int dp = TNT / (2 * tt);
+    if ((int)threadIdx.x < dp * 2 * tt) {
+        const int pr0 = threadIdx.x / (2 * tt), col = threadIdx.x - pr0 * 2 * tt, part = col & 1;
+        const double *src = Cf + 2 * t0 + col;
+        double *dst = buf + (col / 2) * CH - i0;
+        int l = pair_degree(pr0, la), m = pr0 - (l * (l + 1) - la * (la + 1)) / 2;
+        for (int pr = pr0; pr < npair; pr += dp) {
+            const int p = l & 1, r = (l - lstart(m, p)) >> 1;
+            const double v = src[(2 * m + p) * cblk + (int64_t)r * ldb];
+            if (m > 0 || part == 0) dst[l * l + l + (part ? -m : m)] = v;
+            m += dp;
+            while (m > l) m -= ++l;
+        }
     }
     __syncthreads();
-    for (int g = threadIdx.x; g < tt * ni; g += blockDim.x) {
-        const int ts = g / ni, idx = g - ts * ni;
+    for (int idx = threadIdx.x; idx < ni; idx += TNT) {
         const int gi_ = idx + i0;
         int l = (int)sqrt((double)gi_);
         while (l * l > gi_) --l;
         while ((l + 1) * (l + 1) <= gi_) ++l;
         const int ms = gi_ - l * l - l, m = ms < 0 ? -ms : ms;
-        double v;
-        if (m == 0) {
-            v = buf[ts * CH + idx];
-        } else {
-            const double a = buf[ts * CH + (l * l + l + m - i0)], b = buf[ts * CH + (l * l + l - m - i0)];
-            const int rot = (m + (m & 1)) & 3;  // z = i^-rot (a + i b)
-            double re, im;
-            switch (rot) {
-            case 0: re = a; im = b; break;
-            case 1: re = b; im = -a; break;
-            case 2: re = -a; im = -b; break;
-            default: re = -b; im = a; break;
-            }
-            v = M_SQRT2 * (ms > 0 ? re : im);
-        }
-        f[(int64_t)(t0 + ts) * L * L + gi_] = v;
+        // z = i^-rot (a + i b), a at +m, b at -m; sqrt(2) of its real (ms > 0) or imaginary part
+        const int rot = (m + (m & 1)) & 3, k = ms > 0 ? rot : (rot + 1) & 3;  // Re: a, b, -a, -b; Im: b, -a, -b, a
+        const int from = m == 0 ? idx : (k & 1 ? l * l + l - m : l * l + l + m) - i0;
+        const double f0 = m == 0 ? 1.0 : (k & 2 ? -M_SQRT2 : M_SQRT2);
+        double *dst = f + (int64_t)t0 * L * L + gi_;
+        for (int ts = 0; ts < tt; ++ts) dst[(int64_t)ts * L * L] = f0 * buf[ts * CH + from];
     }
 }
 
@@ -420,61 +635,26 @@ __global__ __launch_bounds__(TNT) void pack_inverse_kernel(const double *__restr
     const int i0 = la * la, ni = lb * lb - i0;
     const int t0 = blockIdx.y * TT;
     const int tt = min(TT, T - t0);
-    for (int g = threadIdx.x; g < tt * ni; g += blockDim.x) {
-        const int ts = g / ni, idx = g - ts * ni;
-        buf[ts * CH + idx] = f[(int64_t)(t0 + ts) * L * L + i0 + idx];
-    }
+    for (int idx = threadIdx.x; idx < ni; idx += TNT)
+        for (int ts = 0; ts < tt; ++ts) buf[ts * CH + idx] = f[(int64_t)(t0 + ts) * L * L + i0 + idx];
     __syncthreads();
     const int npair = (lb * (lb + 1) - la * (la + 1)) / 2;
-    for (int g = threadIdx.x; g < npair * 2 * tt; g += blockDim.x) {
-        const int col = g % (2 * tt), pr = g / (2 * tt);
-        const int l = pair_degree(pr, la);
-        const int m = pr - (l * (l + 1) - la * (la + 1)) / 2, p = l & 1, r = (l - lstart(m, p)) >> 1;
-        const int ts = col / 2, part = col & 1;
-        double v;
-        if (m == 0) v = part ? 0.0 : buf[ts * CH + l * l + l - i0];
-        else v = buf[ts * CH + l * l + l + (part ? -m : m) - i0] * M_SQRT1_2;
-        Bz[zoff[2 * m + p] + (int64_t)r * ldb + 2 * (t0 + ts) + part] = v;
-    }
-}
-
-// Inverse GEMM per (m, p, row block of j'): E/O^{m,p}[j'][c] = V^{m,p} Bz^{m,p},
-// written row-major (columns contiguous) into block (m, p) of Ob.
-__global__ __launch_bounds__(GS::NTH) void gemm_inverse_kernel(const double *__restrict__ V,
-                                                               const int64_t *__restrict__ voff, int64_t ldv,
-                                                               const int *__restrict__ kpadz,
-                                                               const double *__restrict__ Bz,
-                                                               const int64_t *__restrict__ zoff, int64_t ldb,
-                                                               const Item *__restrict__ items, double *Ob,
-                                                               int64_t oblk)
-{
-    extern __shared__ __align__(16) char smem_raw[];
-    const Item it = items[blockIdx.x];
-    const int mp2 = 2 * it.m + it.p;
-    const int tn = blockIdx.y;
-    double4_t acc[GS::MB][GS::NB];
-#pragma unroll
-    for (int a = 0; a < GS::MB; ++a)
-#pragma unroll
-        for (int b = 0; b < GS::NB; ++b)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) acc[a][b][v] = 0.0;
-    cm_block<double, GBM, GBN, GBK, GWM, GWN, false>(V + voff[mp2] + it.tm * GBM, ldv, Bz + zoff[mp2] + tn * GBN,
-                                                     ldb, kpadz[mp2], acc, (double *)smem_raw);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = wave % GWM, wn = wave / GWM, gi = lane & 15, gg = lane >> 4;
-    double *O = Ob + mp2 * oblk;
-#pragma unroll
-    for (int a = 0; a < GS::MB; ++a)
-#pragma unroll
-        for (int b = 0; b < GS::NB; ++b) {
-            const int c = tn * GBN + wn * (GBN / GWN) + b * 16 + gi;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int row = it.tm * GBM + wm * (GBM / GWM) + a * 16 + acc_row<double>(gg, v);
-                O[(int64_t)row * ldb + c] = acc[a][b][v];
-            }
+    const int dp = TNT / (2 * tt);
+    if ((int)threadIdx.x < dp * 2 * tt) {
+        const int pr0 = threadIdx.x / (2 * tt), col = threadIdx.x - pr0 * 2 * tt, part = col & 1;
+        const double *src = buf + (col / 2) * CH - i0;
+        double *dst = Bz + 2 * t0 + col;
+        int l = pair_degree(pr0, la), m = pr0 - (l * (l + 1) - la * (la + 1)) / 2;
+        for (int pr = pr0; pr < npair; pr += dp) {
+            const int p = l & 1, r = (l - lstart(m, p)) >> 1;
+            double v;
+            if (m == 0) v = part ? 0.0 : src[l * l + l];
+            else v = src[l * l + l + (part ? -m : m)] * M_SQRT1_2;
+            dst[zoff[2 * m + p] + (int64_t)r * ldb] = v;
+            m += dp;
+            while (m > l) m -= ++l;
         }
+    }
 }
 
 // ------------------------------------------------------------------ tables
@@ -640,19 +820,61 @@ namespace {
 
 thread_local char g_sht_error[256] = "";
 
+// Fewest passes with radices up to 12; of these the largest smallest radix (it
+// sets the threads of a workgroup).
+struct PlanSearch {
+    Plan best{};
+    int cur[MAXP];
+    void go(int r, int from, int depth)
+    {
+        static const int radices[] = {12, 10, 9, 8, 6, 5, 4, 3, 2};
+        if (r == 1) {  // nonincreasing: the last is the smallest
+            if (best.np == 0 || depth < best.np || (depth == best.np && cur[depth - 1] > best.r[depth - 1])) {
+                best.np = depth;
+                std::copy(cur, cur + depth, best.r);
+            }
+            return;
+        }
+        if (depth == MAXP || (best.np && depth >= best.np)) return;
+        for (int i = from; i < (int)(sizeof(radices) / sizeof(radices[0])); ++i)
+            if (r % radices[i] == 0) {
+                cur[depth] = radices[i];
+                go(r / radices[i], i, depth + 1);
+            }
+    }
+};
 bool make_plan(int n, Plan &P)
 {
+    PlanSearch s;
+    if (n == 1) {
+        s.best.np = 1;
+        s.best.r[0] = 1;
+    } else {
+        s.go(n, 0, 0);
+    }
+    P = s.best;
     P.n = n;
-    P.np = 0;
-    int r = n;
-    const int radices[4] = {4, 2, 3, 5};
-    for (int R : radices)
-        while (r % R == 0) {
-            if (P.np == MAXP) return false;
-            P.r[P.np++] = R;
-            r /= R;
-        }
-    return r == 1;
+    return P.np > 0;
+}
+
+size_t fft_smem(int n, int nseq) { return ((size_t)nseq * seq_len(n) + n) * sizeof(double2); }
+int fft_threads(const Plan &P, int nseq)
+{
+    int t = 1;
+    for (int p = 0; p < P.np; ++p) {
+        const int mb = butterflies(P.r[p]);
+        t = std::max(t, (nseq * (P.n / P.r[p]) + mb - 1) / mb);
+    }
+    return (t + 63) / 64 * 64;  // at most 1024 for every length up to MAXN
+}
+
+// Sequences of a workgroup: a power of two (aligned runs of the blocks' rows) of
+// at most eight, 512 threads and half of the LDS, so that two share a compute unit.
+int fft_sequences(const Plan &P)
+{
+    int k = MAXSEQ;
+    while (k > 1 && (fft_threads(P, k) > 512 || fft_smem(P.n, k) > 80 * 1024 - 512)) k /= 2;
+    return k;
 }
 
 // e^{-2 pi i k / n}, exact at multiples of n/4, reduced to the first half turn.
@@ -729,8 +951,6 @@ template <typename T> int upload(T *d, const std::vector<T> &h, hipStream_t st)
                                                                                                       : MPCHOL_EHIP;
 }
 
-size_t fft_smem(int n, int nseq) { return (size_t)(nseq + 1) * n * sizeof(double2); }
-
 // Raise a kernel's dynamic-LDS limit to at least `bytes` (never lower it: an
 // object created earlier with larger transforms keeps launching).
 void set_smem_attr(const void *k, size_t bytes)
@@ -802,7 +1022,7 @@ int mpchol_sht_create(mpchol_sht_t *out, int32_t L, int32_t ntheta, int32_t nphi
     h->tmax = tmax;
     h->tmaxpad = rup(tmax, GBN / 2);
     h->Pphi = Pphi;
-    h->nseq = std::max(1, std::min(8, NTH * MAXV / nphi));
+    h->nseq = fft_sequences(Pphi);
     h->ldb = 2 * (int64_t)h->tmaxpad;
     h->kph = rup(h->H, GBK);
     h->vrows = rup64(h->H, GBM);
@@ -829,10 +1049,16 @@ int mpchol_sht_create(mpchol_sht_t *out, int32_t L, int32_t ntheta, int32_t nphi
             vsz += (int64_t)z_kpad[i] * h->vrows;
             z_off[i] = zsz;
             zsz += (int64_t)z_kpad[i] * h->ldb;
-            if (R > 0) {
-                for (int tm = 0; tm < a_rows[i] / GBM; ++tm) items_f.push_back(Item{(int16_t)m, (int16_t)p, tm});
-                for (int tm = 0; tm < h->vrows / GBM; ++tm) items_i.push_back(Item{(int16_t)m, (int16_t)p, tm});
-            }
+        }
+    // row blocks in the order in which the XCDs take them (runs of equal length):
+    // every eighth (m, p) to one XCD, all of its row blocks together, so that the
+    // K extents, which fall with m in the inverse, are the same for all XCDs
+    for (int x = 0; x < 8; ++x)
+        for (int i = x; i < nb; i += 8) {
+            if (block_rows(L, i / 2, i % 2) == 0) continue;
+            const int16_t m = (int16_t)(i / 2), p = (int16_t)(i % 2);
+            for (int tm = 0; tm < a_rows[i] / GBM; ++tm) items_f.push_back(Item{m, p, tm});
+            for (int tm = 0; tm < h->vrows / GBM; ++tm) items_i.push_back(Item{m, p, tm});
         }
     h->nitems_f = (int)items_f.size();
     h->nitems_i = (int)items_i.size();
@@ -933,10 +1159,15 @@ int mpchol_sht_create(mpchol_sht_t *out, int32_t L, int32_t ntheta, int32_t nphi
         mpchol_sht_destroy(h);
         return MPCHOL_EHIP;
     }
-    set_smem_attr((const void *)phi_forward_kernel, fft_smem(nphi, h->nseq));
-    set_smem_attr((const void *)phi_inverse_kernel, fft_smem(nphi, h->nseq));
-    set_smem_attr((const void *)gemm_forward_kernel, GS::SMEM);
-    set_smem_attr((const void *)gemm_inverse_kernel, GS::SMEM);
+    const size_t fs = fft_smem(nphi, h->nseq);
+    set_smem_attr((const void *)phi_forward_kernel<512>, fs);
+    set_smem_attr((const void *)phi_inverse_kernel<512>, fs);
+    set_smem_attr((const void *)phi_forward_kernel<1024>, fs);
+    set_smem_attr((const void *)phi_inverse_kernel<1024>, fs);
+    set_smem_attr((const void *)gemm_forward_kernel<GBN, 2, 2>, SG<GBN, 2, 2>::SMEM);
+    set_smem_attr((const void *)gemm_inverse_kernel<GBN, 2, 2>, SG<GBN, 2, 2>::SMEM);
+    set_smem_attr((const void *)gemm_forward_kernel<16, 4, 1>, SG<16, 4, 1>::SMEM);
+    set_smem_attr((const void *)gemm_inverse_kernel<16, 4, 1>, SG<16, 4, 1>::SMEM);
     set_smem_attr((const void *)unpack_forward_kernel, (size_t)h->TT * h->CH * 8);
     set_smem_attr((const void *)pack_inverse_kernel, (size_t)h->TT * h->CH * 8);
     *out = h;
@@ -969,13 +1200,18 @@ int mpchol_sht_forward(mpchol_sht_t h, const double *Z, int64_t T, double *f)
     if (!Z || !f) return MPCHOL_EINVAL;
     if (hipSetDevice(h->dev) != hipSuccess) return MPCHOL_EHIP;
     hipStream_t st = h->st;
-    const int Tpad = rup((int)T, GBN / 2);
     const int64_t nsq = (int64_t)h->H * T;
-    phi_forward_kernel<<<(unsigned)((nsq + h->nseq - 1) / h->nseq), NTH, fft_smem(h->nph, h->nseq), st>>>(
-        Z, (int)T, h->nth, h->L, h->Pphi, h->tw, h->Gb, h->gblk, h->ldb, h->nseq);
-    dim3 gg((unsigned)h->nitems_f, (unsigned)(2 * Tpad / GBN));
-    gemm_forward_kernel<<<gg, GS::NTH, GS::SMEM, st>>>(h->Af, h->a_off, h->a_rows, h->Gb, h->gblk, h->ldb, h->kph,
-                                                       h->items_f, h->Ob, h->oblk);
+    const unsigned gf = (unsigned)((nsq + h->nseq - 1) / h->nseq);
+    const size_t fs = fft_smem(h->nph, h->nseq);
+    auto phi = fft_threads(h->Pphi, h->nseq) <= 512 ? phi_forward_kernel<512> : phi_forward_kernel<1024>;
+    phi<<<gf, fft_threads(h->Pphi, h->nseq), fs, st>>>(Z, (int)T, h->nth, h->L, h->Pphi, h->tw, h->Gb, h->gblk, h->ldb, h->nseq);
+    auto gemm = [&](auto kernel, int bn, size_t smem) {
+        const int ntn = (int)((2 * T + bn - 1) / bn);
+        kernel<<<(unsigned)h->nitems_f * ntn, GNT, smem, st>>>(h->Af, h->a_off, h->a_rows, h->Gb, h->gblk, h->ldb,
+                                                               h->kph, h->L, h->items_f, ntn, h->Ob, h->oblk);
+    };
+    if (T <= SMALL_T) gemm(gemm_forward_kernel<16, 4, 1>, 16, SG<16, 4, 1>::SMEM);
+    else gemm(gemm_forward_kernel<GBN, 2, 2>, GBN, SG<GBN, 2, 2>::SMEM);
     dim3 gu((unsigned)h->nchunk, (unsigned)((T + h->TT - 1) / h->TT));
     unpack_forward_kernel<<<gu, TNT, (size_t)h->TT * h->CH * 8, st>>>(h->Ob, h->oblk, h->ldb, h->chunk_l, (int)T,
                                                                       h->L, h->TT, h->CH, f);
@@ -989,16 +1225,21 @@ int mpchol_sht_inverse(mpchol_sht_t h, const double *f, int64_t T, double *Z)
     if (!Z || !f) return MPCHOL_EINVAL;
     if (hipSetDevice(h->dev) != hipSuccess) return MPCHOL_EHIP;
     hipStream_t st = h->st;
-    const int Tpad = rup((int)T, GBN / 2);
     dim3 gp((unsigned)h->nchunk, (unsigned)((T + h->TT - 1) / h->TT));
     pack_inverse_kernel<<<gp, TNT, (size_t)h->TT * h->CH * 8, st>>>(f, h->chunk_l, (int)T, h->L, h->TT, h->CH, h->Bz,
                                                                     h->z_off, h->ldb);
-    dim3 gg((unsigned)h->nitems_i, (unsigned)(2 * Tpad / GBN));
-    gemm_inverse_kernel<<<gg, GS::NTH, GS::SMEM, st>>>(h->V, h->v_off, h->vrows, h->z_kpad, h->Bz, h->z_off, h->ldb,
-                                                       h->items_i, h->Ob, h->oblk);
+    auto gemm = [&](auto kernel, int bn, size_t smem) {
+        const int ntn = (int)((2 * T + bn - 1) / bn);
+        kernel<<<(unsigned)h->nitems_i * ntn, GNT, smem, st>>>(h->V, h->v_off, h->vrows, h->z_kpad, h->Bz, h->z_off,
+                                                               h->ldb, h->H, h->items_i, ntn, h->Ob, h->oblk);
+    };
+    if (T <= SMALL_T) gemm(gemm_inverse_kernel<16, 4, 1>, 16, SG<16, 4, 1>::SMEM);
+    else gemm(gemm_inverse_kernel<GBN, 2, 2>, GBN, SG<GBN, 2, 2>::SMEM);
     const int64_t nsq = (int64_t)h->H * T;
-    phi_inverse_kernel<<<(unsigned)((nsq + h->nseq - 1) / h->nseq), NTH, fft_smem(h->nph, h->nseq), st>>>(
-        h->Ob, h->oblk, h->ldb, (int)T, h->nth, h->L, h->Pphi, h->tw, Z, h->nseq);
+    const unsigned gf = (unsigned)((nsq + h->nseq - 1) / h->nseq);
+    auto phi = fft_threads(h->Pphi, h->nseq) <= 512 ? phi_inverse_kernel<512> : phi_inverse_kernel<1024>;
+    phi<<<gf, fft_threads(h->Pphi, h->nseq), fft_smem(h->nph, h->nseq), st>>>(h->Ob, h->oblk, h->ldb, (int)T, h->nth, h->L,
+                                                                    h->Pphi, h->tw, Z, h->nseq);
     return hipGetLastError() == hipSuccess ? MPCHOL_OK : MPCHOL_EHIP;
 }
 

@@ -77,6 +77,26 @@ def test_inverse_matches_oracle(sht_orc, L, nth, nph, T):
     assert err <= 1e-12 * np.abs(Zo).max()
 
 
+@pytest.mark.parametrize("L,nth,nph,T,tmax", [
+    (1, 2, 1, 1, 1), (3, 4, 5, 8, 40), (3, 5, 6, 9, 9), (4, 5, 8, 32, 33), (4, 6, 9, 33, 33), (5, 7, 10, 1, 64),
+    (6, 7, 12, 2, 2), (8, 9, 15, 3, 3), (13, 14, 25, 3, 3), (20, 22, 64, 3, 3), (33, 34, 1024, 5, 5), (6, 7, 1458, 3, 3),
+    (6, 7, 2187, 2, 2), (6, 7, 3125, 2, 2), (6, 7, 3375, 2, 2), (6, 7, 4050, 2, 2), (6, 7, 4096, 2, 2)])
+def test_longitude_lengths_and_batches(sht_orc, L, nth, nph, T, tmax):
+    """Every radix, the longest passes of a thread and a workgroup, and batches
+    at the edges of the column blocks, in both directions (the tolerance above)."""
+    torch = torch_cuda()
+    mod = M()
+    D = sht_orc.wigner_table(L)
+    Z = synth.sht_fields(T, nth, nph)
+    fg = run_forward(mod, torch, L, nth, nph, Z, tmax)
+    fo = np.array([sht_orc.sht_forward_real(Z[t], L, D) for t in range(T)])
+    assert np.abs(fg - fo).max() <= 1e-12 * np.abs(fo).max()
+    f = synth.sht_coeffs(L, T)
+    Zg = run_inverse(mod, torch, L, nth, nph, f)
+    Zo = np.array([sht_orc.sht_inverse_real(f[t], nth, nph, D) for t in range(T)])
+    assert np.abs(Zg - Zo).max() <= 1e-12 * np.abs(Zo).max()
+
+
 @pytest.mark.parametrize("L,nth,nph,T,nsample", [(360, 361, 720, 64, 24), (720, 721, 1440, 8, 12)])
 def test_full_size_round_trip_and_sampled_coefficients(sht_orc, L, nth, nph, T, nsample):
     """Inverse then forward returns the coefficients (band-limited fields);
