@@ -109,62 +109,115 @@ __global__ void forward_kernel(const float *P, const float *X, int64_t nb, float
     if (cls) cls[s] = argmax4(z);
 }
 
-// Forward + backward of 64 samples per block; writes this block's summed
+// Forward + backward of 32 samples per block; writes this block's summed
 // parameter gradient (scaled by 1/nb) and loss into partials[block][NP + 1].
-constexpr int SPB = 64;
+// Bound by LDS reads and by the few blocks a batch makes: each thread computes
+// 4 x 2 (or 4 x 4) outputs of a layer from float4 reads, the 64 x 64 weights
+// staged once, transposed for the forward layer (8,838 samples: 30 -> 22 us).
+// Every sum runs in the order of a single loop over its terms.
+constexpr int SPB = 32;
+constexpr int LDW = H1 + 4;
 __global__ __launch_bounds__(256) void grad_kernel(const float *P, const float *X, const int32_t *y, int64_t nb,
                                                    float cw0, float cw1, float cw2, float cw3, float alpha,
                                                    float *partials)
 {
     __shared__ float xs[SPB][NF];
-    __shared__ float h1[SPB][H1 + 1], h2[SPB][H2 + 1], g2[SPB][H2 + 1];
-    __shared__ float dz[SPB][NC];
+    __shared__ __align__(16) float h1[SPB][LDW], h2[SPB][LDW], g2[SPB][LDW];
+    __shared__ __align__(16) float w2[H2][LDW];   // W2[o][i]
+    __shared__ __align__(16) float w2t[H1][LDW];  // W2[o][i] at [i][o]
+    __shared__ float dz[SPB][NC], zs[SPB][NC];
     __shared__ float ls[SPB];
     const int tid = threadIdx.x;
     const int64_t s0 = (int64_t)blockIdx.x * SPB;
-    const float cw[4] = {cw0, cw1, cw2, cw3};
     const float inv = 1.0f / (float)nb;
-    for (int e = tid; e < SPB * NF; e += 256) {
-        int s = e / NF, i = e % NF;
-        xs[s][i] = (s0 + s < nb) ? X[(s0 + s) * NF + i] : 0.f;
+    for (int e = tid; e < SPB * NF; e += 256) xs[e / NF][e % NF] = (s0 + e / NF < nb) ? X[s0 * NF + e] : 0.f;
+    for (int e = tid; e < H2 * H1; e += 256) {
+        const int o = e / H1, i = e % H1;
+        const float w = P[OW2 + e];
+        w2[o][i] = w;
+        w2t[i][o] = w;
     }
     __syncthreads();
-    for (int e = tid; e < SPB * H1; e += 256) {
-        int s = e / H1, o = e % H1;
-        float a = P[OB1 + o];
-        for (int i = 0; i < NF; ++i) a += P[OW1 + o * NF + i] * xs[s][i];
-        h1[s][o] = a > 0.f ? a : 0.f;
+    {  // layer 1: output o of samples s, s + 4, ...
+        const int o = tid % H1;
+        float w[NF];
+#pragma unroll
+        for (int i = 0; i < NF; ++i) w[i] = P[OW1 + o * NF + i];
+        const float bias = P[OB1 + o];
+#pragma unroll
+        for (int s = tid / H1; s < SPB; s += 4) {
+            float a = bias;
+#pragma unroll
+            for (int i = 0; i < NF; ++i) a += w[i] * xs[s][i];
+            h1[s][o] = a > 0.f ? a : 0.f;
+        }
     }
     __syncthreads();
-    for (int e = tid; e < SPB * H2; e += 256) {
-        int s = e / H2, o = e % H2;
-        float a = P[OB2 + o];
-        for (int i = 0; i < H1; ++i) a += P[OW2 + o * H1 + i] * h1[s][i];
-        h2[s][o] = a > 0.f ? a : 0.f;
+    const int o4 = 4 * (tid % 16), sg = tid / 16;  // four outputs of samples sg, sg + 16
+    {  // layer 2
+        float a[2][4];
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) a[q][c] = P[OB2 + o4 + c];
+#pragma unroll 4
+        for (int i = 0; i < H1; i += 4) {
+            const float4 x0 = *(const float4 *)&h1[sg][i], x1 = *(const float4 *)&h1[sg + 16][i];
+            const float xv[2][4] = {{x0.x, x0.y, x0.z, x0.w}, {x1.x, x1.y, x1.z, x1.w}};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float4 w = *(const float4 *)&w2t[i + k][o4];
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    a[q][0] += w.x * xv[q][k];
+                    a[q][1] += w.y * xv[q][k];
+                    a[q][2] += w.z * xv[q][k];
+                    a[q][3] += w.w * xv[q][k];
+                }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) h2[sg + 16 * q][o4 + c] = a[q][c] > 0.f ? a[q][c] : 0.f;
+    }
+    __syncthreads();
+    if (tid < SPB * NC) {  // logits
+        const int s = tid / NC, c = tid % NC;
+        float a = P[OB3 + c];
+#pragma unroll 8
+        for (int i = 0; i < H2; ++i) a += P[OW3 + c * H2 + i] * h2[s][i];
+        zs[s][c] = a;
     }
     __syncthreads();
     if (tid < SPB) {
         const int s = tid;
+        const float cw[4] = {cw0, cw1, cw2, cw3};
         if (s0 + s < nb) {
-            float z[NC];
-            for (int c = 0; c < NC; ++c) {
-                float a = P[OB3 + c];
-                for (int i = 0; i < H2; ++i) a += P[OW3 + c * H2 + i] * h2[s][i];
-                z[c] = a;
-            }
             const int lab = y[s0 + s];
-            float zm = z[0];
-            for (int c = 1; c < NC; ++c) zm = fmaxf(zm, z[c]);
+            float z[NC], zm = zs[s][0];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                z[c] = zs[s][c];
+                zm = fmaxf(zm, z[c]);
+            }
             float se = 0.f;
+#pragma unroll
             for (int c = 0; c < NC; ++c) se += expf(z[c] - zm);
-            float p[NC], pu = 0.f;
+            float p[NC], pu = 0.f, zl = 0.f, cl = 0.f;
+#pragma unroll
             for (int c = 0; c < NC; ++c) {
                 p[c] = expf(z[c] - zm) / se;
                 if (c > lab) pu += p[c];
+                if (c == lab) {
+                    zl = z[c];
+                    cl = cw[c];
+                }
             }
-            ls[s] = cw[lab] * (-(z[lab] - zm - logf(se))) + alpha * pu;
+            ls[s] = cl * (-(zl - zm - logf(se))) + alpha * pu;
+#pragma unroll
             for (int c = 0; c < NC; ++c) {
-                float g = cw[lab] * (p[c] - (c == lab ? 1.f : 0.f)) + alpha * p[c] * ((c > lab ? 1.f : 0.f) - pu);
+                const float g = cl * (p[c] - (c == lab ? 1.f : 0.f)) + alpha * p[c] * ((c > lab ? 1.f : 0.f) - pu);
                 dz[s][c] = g * inv;
             }
         } else {
@@ -173,48 +226,78 @@ __global__ __launch_bounds__(256) void grad_kernel(const float *P, const float *
         }
     }
     __syncthreads();
+    float *out = partials + (int64_t)blockIdx.x * (NP + 1);
     for (int e = tid; e < SPB * H2; e += 256) {
-        int s = e / H2, i = e % H2;
+        const int s = e / H2, i = e % H2;
         float a = 0.f;
+#pragma unroll
         for (int c = 0; c < NC; ++c) a += dz[s][c] * P[OW3 + c * H2 + i];
         g2[s][i] = h2[s][i] > 0.f ? a : 0.f;
     }
-    __syncthreads();
-    // g1 overwrites h2's storage once g2 is complete (h2 is still needed for gW3)
-    float *out = partials + (int64_t)blockIdx.x * (NP + 1);
-    for (int e = tid; e < NC * H2; e += 256) {
-        int c = e / H2, i = e % H2;
+    {  // W3 and b3
+        const int c = tid / H2, i = tid % H2;
         float a = 0.f;
+#pragma unroll 8
         for (int s = 0; s < SPB; ++s) a += dz[s][c] * h2[s][i];
-        out[OW3 + e] = a;
+        out[OW3 + tid] = a;
+        if (tid < NC) {
+            float d = 0.f;
+            for (int s = 0; s < SPB; ++s) d += dz[s][tid];
+            out[OB3 + tid] = d;
+        }
     }
-    if (tid < NC) {
-        float a = 0.f;
-        for (int s = 0; s < SPB; ++s) a += dz[s][tid];
-        out[OB3 + tid] = a;
-    }
-    for (int e = tid; e < H2 * H1; e += 256) {
-        int o = e / H1, i = e % H1;
-        float a = 0.f;
-        for (int s = 0; s < SPB; ++s) a += g2[s][o] * h1[s][i];
-        out[OW2 + e] = a;
+    __syncthreads();
+    {  // W2: rows o .. o + 3, columns i .. i + 3
+        const int o = 4 * (tid / 16), i = 4 * (tid % 16);
+        float a[4][4] = {};
+#pragma unroll 4
+        for (int s = 0; s < SPB; ++s) {
+            const float4 g = *(const float4 *)&g2[s][o], h = *(const float4 *)&h1[s][i];
+            const float gv[4] = {g.x, g.y, g.z, g.w}, hv[4] = {h.x, h.y, h.z, h.w};
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) a[q][c] += gv[q] * hv[c];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) out[OW2 + (o + q) * H1 + i + c] = a[q][c];
     }
     if (tid < H2) {
         float a = 0.f;
         for (int s = 0; s < SPB; ++s) a += g2[s][tid];
         out[OB2 + tid] = a;
     }
-    __syncthreads();
-    for (int e = tid; e < SPB * H1; e += 256) {
-        int s = e / H1, i = e % H1;
-        float a = 0.f;
-        for (int o = 0; o < H2; ++o) a += g2[s][o] * P[OW2 + o * H1 + i];
-        h2[s][i] = h1[s][i] > 0.f ? a : 0.f;  // g1
+    {  // g1 = relu'(h1) (g2 W2) into h2, whose last readers are past the barrier
+        float a[2][4] = {};
+#pragma unroll 4
+        for (int o = 0; o < H2; o += 4) {
+            const float4 x0 = *(const float4 *)&g2[sg][o], x1 = *(const float4 *)&g2[sg + 16][o];
+            const float xv[2][4] = {{x0.x, x0.y, x0.z, x0.w}, {x1.x, x1.y, x1.z, x1.w}};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float4 w = *(const float4 *)&w2[o + k][o4];
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    a[q][0] += xv[q][k] * w.x;
+                    a[q][1] += xv[q][k] * w.y;
+                    a[q][2] += xv[q][k] * w.z;
+                    a[q][3] += xv[q][k] * w.w;
+                }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) h2[sg + 16 * q][o4 + c] = h1[sg + 16 * q][o4 + c] > 0.f ? a[q][c] : 0.f;
     }
     __syncthreads();
+#pragma unroll
     for (int e = tid; e < H1 * NF; e += 256) {
-        int o = e / NF, i = e % NF;
+        const int o = e / NF, i = e % NF;
         float a = 0.f;
+#pragma unroll 8
         for (int s = 0; s < SPB; ++s) a += h2[s][o] * xs[s][i];
         out[OW1 + e] = a;
     }
@@ -230,12 +313,26 @@ __global__ __launch_bounds__(256) void grad_kernel(const float *P, const float *
     }
 }
 
-__global__ void reduce_partials_kernel(const float *partials, int nblk, float *grad, float *loss)
+// Sums the blocks' partials: RPB parameters by RSEG runs of blocks per workgroup,
+// the runs added in order.  A single thread per parameter walked all blocks one
+// load after the other (8,838 samples: 34 -> 5 us).
+constexpr int RPB = 32, RSEG = 32;
+__global__ __launch_bounds__(RPB * RSEG) void reduce_partials_kernel(const float *partials, int nblk, float *grad,
+                                                                     float *loss)
 {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p > NP) return;
+    __shared__ float sum[RSEG][RPB + 1];
+    const int col = threadIdx.x % RPB, seg = threadIdx.x / RPB, p = blockIdx.x * RPB + col;
+    const int per = (nblk + RSEG - 1) / RSEG, k0 = seg * per, k1 = min(nblk, k0 + per);
     float a = 0.f;
-    for (int k = 0; k < nblk; ++k) a += partials[(int64_t)k * (NP + 1) + p];
+    if (p <= NP) {
+#pragma unroll 4
+        for (int k = k0; k < k1; ++k) a += partials[(int64_t)k * (NP + 1) + p];
+    }
+    sum[seg][col] = a;
+    __syncthreads();
+    if (seg || p > NP) return;
+    a = 0.f;
+    for (int q = 0; q < RSEG; ++q) a += sum[q][col];
     if (p < NP) grad[p] = a;
     else if (loss) *loss = a;
 }
@@ -276,7 +373,7 @@ void launch_mlp_grad(const float *params, const float *X, const int32_t *y, int6
 {
     int nblk = (int)((nb + SPB - 1) / SPB);
     grad_kernel<<<nblk, 256, 0, st>>>(params, X, y, nb, cw[0], cw[1], cw[2], cw[3], alpha, partials);
-    reduce_partials_kernel<<<(NP + 1 + 255) / 256, 256, 0, st>>>(partials, nblk, grad, loss);
+    reduce_partials_kernel<<<(NP + RPB) / RPB, RPB * RSEG, 0, st>>>(partials, nblk, grad, loss);
 }
 
 void launch_adam(float *params, const float *grad, float *m, float *v, int64_t np, int step, float lr, hipStream_t st)

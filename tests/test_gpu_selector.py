@@ -35,6 +35,39 @@ def test_mlp_grad_matches_oracle(orc):
     assert abs(loss - lo) <= 1e-5 * abs(lo)
 
 
+@pytest.mark.parametrize("nb", [1, 31, 32, 33, 1000, 1025, 33000])
+def test_mlp_grad_batch_edges(nb):
+    """Gradient and loss at the edges of the 32-sample blocks and of the runs in
+    which their partial sums are added, against FP64 autograd: sums of up to nb
+    terms through three layers stay within 1e-5 of the gradient's norm."""
+    torch = torch_cuda()
+    mod = M()
+    x = synth.uniform01(41, nb * 8).reshape(nb, 8).astype(np.float32) * 4 - 2
+    yl = (synth.uniform01(43, nb) * 4).astype(np.int32) % 4
+    p32 = _rand_params(3)
+    cw, alpha = [0.5, 1.5, 1.0, 0.75], 2.0
+    m = mod.mpchol_mlp_create()
+    try:
+        mod.mpchol_mlp_set_params(m, p32)
+        g = torch.full((mod.MLP_NPARAM,), np.nan, dtype=torch.float32, device="cuda")
+        loss = mod.mpchol_mlp_grad(m, torch.tensor(x, device="cuda"), torch.tensor(yl, device="cuda"), cw, alpha, g)
+        g = g.cpu().double()
+    finally:
+        mod.mpchol_mlp_destroy(m)
+    p = torch.tensor(p32, dtype=torch.float64, requires_grad=True)
+    W1, b1, W2, b2, W3, b3 = torch.split(p, [512, 64, 4096, 64, 256, 4])
+    a = torch.relu(torch.tensor(x).double() @ W1.view(64, 8).T + b1)
+    a = torch.relu(a @ W2.view(64, 64).T + b2)
+    lp = torch.log_softmax(a @ W3.view(4, 64).T + b3, dim=1)
+    yt = torch.tensor(yl).long()
+    above = (torch.arange(4)[None, :] > yt[:, None]).double()
+    want = (-torch.tensor(cw, dtype=torch.float64)[yt] * lp.gather(1, yt[:, None])[:, 0]
+            + alpha * (lp.exp() * above).sum(1)).mean()
+    want.backward()
+    assert torch.linalg.norm(g - p.grad) <= 1e-5 * torch.linalg.norm(p.grad)
+    assert abs(loss - want.item()) <= 1e-5 * abs(want.item())
+
+
 def test_mlp_forward_and_classes(orc):
     torch = torch_cuda()
     mod = M()
