@@ -112,6 +112,25 @@ __device__ inline double load_stored(const void *tile, int cls, int lo16, int t,
     }
 }
 
+// Two consecutive stored values (element offset even) without a branch on the
+// class: the aligned 16 bytes that hold them, read by every class with the same
+// load, so that several stay in flight (loads behind a switch on the class are
+// waited for one by one), and taken apart when they are used.  A pair never
+// straddles: it is aligned to its own size, at most 16 bytes.
+__device__ inline int class_shift(int cls) { return cls == P64 ? 3 : cls == P32 ? 2 : cls == P16 ? 1 : 0; }
+
+__device__ inline ulonglong2 load_pair16(const char *tile, int byte)
+{
+    return *(const ulonglong2 *)(tile + (byte & ~15));
+}
+
+// The codes of the pair at byte offset `byte` of its tile, in the low bits (classes below FP64).
+__device__ inline uint64_t pair_codes(ulonglong2 v, int byte)
+{
+    const uint64_t u = (byte & 8) ? v.y : v.x;
+    return u >> (8 * (byte & 7));
+}
+
 // Inverse of tile_index: the lower tile (I, J) with I(I+1)/2 + J = t.
 __device__ inline void tile_ij(int64_t t, int &I, int &J)
 {

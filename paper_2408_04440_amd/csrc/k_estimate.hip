@@ -21,7 +21,6 @@
 namespace mpc {
 
 constexpr int EK = 64;   // probes per pass (columns of V)
-constexpr int EB = 64;   // rows / columns of an output block
 constexpr int ER = 32;   // K rows staged per step
 constexpr int SC = 256;  // rows per scan chunk
 
@@ -76,45 +75,55 @@ __global__ __launch_bounds__(256) void sigma_v_kernel(Tiles T, Source S, const d
 // Local recursions of chunk c for probe q (rows s .. e, e < n):
 //   f_i = d_i f_{i-1} + u_i (f_{s-1} = 0)   -> F buffer,
 //   h_i = d_{i+1} h_{i+1} + u_i (h_{e+1} = 0) -> H buffer.
-__global__ __launch_bounds__(64) void scan_local_kernel(Tiles T, Source S, const double *V, int64_t ldv, double *F,
-                                                        double *H)
+// F by the blocks of grid row 0, H by those of grid row 1.
+__global__ __launch_bounds__(64) void scan_local_kernel(Tiles T, Source S, const double *__restrict__ V, int64_t ldv,
+                                                        double *__restrict__ F, double *__restrict__ H)
 {
     const int c = blockIdx.x, q = threadIdx.x;
     const int64_t s = (int64_t)c * SC, e = min((int64_t)T.n, s + SC) - 1;
     const double *v = V + q * ldv;
-    double f = 0.0;
-    for (int64_t i = s; i <= e; ++i) {
-        const double d = (i > s) ? exp(-(S.x[i] - S.x[i - 1]) / S.rho) : 0.0;
-        f = d * f + S.sigma[i] * v[i];
-        F[i + q * ldv] = f;
-    }
-    double h = 0.0;
-    for (int64_t i = e; i >= s; --i) {
-        const double d = (i < e) ? exp(-(S.x[i + 1] - S.x[i]) / S.rho) : 0.0;
-        h = d * h + S.sigma[i] * v[i];
-        H[i + q * ldv] = h;
+    if (blockIdx.y == 0) {
+        double f = 0.0;
+        for (int64_t i = s; i <= e; ++i) {
+            const double d = (i > s) ? exp(-(S.x[i] - S.x[i - 1]) / S.rho) : 0.0;
+            f = d * f + S.sigma[i] * v[i];
+            F[i + q * ldv] = f;
+        }
+    } else {
+        double h = 0.0;
+        for (int64_t i = e; i >= s; --i) {
+            const double d = (i < e) ? exp(-(S.x[i + 1] - S.x[i]) / S.rho) : 0.0;
+            h = d * h + S.sigma[i] * v[i];
+            H[i + q * ldv] = h;
+        }
     }
 }
 
-// Chunk carries for probe q: Fin[c] = F_{s_c - 1}, Hin[c] = H_{e_c + 1} (0
-// at the ends), from the chunk-boundary values of the local recursions.
-__global__ __launch_bounds__(64) void scan_carry_kernel(Tiles T, Source S, const double *F, const double *H,
-                                                        int64_t ldv, int nchunk, double *Fin, double *Hin)
+// Chunk carries for probe q: Fin[c] = F_{s_c - 1} (block 0), Hin[c] = H_{e_c + 1}
+// (block 1; both 0 at the ends), from the chunk-boundary values of the local
+// recursions.
+__global__ __launch_bounds__(64) void scan_carry_kernel(Tiles T, Source S, const double *__restrict__ F,
+                                                        const double *__restrict__ H, int64_t ldv, int nchunk,
+                                                        double *__restrict__ Fin, double *__restrict__ Hin)
 {
     const int q = threadIdx.x;
-    double carry = 0.0;  // F at the last row of the previous chunk
-    for (int c = 0; c < nchunk; ++c) {
-        const int64_t s = (int64_t)c * SC, e = min((int64_t)T.n, s + SC) - 1;
-        Fin[c * EK + q] = carry;
-        const double dc = (c > 0) ? exp(-(S.x[e] - S.x[s - 1]) / S.rho) : 0.0;
-        carry = F[e + q * ldv] + dc * carry;
-    }
-    carry = 0.0;  // H at the first row of the next chunk
-    for (int c = nchunk - 1; c >= 0; --c) {
-        const int64_t s = (int64_t)c * SC, e = min((int64_t)T.n, s + SC) - 1;
-        Hin[c * EK + q] = carry;
-        const double dc = (c < nchunk - 1) ? exp(-(S.x[e + 1] - S.x[s]) / S.rho) : 0.0;
-        carry = H[s + q * ldv] + dc * carry;
+    double carry = 0.0;
+    if (blockIdx.x == 0) {  // F at the last row of the previous chunk
+#pragma unroll 4
+        for (int c = 0; c < nchunk; ++c) {
+            const int64_t s = (int64_t)c * SC, e = min((int64_t)T.n, s + SC) - 1;
+            Fin[c * EK + q] = carry;
+            const double dc = (c > 0) ? exp(-(S.x[e] - S.x[s - 1]) / S.rho) : 0.0;
+            carry = F[e + q * ldv] + dc * carry;
+        }
+    } else {  // H at the first row of the next chunk
+#pragma unroll 4
+        for (int c = nchunk - 1; c >= 0; --c) {
+            const int64_t s = (int64_t)c * SC, e = min((int64_t)T.n, s + SC) - 1;
+            Hin[c * EK + q] = carry;
+            const double dc = (c < nchunk - 1) ? exp(-(S.x[e + 1] - S.x[s]) / S.rho) : 0.0;
+            carry = H[s + q * ldv] + dc * carry;
+        }
     }
 }
 
@@ -144,172 +153,155 @@ __global__ __launch_bounds__(256) void scan_finish_kernel(Tiles T, Source S, con
 }
 
 // ---------------------------------------------------------------- L^T V, L W
-// Both products walk a tile column (row) of the stored factor in steps of ER
-// rows (columns) of K: each step's piece of L (widened to FP64) and of the
-// probes is read into registers while the previous step is multiplied from
-// LDS, then written to LDS once every wave is done with it (one LDS buffer,
-// which leaves room for four blocks per compute unit).
-constexpr int EPT = ER * EB / 256;  // elements of the L piece per thread
-constexpr int QPT = ER * EK / 256;  // elements of the probe piece per thread
-static_assert(ER * EB % 256 == 0 && ER * EK % 256 == 0, "staging split");
+// LT:  W[c of tile column K] = sum_{I >= K} L_IK(:, c)^T V[rows of I],
+// !LT: Z[r of tile row I]    = sum_{K <= I} L_IK(r, :) W[rows of K]:
+// strips of BM outputs, four waves of BM outputs x 16 probes, the sum taken ER
+// rows (columns) of the stored tiles at a time on the FP64 MFMA.  What bounds it:
+// the latency of the pieces, then the MFMA.  Two steps' pieces of L and probes are
+// on their way in registers while a third is multiplied from LDS; they are widened
+// only when staged, and no branch on the class stands between the loads.  A block
+// takes a long strip and then the short one from the other end, so that all blocks
+// are equally long.  All strips walk the probes from the same end, so that the L2
+// serves each piece to the blocks that meet there.  (N = 32,768: 4.4 (LT) and
+// 5.4 -> 2.1 ms each, 33 TFLOP/s; strips of 64 took 3.6 and 3.3 ms.)
+constexpr int BM = 32;                  // outputs per strip
+constexpr int LPT = ER * BM / 256 / 2;  // row pairs of the L piece per thread
+constexpr int QPT = ER * EK / 256;      // elements of the probe piece per thread
+constexpr int LDK = ER + 2, LDR = BM + 16;  // 32 lanes of a read meet each of the 64 banks once
+static_assert(ER * BM % 512 == 0 && ER * EK % 256 == 0, "staging split");
 
-// The 2 x 2 MFMA tiles of a wave: acc[m][n] += B-piece(n)^T-ish products over
-// the ER rows of one staged step, with swapped operands (lane gi owns output
-// row c of the 32 x 32 wave tile, element v the probe acc_row(gg, v)).
-__device__ inline void apply_step(const double (*ls)[EB + 1], const double (*vs)[EK + 1], int wm, int wn, int gi,
-                                  int gg, double4_t (&acc)[2][2])
+template <bool LT>
+__global__ __launch_bounds__(256) void factor_apply_kernel(Tiles T, const double *__restrict__ X, int64_t ldx,
+                                                           double *__restrict__ Y, int strips, bool pair)
 {
+    // LT: rows of a tile are the summed index, consecutive in memory and in LDS
+    // (ls[c][r]); otherwise the outputs are (ls[k][r])
+    __shared__ __align__(16) double ls[2][LT ? BM * LDK : ER * LDR], xs[2][EK * LDK];
+    constexpr int MB = BM / 16, FAST = LT ? ER : BM;  // row index runs over FAST
+    constexpr int COL = 2 * 256 / FAST;               // columns per round of loads
+    const int b = T.b, per = b / BM, nrs = b / ER;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, gi = lane & 15, gg = lane >> 4;
+    const int r2 = 2 * (tid % (FAST / 2)), c0 = tid / (FAST / 2);
+    double4_t acc[MB];
 #pragma unroll
-    for (int s = 0; s < ER / 4; ++s) {
-        double fa[2], fb[2];
-#pragma unroll
-        for (int m = 0; m < 2; ++m) fa[m] = ls[s * 4 + gg][wm * 32 + m * 16 + gi];
-#pragma unroll
-        for (int n = 0; n < 2; ++n) fb[n] = vs[s * 4 + gg][wn * 32 + n * 16 + gi];
-#pragma unroll
-        for (int m = 0; m < 2; ++m)
-#pragma unroll
-            for (int n = 0; n < 2; ++n) acc[m][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(fb[n], fa[m], acc[m][n], 0, 0, 0);
-    }
-}
-
-// W[rows c0.. of tile column K] = sum_{I >= K} L_IK(:, c0:c0+64)^T V[rows of I]:
-// block per (K, 64-column strip), four waves of 32 x 32 outputs (c x probe),
-// K dimension = the rows r of L_IK, ER at a time.
-__global__ __launch_bounds__(256) void lt_apply_kernel(Tiles T, const double *V, int64_t ldv, double *W)
-{
-    __shared__ double ls[ER][EB + 1];  // ls[r][c] = L_IK(r0 + r, c0 + c)
-    __shared__ double vs[ER][EK + 1];  // vs[r][q] = V[I*b + r0 + r, q]
-    const int b = T.b, per = b / EB, nrs = b / ER;
-    const int K = blockIdx.x / per, c0 = (blockIdx.x % per) * EB;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave % 2, wn = wave / 2, gi = lane & 15, gg = lane >> 4;
-    double4_t acc[2][2];
-#pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-        for (int n = 0; n < 2; ++n) acc[m][n] = (double4_t){0.0, 0.0, 0.0, 0.0};
-    double lr[EPT], vr[QPT];
-    auto fetch = [&](int st) {  // step st: tile I = K + st / nrs, rows r0 = (st % nrs) * ER
-        const int I = K + st / nrs, r0 = (st % nrs) * ER;
-        const int cls = (I == K) ? P64 : T.map[I + (int64_t)K * T.nt];
-        const int ts = T.tscale[I + (int64_t)K * T.nt];
+    for (int m = 0; m < MB; ++m) acc[m] = (double4_t){0.0, 0.0, 0.0, 0.0};
+    // strips in order of length; "far" tile rows (columns) from the longest
+    const int sa = blockIdx.x, sb = strips - 1 - sa;
+    const int na = (T.nt - sa / per) * nrs, nsteps = na + (pair ? (T.nt - sb / per) * nrs : 0);
+    struct Step {  // one step's piece, on its way
+        ulonglong2 l[LPT];
+        double x[QPT];
+        int cls, ts;
+    } f0, f1;
+    int next = 0;
+    const double *xp = X + tid % ER + (int64_t)(tid / ER) * ldx;
+    auto place = [&](int st, int &I, int &K, int &o0, int &k0) {  // step st: piece of tile (I, K)
+        const bool first = st < na;
+        const int strip = first ? sa : sb, s = first ? st : st - na;
+        const int far = strip / per, w = s / nrs;
+        o0 = (strip - far * per) * BM;
+        k0 = (s - w * nrs) * ER;
+        I = LT ? T.nt - 1 - w : T.nt - 1 - far;
+        K = LT ? far : w;
+    };
+    auto class_at = [&](int st) {
+        int I, K, o0, k0;
+        place(min(st, nsteps - 1), I, K, o0, k0);
+        return (I == K) ? (int)P64 : (int)T.map[I + (int64_t)K * T.nt];
+    };
+    auto fetch = [&](Step &f, int st) {
+        int I, K, o0, k0;
+        place(min(st, nsteps - 1), I, K, o0, k0);
+        f.cls = __builtin_amdgcn_readfirstlane(next);  // read a step ahead
+        next = class_at(st + 1);
+        f.ts = T.tscale[I + (int64_t)K * T.nt];
         const char *tile = T.slots + tile_index(I, K) * T.slot_bytes;
+        const int off = (LT ? k0 + r2 + (o0 + c0) * b : o0 + r2 + (k0 + c0) * b), sh = class_shift(f.cls);
 #pragma unroll
-        for (int j = 0; j < EPT; ++j) {
-            const int e = tid + 256 * j, r = e % ER, c = e / ER;
-            lr[j] = load_stored(tile, cls, T.lo16, ts, (int64_t)(r0 + r) + (int64_t)(c0 + c) * b);
-        }
+        for (int j = 0; j < LPT; ++j) f.l[j] = load_pair16(tile, (off + COL * j * b) << sh);
+        const double *x = xp + (int64_t)(LT ? I : K) * b + k0;
 #pragma unroll
-        for (int j = 0; j < QPT; ++j) {
-            const int e = tid + 256 * j, r = e % ER, q = e / ER;
-            vr[j] = V[(int64_t)I * b + r0 + r + q * ldv];
-        }
+        for (int j = 0; j < QPT; ++j) f.x[j] = x[(int64_t)(256 / ER * j) * ldx];
     };
-    auto put = [&]() {
+    auto put = [&](const Step &f, int buf) {
+        // columns and strips start at multiples of 32 values: only the row pair places a value in its 16 bytes
+        const int byte = r2 << class_shift(f.cls);
 #pragma unroll
-        for (int j = 0; j < EPT; ++j) {
-            const int e = tid + 256 * j;
-            ls[e % ER][e / ER] = lr[j];
+        for (int j = 0; j < LPT; ++j) {
+            double d0, d1;
+            if (f.cls == P64) {
+                d0 = __longlong_as_double((long long)f.l[j].x);
+                d1 = __longlong_as_double((long long)f.l[j].y);
+            } else {
+                const uint64_t u = pair_codes(f.l[j], byte);
+                const uint32_t w = (uint32_t)u;
+                if (f.cls == P32) {
+                    d0 = (double)__uint_as_float(w);
+                    d1 = (double)__uint_as_float((uint32_t)(u >> 32));
+                } else if (f.cls == P16) {
+                    d0 = decode_class(w & 0xFFFFu, P16, T.lo16, f.ts);
+                    d1 = decode_class((w >> 16) & 0xFFFFu, P16, T.lo16, f.ts);
+                } else {
+                    d0 = decode_class(w & 0xFFu, P8, T.lo16, f.ts);
+                    d1 = decode_class((w >> 8) & 0xFFu, P8, T.lo16, f.ts);
+                }
+            }
+            *(double2 *)&ls[buf][(c0 + COL * j) * (LT ? LDK : LDR) + r2] = make_double2(d0, d1);
         }
 #pragma unroll
-        for (int j = 0; j < QPT; ++j) {
-            const int e = tid + 256 * j;
-            vs[e % ER][e / ER] = vr[j];
-        }
+        for (int j = 0; j < QPT; ++j) xs[buf][(tid / ER + 256 / ER * j) * LDK + tid % ER] = f.x[j];
     };
-    const int nsteps = (T.nt - K) * nrs;
-    fetch(0);
-    put();
-    __syncthreads();
-    for (int st = 0; st < nsteps; ++st) {
-        if (st + 1 < nsteps) fetch(st + 1);
-        apply_step(ls, vs, wm, wn, gi, gg, acc);
-        __syncthreads();
-        if (st + 1 < nsteps) {
-            put();
-            __syncthreads();
-        }
-    }
+    auto store = [&](int strip) {
+        const int far = strip / per, fixed = LT ? far : T.nt - 1 - far;
+        double *y = Y + (int64_t)fixed * b + (strip - far * per) * BM + gi + (int64_t)(wave * 16) * ldx;
 #pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-        for (int n = 0; n < 2; ++n)
+        for (int m = 0; m < MB; ++m)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int c = wm * 32 + m * 16 + gi, q = wn * 32 + n * 16 + acc_row<double>(gg, v);
-                W[(int64_t)K * b + c0 + c + q * ldv] = acc[m][n][v];
+                y[m * 16 + (int64_t)acc_row<double>(gg, v) * ldx] = acc[m][v];
+                acc[m][v] = 0.0;
             }
+    };
+    auto multiply = [&](int buf) {
+        const double *lc = ls[buf], *xc = xs[buf];
+#pragma unroll
+        for (int s = 0; s < ER / 4; ++s) {
+            // swapped operands: lane gi owns output gi, element v the probe acc_row(gg, v)
+            const double fx = xc[(wave * 16 + gi) * LDK + s * 4 + gg];
+#pragma unroll
+            for (int m = 0; m < MB; ++m) {
+                const double fl = LT ? lc[(m * 16 + gi) * LDK + s * 4 + gg] : lc[(s * 4 + gg) * LDR + m * 16 + gi];
+                acc[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(fx, fl, acc[m], 0, 0, 0);
+            }
+        }
+    };
+    next = class_at(0);
+    fetch(f0, 0);
+    fetch(f1, 1);
+    put(f0, 0);
+    __syncthreads();
+    for (int st = 0; st < nsteps; st += 2) {  // na and nsteps are even: b / ER is
+        fetch(f0, st + 2);
+        multiply(0);
+        put(f1, 1);
+        __syncthreads();
+        fetch(f1, st + 3);
+        multiply(1);
+        if (st + 2 == na) store(sa);
+        put(f0, 0);
+        __syncthreads();
+    }
+    if (pair) store(sb);
 }
 
-// Z[rows r0.. of tile row I] = sum_{K <= I} L_IK(r0:r0+64, :) W[rows of K]:
-// block per (I, 64-row strip), K dimension = the columns of L_IK, ER at a time.
-// The last tile rows, with the most tiles to walk, take the first blocks so
-// that the longest blocks start first.
-__global__ __launch_bounds__(256) void l_apply_kernel(Tiles T, const double *W, int64_t ldw, double *Z)
+// Pairs of strips where they still make two blocks per compute unit; with fewer
+// strips the longest one decides, and single strips start them all at once.
+template <bool LT>
+static void factor_apply(const Tiles &T, const double *X, int64_t ldx, double *Y, hipStream_t st)
 {
-    __shared__ double ls[ER][EB + 1];  // ls[c][r] = L_IK(r0 + r, c0 + c)
-    __shared__ double ws[ER][EK + 1];  // ws[c][q] = W[K*b + c0 + c, q]
-    const int b = T.b, per = b / EB, nrs = b / ER;
-    const int I = T.nt - 1 - (int)(blockIdx.x / per), r0 = (blockIdx.x % per) * EB;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave % 2, wn = wave / 2, gi = lane & 15, gg = lane >> 4;
-    double4_t acc[2][2];
-#pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-        for (int n = 0; n < 2; ++n) acc[m][n] = (double4_t){0.0, 0.0, 0.0, 0.0};
-    double lr[EPT], wr[QPT];
-    auto fetch = [&](int st) {  // step st: tile K = st / nrs, columns c0 = (st % nrs) * ER
-        const int K = st / nrs, c0 = (st % nrs) * ER;
-        const int cls = (I == K) ? P64 : T.map[I + (int64_t)K * T.nt];
-        const int ts = T.tscale[I + (int64_t)K * T.nt];
-        const char *tile = T.slots + tile_index(I, K) * T.slot_bytes;
-#pragma unroll
-        for (int j = 0; j < EPT; ++j) {
-            const int e = tid + 256 * j, r = e % EB, c = e / EB;
-            lr[j] = load_stored(tile, cls, T.lo16, ts, (int64_t)(r0 + r) + (int64_t)(c0 + c) * b);
-        }
-#pragma unroll
-        for (int j = 0; j < QPT; ++j) {
-            const int e = tid + 256 * j, c = e % ER, q = e / ER;
-            wr[j] = W[(int64_t)K * b + c0 + c + q * ldw];
-        }
-    };
-    auto put = [&]() {
-#pragma unroll
-        for (int j = 0; j < EPT; ++j) {
-            const int e = tid + 256 * j;
-            ls[e / EB][e % EB] = lr[j];
-        }
-#pragma unroll
-        for (int j = 0; j < QPT; ++j) {
-            const int e = tid + 256 * j;
-            ws[e % ER][e / ER] = wr[j];
-        }
-    };
-    const int nsteps = (I + 1) * nrs;
-    fetch(0);
-    put();
-    __syncthreads();
-    for (int st = 0; st < nsteps; ++st) {
-        if (st + 1 < nsteps) fetch(st + 1);
-        apply_step(ls, ws, wm, wn, gi, gg, acc);
-        __syncthreads();
-        if (st + 1 < nsteps) {
-            put();
-            __syncthreads();
-        }
-    }
-#pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-        for (int n = 0; n < 2; ++n)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int r = wm * 32 + m * 16 + gi, q = wn * 32 + n * 16 + acc_row<double>(gg, v);
-                Z[(int64_t)I * b + r0 + r + q * ldw] = acc[m][n][v];
-            }
+    const int strips = T.nt * (T.b / BM);  // even: b is a multiple of 128
+    const bool pair = strips >= 1024;
+    factor_apply_kernel<LT><<<(unsigned)(pair ? strips / 2 : strips), 256, 0, st>>>(T, X, ldx, Y, strips, pair);
 }
 
 // Widen FP32 normals to FP64 probes, zero beyond n.
@@ -321,26 +313,42 @@ __global__ void probes_kernel(const float *z, int64_t n, int64_t np, double *V)
     V[e] = (i < n) ? (double)z[i + q * n] : 0.0;
 }
 
-// sum over rows < n and probes of (SV - Z)^2, one block, fixed order.
-__global__ __launch_bounds__(1024) void residual_norm_kernel(const double *SV, const double *Z, int64_t n, int64_t np,
-                                                             double *out)
+// sum over rows < n and probes of (SV - Z)^2 in a fixed order: the SC rows of a
+// chunk by one block each, then the chunks' sums by one block (one block for
+// all of it took 1.19 ms at N = 32,768).
+__device__ inline double block_sum256(double a)
 {
-    __shared__ double s[1024];
-    double a = 0.0;
-    for (int64_t e = threadIdx.x; e < np * EK; e += 1024) {
-        int64_t i = e % np;
-        if (i < n) {
-            double d = SV[e] - Z[e];
-            a += d * d;
-        }
-    }
+    __shared__ double s[256];
     s[threadIdx.x] = a;
     __syncthreads();
-    for (int w = 512; w > 0; w >>= 1) {
+    for (int w = 128; w > 0; w >>= 1) {
         if (threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) *out = s[0];
+    return s[0];
+}
+
+__global__ __launch_bounds__(SC) void residual_part_kernel(const double *SV, const double *Z, int64_t n, int64_t np,
+                                                           double *part)
+{
+    const int64_t i = (int64_t)blockIdx.x * SC + threadIdx.x;
+    double a = 0.0;
+    if (i < n)
+#pragma unroll 8
+        for (int q = 0; q < EK; ++q) {
+            const double d = SV[i + q * np] - Z[i + q * np];
+            a += d * d;
+        }
+    a = block_sum256(a);
+    if (threadIdx.x == 0) part[blockIdx.x] = a;
+}
+
+__global__ __launch_bounds__(256) void residual_sum_kernel(const double *part, int nparts, double *out)
+{
+    double a = 0.0;
+    for (int p = threadIdx.x; p < nparts; p += 256) a += part[p];
+    a = block_sum256(a);
+    if (threadIdx.x == 0) *out = a;
 }
 
 int estimate_chunks(int64_t n) { return (int)((n + SC - 1) / SC); }
@@ -359,18 +367,18 @@ void launch_estimate(const Tiles &T, const Source &S, bool sorted, uint64_t seed
     probes_kernel<<<eb, 256, 0, st>>>(zbuf, T.n, np, V);
     if (sorted && !S.orig) {
         const int nc = estimate_chunks(T.n);
-        scan_local_kernel<<<nc, EK, 0, st>>>(T, S, V, np, SV, W);  // F -> SV, H -> W
-        scan_carry_kernel<<<1, EK, 0, st>>>(T, S, SV, W, np, nc, Fin, Hin);
+        scan_local_kernel<<<dim3(nc, 2), EK, 0, st>>>(T, S, V, np, SV, W);  // F -> SV, H -> W
+        scan_carry_kernel<<<2, EK, 0, st>>>(T, S, SV, W, np, nc, Fin, Hin);
         scan_finish_kernel<<<eb, 256, 0, st>>>(T, S, V, np, SV, W, Fin, Hin, SV);
     } else {
         (void)hipMemsetAsync(SV, 0, (size_t)np * EK * 8, st);
         const dim3 g((unsigned)((np + 255) / 256), (unsigned)((np + 16383) / 16384));
         for (int q0 = 0; q0 < EK; q0 += DQ) sigma_v_kernel<<<g, 256, 0, st>>>(T, S, V + q0 * np, np, SV + q0 * np);
     }
-    const int per = T.b / EB;
-    lt_apply_kernel<<<(unsigned)((int64_t)T.nt * per), 256, 0, st>>>(T, V, np, W);
-    l_apply_kernel<<<(unsigned)((int64_t)T.nt * per), 256, 0, st>>>(T, W, np, Z);
-    residual_norm_kernel<<<1, 1024, 0, st>>>(SV, Z, T.n, np, out);
+    factor_apply<true>(T, V, np, W, st);
+    factor_apply<false>(T, W, np, Z, st);
+    residual_part_kernel<<<estimate_chunks(T.n), SC, 0, st>>>(SV, Z, T.n, np, Fin);
+    residual_sum_kernel<<<1, 256, 0, st>>>(Fin, estimate_chunks(T.n), out);
 }
 
 int estimate_probes() { return EK; }

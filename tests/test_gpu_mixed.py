@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 import synth
-from _gpu import M, factor_dense, log, same_factor_residuals, tile_rel, tile_residual_levels
+from _gpu import M, factor_dense, log, same_factor_residuals, tile_rel, tile_residual_levels, torch_cuda
 
 pytestmark = pytest.mark.gpu
 
@@ -328,3 +328,37 @@ def test_verify_with_estimator_falls_back():
     finally:
         mod.mpchol_destroy(h)
     assert st["fallbacks"] >= 1 and be <= 1e-9
+
+
+@pytest.mark.parametrize("n,tile,eps", [(100, 128, 1e-9), (300, 128, 1e-2), (1000, 512, 1e-5), (2500, 128, 1e-3),
+                                        (2049, 256, 1e-4), (2100, 2048, 1e-6)])
+def test_estimate_is_its_probes_residual(n, tile, eps):
+    """The estimate against ||E V||_F / (8 ||Sigma||_F) in FP64 torch for the
+    same 64 probes, E = Sigma - L L^T with the GPU's own factor.  Sums of at most
+    n terms: an entry of E v is off by 2 n u (|L| |L|^T + |Sigma|) |v| on either
+    side, so the estimate by 4 n u sqrt(n) (trace + ||Sigma||_F) / ||Sigma||_F."""
+    torch = torch_cuda()
+    mod = M()
+    sigma, x = synth.workload(int(np.ceil(np.sqrt(n))))
+    sigma, x = sigma[:n], x[:n]
+    h = mod.mpchol_create(n, tile)
+    try:
+        mod.mpchol_set_generator(h, sigma, x, 5.0, 1e-8)
+        mod.mpchol_precision_map(h, mod.RULE_NORM, eps)
+        assert mod.mpchol_factor(h) == 0
+        Lt = torch.zeros((n, n), dtype=torch.float64, device="cuda")
+        mod.mpchol_get_factor(h, Lt.T, n)  # holds the factor's columns as rows
+        z = torch.empty(64 * n, dtype=torch.float32, device="cuda")
+        mod.mpchol_normal_draws(h, 64 * n, 11, z)
+        est = mod.mpchol_backward_error_estimate(h, 1, 11)
+    finally:
+        mod.mpchol_destroy(h)
+    s, xs = torch.tensor(sigma, device="cuda"), torch.tensor(x, device="cuda")
+    S = s[:, None] * s[None, :] * torch.exp(-(xs[:, None] - xs[None, :]).abs() / 5.0)
+    S += 1e-8 * torch.eye(n, dtype=torch.float64, device="cuda")
+    V = z.view(64, n).double()
+    fro = float(S.norm())
+    want = float((V @ S - (V @ Lt.T.contiguous()) @ Lt).norm()) / (8.0 * fro)
+    tol = 4 * n * 2.0 ** -53 * np.sqrt(n) * (float(S.trace()) + fro) / fro
+    log(f"  n={n} tile={tile}: {est:.6e} {want:.6e} tol {tol:.1e}")
+    assert abs(est - want) <= tol
