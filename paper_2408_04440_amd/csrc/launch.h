@@ -90,9 +90,10 @@ void launch_estimate(const Tiles &T, const Source &S, bool sorted, uint64_t seed
 int estimate_chunks(int64_t n);
 
 // ---- covariance from samples (k_samples.hip)
-// xp: (NT*b) x mp scratch (mp = m rounded up to 16); orig: the kept copy.
+// scratch: cov_samples_scratch() doubles; orig: the kept copy.
+int64_t cov_samples_scratch(const Tiles &T, const double *xi, int64_t ldxi, int64_t m);
 int launch_cov_samples(const Tiles &T, const double *xi, int64_t ldxi, int64_t m, double scale, double nugget,
-                       double *xp, int64_t mp, double *orig, hipStream_t st);
+                       double *scratch, double *orig, hipStream_t st);
 int estimate_probes();
 
 // ---- solve (k_solve.hip): ctl = solve_ctl_bytes() of scratch, cleared by the launch

@@ -423,33 +423,38 @@ int mpchol_set_samples(mpchol_t h, const double *xi, int64_t ldxi, int64_t m, do
         int rc = dalloc(&h->orig, h->ntile * h->slot_bytes);
         if (rc) return rc;
     }
-    const int64_t mp = (m + 15) / 16 * 16, ldp = (int64_t)h->nt * h->b;
-    double *xp = nullptr, *tmp = nullptr;
-    int rc = dalloc(&xp, (size_t)ldp * mp * 8);
-    if (rc) return rc;
+    double *tmp = nullptr, *own = nullptr;
     const double *dx = xi;
     if (!on_device) {
         const size_t bytes = (size_t)ldxi * (size_t)m * 8;
-        rc = dalloc(&tmp, bytes);
-        if (rc) {
-            (void)hipFree(xp);
-            return rc;
-        }
+        int rc = dalloc(&tmp, bytes);
+        if (rc) return rc;
         if (hipMemcpyAsync(tmp, xi, bytes, hipMemcpyHostToDevice, h->st) != hipSuccess) {
-            (void)hipFree(xp);
             (void)hipFree(tmp);
             return MPCHOL_EHIP;
         }
         dx = tmp;
     }
+    // scratch: the factor's slots, which the new source makes void, where they are large enough
+    const size_t need = (size_t)cov_samples_scratch(h->tiles(), dx, ldxi, m) * 8;
+    double *scratch = (double *)h->slots;
+    if (need > (size_t)h->ntile * h->slot_bytes) {
+        int rc = dalloc(&own, need);
+        if (rc) {
+            if (tmp) (void)hipFree(tmp);
+            return rc;
+        }
+        scratch = own;
+    }
+    h->state = S_CREATED;
     hipError_t e = hipEventRecord(h->ev[2], h->st);
-    launch_cov_samples(h->tiles(), dx, ldxi, m, scale, nugget, xp, mp, h->orig, h->st);
+    launch_cov_samples(h->tiles(), dx, ldxi, m, scale, nugget, scratch, h->orig, h->st);
     if (e == hipSuccess) e = hipEventRecord(h->ev[3], h->st);
     if (e == hipSuccess) e = hipStreamSynchronize(h->st);
     if (e == hipSuccess) e = hipGetLastError();
     float ms = 0;
     if (e == hipSuccess) e = hipEventElapsedTime(&ms, h->ev[2], h->ev[3]);
-    (void)hipFree(xp);
+    if (own) (void)hipFree(own);
     if (tmp) (void)hipFree(tmp);
     if (e != hipSuccess) {
         hip_fail(e, "set_samples", __LINE__);

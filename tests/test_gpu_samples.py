@@ -144,3 +144,35 @@ def test_samples_sampled_entries_at_8192(orc):
     rel = np.max(np.abs(got - want)) / np.max(np.abs(want))
     log(f"  sampled entries: max |LL^T - Sigma| / max|Sigma| = {rel:.2e}")
     assert rel <= 1e-13
+
+
+@pytest.mark.parametrize("n,m,tile,ld,shift", [(100, 1, 128, 100, 0), (128, 32, 128, 128, 0), (130, 33, 256, 134, 0),
+                                               (1000, 127, 512, 1001, 0), (1000, 500, 512, 1004, 1),
+                                               (4100, 95, 2048, 4100, 0), (4095, 64, 128, 4095, 0)])
+def test_samples_blocks_units_and_alignment(n, m, tile, ld, shift):
+    """Whole blocks and dealt ones (4100: 561 blocks, 49 of them dealt), partial last blocks
+    and units, odd leading dimensions and an odd base (the packed route): small
+    integers give Sigma exactly, so do the entries of L L^T = Sigma with integer L."""
+    torch = torch_cuda()
+    L0 = synth.int_lower(n, 3)[:, :m] if m < n else synth.int_lower(n, 3)
+    buf = torch.full((m * ld + shift,), float("nan"), dtype=torch.float64, device="cuda")
+    X = buf[shift:shift + m * ld].view(m, ld)  # row k: sample k
+    X[:, :n] = torch.tensor(np.ascontiguousarray(L0.T), device="cuda")
+    S = L0 @ L0.T
+    # Sigma + nugget I against the same matrix given directly: equal factors to the last bit
+    nug = float(4 * np.abs(S).sum(axis=1).max())
+    mod = M()
+    outs = []
+    for direct in (False, True):
+        h = mod.mpchol_create(n, tile)
+        try:
+            if direct:
+                mod.mpchol_set_matrix(h, np.asfortranarray(S + nug * np.eye(n)))
+            else:
+                mod.mpchol_set_samples(h, X.T[:n], 1.0, nug)
+            mod.mpchol_precision_map(h, mod.RULE_FP64)
+            assert mod.mpchol_factor(h) == 0
+            outs.append((factor_dense(h, n), mod.mpchol_get_stats(h)))
+        finally:
+            mod.mpchol_destroy(h)
+    assert np.array_equal(outs[0][0], outs[1][0])
