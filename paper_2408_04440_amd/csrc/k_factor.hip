@@ -632,6 +632,21 @@ void update_cm_kernel(Tiles Tt, const T *panel0, const T *panel1, const int32_t 
         for (int n = 0; n < S::NB; ++n)
 #pragma unroll
             for (int v = 0; v < 4; ++v) acc[m][n][v] = 0;
+    // small FP64 blocks, bound by latency: what they change is read before the products
+    constexpr bool EARLY = sizeof(T) == 8 && BM < 128;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wm = wave % WM, wn = wave / WM, gi = lane & 15, gg = lane >> 4;
+    T *C = (T *)(Tt.slots + tile_index(I, J) * Tt.slot_bytes) + tm * BM + (int64_t)tn * BN * b;
+    typename CM<T>::acc_t old[EARLY ? S::MB : 1][EARLY ? S::NB : 1];
+    if constexpr (EARLY) {
+#pragma unroll
+        for (int m = 0; m < S::MB; ++m)
+#pragma unroll
+            for (int n = 0; n < S::NB; ++n)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    old[m][n][v] = C[wm * (BM / WM) + m * 16 + gi + (wn * (BN / WN) + n * 16 + acc_row<T>(gg, v)) * b];
+    }
     // FP64 accumulators hold four rows 4 apart per lane; with the operands
     // swapped each lane owns one row instead, so the stores below cover
     // 16 contiguous doubles per column.  FP32 rows are already contiguous.
@@ -647,14 +662,16 @@ void update_cm_kernel(Tiles Tt, const T *panel0, const T *panel1, const int32_t 
         cm_block<T, BM, BN, BK, WM, WN, SWAP, PRIO>(panel0 + I * bb + tm * BM, b, panel0 + J * bb + tn * BN, b, b, acc,
                                                     (T *)smem_raw, panel1 ? panel1 + I * bb + tm * BM : nullptr,
                                                     panel1 ? panel1 + J * bb + tn * BN : nullptr);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = wave % WM, wn = wave / WM, gi = lane & 15, gg = lane >> 4;
-    T *C = (T *)(Tt.slots + tile_index(I, J) * Tt.slot_bytes) + tm * BM + (int64_t)tn * BN * b;
 #pragma unroll
     for (int m = 0; m < S::MB; ++m)
 #pragma unroll
         for (int n = 0; n < S::NB; ++n) {
-            if (SWAP) {
+            if (EARLY) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    C[wm * (BM / WM) + m * 16 + gi + (wn * (BN / WN) + n * 16 + acc_row<T>(gg, v)) * b] =
+                        old[EARLY ? m : 0][EARLY ? n : 0][v] - acc[m][n][v];
+            } else if (SWAP) {
                 int r = wm * (BM / WM) + m * 16 + gi, c = wn * (BN / WN) + n * 16;
                 T *p = C + r + (int64_t)c * b;
 #pragma unroll
@@ -876,9 +893,15 @@ void launch_update(const Tiles &T, const Panel *const *Ps, int npan, int q, cons
     switch (q) {
     case P64:
         // a grid of 128 x 128 blocks that does not fill the 512 places on the GPU is
-        // bound by one block's time: blocks of 64 x 64 take a quarter of it
-        if ((int64_t)nitems * (T.b / 128) * (T.b / 128) < 512)
-            launch_cm<double, 64, 64, 16, 2, 2>(T, P.p64, P2 ? P2->p64 : nullptr, items, nitems, st);
+        // bound by one block's chain of loads: blocks of 64 x 64 take a quarter of its
+        // products, and stage 32 columns at a time (16 waves; against four waves and 16
+        // columns: N = 8,192, tile 1024, 8.35 -> 7.66 ms; N = 4,900, 3.55 -> 3.17).
+        // Fewer than 64 blocks would leave compute units idle at 64 x 64 as well: blocks
+        // of 32 x 32, 64 columns at a time (N = 1,000, tile 128: 527 -> 457 us)
+        if (const int64_t blocks = (int64_t)nitems * (T.b / 128) * (T.b / 128); blocks < 64)
+            launch_cm<double, 32, 32, 64, 2, 2>(T, P.p64, P2 ? P2->p64 : nullptr, items, nitems, st);
+        else if (blocks < 512)
+            launch_cm<double, 64, 64, 32, 4, 4>(T, P.p64, P2 ? P2->p64 : nullptr, items, nitems, st);
         else
             launch_cm<double, 128, 128, 16, 4, 4>(T, P.p64, P2 ? P2->p64 : nullptr, items, nitems, st);
         break;

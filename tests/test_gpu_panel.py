@@ -43,3 +43,20 @@ def test_bad_pivot_column(tile, n, col, val):
         assert mod.mpchol_factor(h) == col + 1
     finally:
         mod.mpchol_destroy(h)
+
+
+@pytest.mark.parametrize("tile,n", [(128, 256), (128, 384), (128, 1500), (256, 2048), (384, 3000), (512, 2100),
+                                    (1024, 3072)])
+def test_update_block_shapes(tile, n):
+    """Trailing updates whose grids fall on either side of the block-shape rules,
+    one panel column and pairs: integer products are exact in any order."""
+    mod = M()
+    L0 = synth.int_lower(n, 8)
+    h = mod.mpchol_create(n, tile)
+    try:
+        mod.mpchol_set_matrix(h, L0 @ L0.T)
+        mod.mpchol_precision_map(h, mod.RULE_FP64)
+        assert mod.mpchol_factor(h) == 0
+        assert np.array_equal(factor_dense(h, n), L0)
+    finally:
+        mod.mpchol_destroy(h)
