@@ -883,7 +883,7 @@ void launch_update(const Tiles &T, const Panel *const *Ps, int npan, int q, cons
                    hipStream_t st, bool small)
 {
     if (nitems <= 0 || npan < 1 || npan > 4) return;
-    // "small": a launch beside the running updates (the look-ahead stream)
+    // "small": a launch beside the running updates (inside the panel work)
     // uses block shapes whose LDS fits in the slot one finished update block
     // frees; a 1024-thread block with 147 KB of LDS would wait for a whole
     // idle compute unit.
