@@ -875,6 +875,19 @@ static void launch_rm(const Tiles &T_, const PanelSet<typename RM<KIND>::T> &ps,
     k<<<(unsigned)grid, S::NTH, smem, st>>>(T_, ps, q, items);
 }
 
+// Before a factorization: no bad pivot yet, nothing handed over inside any diagonal tile.
+__global__ __launch_bounds__(256) void factor_reset_kernel(unsigned long long *info, int *ctl, int64_t words)
+{
+    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (e == 0) *info = ~0ull;
+    if (e < words) ctl[e] = 0;
+}
+
+void launch_factor_reset(unsigned long long *info, int *ctl, int64_t words, hipStream_t st)
+{
+    factor_reset_kernel<<<(unsigned)((words + 255) / 256), 256, 0, st>>>(info, ctl, words);
+}
+
 // Block shapes per class from a sweep on MI355X (1024 x 1024 tiles):
 // FP64 128 x 128 with 16 waves of 32 x 32, FP32 256 x 128 with 8 waves,
 // FP16/BF16 256 x 256 with 16 waves, FP8 128 x 128 with 4 waves; tiles of

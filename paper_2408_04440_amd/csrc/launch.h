@@ -58,6 +58,7 @@ void launch_get_factor(const Tiles &T, double *L, int64_t ldl, hipStream_t st);
 // ---- factorization (k_factor.hip)
 // ctl: nt * potrf_ctl_words(b) words, all zero before the first tile of a factorization
 int potrf_ctl_words(int b);
+void launch_factor_reset(unsigned long long *info, int *ctl, int64_t words, hipStream_t st);
 void launch_potrf_tile(const Tiles &T, const Panel &P, int k, int *ctl, hipStream_t st);  // also zeroes P.pmax
 void launch_trsm_panel(const Tiles &T, const Panel &P, int k, const uint8_t *qmask, hipStream_t st);
 // a panel tile of FP64 class with FP64 consumers only: its TRSM stores it, the conversion skips it

@@ -70,7 +70,7 @@ struct mpchol_handle {
     OzakiConst *d_ozc = nullptr; // lo64 INT8: moduli and reconstruction constants (device)
     // per-tile metadata
     uint8_t *d_map = nullptr;
-    int32_t *d_tscale = nullptr;
+    int32_t *d_tscale = nullptr;  // with d_map and d_qmask behind it
     double *d_fro2 = nullptr, *d_amax = nullptr;
     unsigned long long *d_info = nullptr;
     double *d_scalar = nullptr;
@@ -92,6 +92,16 @@ struct mpchol_handle {
     uint8_t *d_qmask = nullptr;
     std::vector<uint8_t> convert_col;  // per column: some panel tile needs the conversion
     int32_t *d_all_items = nullptr;  // every lower tile, for the residual
+    size_t items_cap = 0;
+    // pinned staging: 64 bytes of scalars (factor info, logdet), the norms, the
+    // table of d_tscale, and up to PIN_ITEMS bytes of schedule
+    static constexpr size_t PIN_ITEMS = 256 << 10;
+    char *pin = nullptr;
+    double *pin_norms() const { return (double *)(pin + 64); }
+    char *pin_table() const { return pin + 64 + (size_t)nt * nt * 16; }
+    char *pin_items() const { return pin_table() + ((size_t)nt * nt * 6 + 63) / 64 * 64; }
+    size_t pin_bytes() const { return 64 + (size_t)nt * nt * 22 + 64 + PIN_ITEMS; }
+    std::mutex sample_mu;
     double *d_partial = nullptr, *d_tres2 = nullptr;
     // backward-error estimator scratch
     double *d_est = nullptr;
@@ -220,10 +230,11 @@ static void release(mpchol_handle *h)
 {
     void *ptrs[] = {h->slots, h->orig, h->d_sigma, h->d_x, h->p64, h->p32, h->p32s, h->p16, h->p8, h->p8x, h->pmax, h->pscale,
                     h->poz, h->pexp, h->d_ozc,
-                    h->d_map, h->d_tscale, h->d_fro2, h->d_amax, h->d_info, h->d_scalar, h->d_solve, h->d_potrf, h->d_items, h->d_qmask,
+                    h->d_tscale, h->d_fro2, h->d_info, h->d_scalar, h->d_solve, h->d_potrf, h->d_items,
                     h->d_all_items, h->d_partial, h->d_tres2, h->d_params, h->d_feats, h->d_est, h->d_zbuf};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
+    if (h->pin) (void)hipHostFree(h->pin);
     for (auto &e : h->ev)
         if (e) (void)hipEventDestroy(e);
     for (auto e : h->gev) (void)hipEventDestroy(e);
@@ -325,15 +336,18 @@ int mpchol_create(mpchol_t *hp, int64_t n, int32_t tile, const mpchol_opts *o)
     }
     A(dalloc(&h->pmax, NSET * nt * 8));
     A(dalloc(&h->pscale, NSET * nt * 4 * 4));
-    A(dalloc(&h->d_map, nt * nt));
-    A(dalloc(&h->d_tscale, nt * nt * 4));
-    A(dalloc(&h->d_fro2, nt * nt * 8));
-    A(dalloc(&h->d_amax, nt * nt * 8));
+    // one table, filled by one copy: scales, map, consumer masks; and one for the norms
+    A(dalloc(&h->d_tscale, nt * nt * 6));
+    if (rc == MPCHOL_OK) {
+        h->d_map = (uint8_t *)(h->d_tscale + nt * nt);
+        h->d_qmask = h->d_map + nt * nt;
+    }
+    A(dalloc(&h->d_fro2, 2 * nt * nt * 8));
+    if (rc == MPCHOL_OK) h->d_amax = h->d_fro2 + nt * nt;
     A(dalloc(&h->d_info, 8));
     A(dalloc(&h->d_scalar, 64));
     A(dalloc(&h->d_solve, solve_ctl_bytes()));
     A(dalloc(&h->d_potrf, nt * potrf_ctl_words(tile) * sizeof(int)));
-    A(dalloc(&h->d_qmask, nt * nt));
     A(dalloc(&h->d_all_items, h->ntile * 4));
     A(dalloc(&h->d_partial, h->ntile * (bb / (128 * 128)) * 8));
     A(dalloc(&h->d_tres2, nt * nt * 8));
@@ -344,6 +358,11 @@ int mpchol_create(mpchol_t *hp, int64_t n, int32_t tile, const mpchol_opts *o)
     };
     for (auto &e : h->ev)
         if (rc == MPCHOL_OK) H(hipEventCreate(&e), "hipEventCreate");
+    if (rc == MPCHOL_OK && hipHostMalloc((void **)&h->pin, h->pin_bytes(), hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        h->pin = nullptr;
+        rc = MPCHOL_ENOMEM;
+    }
     if (rc == MPCHOL_OK) H(hipStreamCreateWithFlags(&h->st2, hipStreamNonBlocking), "hipStreamCreateWithFlags");
     if (rc == MPCHOL_OK) H(hipEventCreateWithFlags(&h->ev_next, hipEventDisableTiming), "hipEventCreateWithFlags");
     if (rc == MPCHOL_OK) H(hipEventCreateWithFlags(&h->ev_panel, hipEventDisableTiming), "hipEventCreateWithFlags");
@@ -359,8 +378,8 @@ int mpchol_create(mpchol_t *hp, int64_t n, int32_t tile, const mpchol_opts *o)
         for (int J = (int)nt - 1; J >= 0; --J)
             for (int I = J; I < nt; ++I) all.push_back((I << 16) | J);
         H(hipMemcpy(h->d_all_items, all.data(), all.size() * 4, hipMemcpyHostToDevice), "hipMemcpy(items)");
-        H(hipMemset(h->d_tscale, 0, nt * nt * 4), "hipMemset(tscale)");
-        H(hipMemset(h->d_map, 0, nt * nt), "hipMemset(map)");
+        H(hipMemset(h->d_tscale, 0, nt * nt * 6), "hipMemset(table)");
+        H(hipMemset(h->d_fro2, 0, 2 * nt * nt * 8), "hipMemset(norms)");  // the upper part stays zero
     }
     if (rc != MPCHOL_OK) {
         release(h);
@@ -584,33 +603,42 @@ static void build_schedule_counts(mpchol_handle *h, std::vector<int32_t> &items,
     h->item_off.assign((size_t)npair * NQ * 3 + 1, 0);
     h->item_syrk.assign((size_t)npair * NQ * 3, 0);
     items.clear();
+    std::vector<uint8_t> uc((size_t)nt * nt, 0);  // update class of every lower tile
+    for (int J = 0; J < nt; ++J)
+        for (int I = J; I < nt; ++I) uc[I + (size_t)J * nt] = (uint8_t)update_class(h, I, J, int8_ok);
+    std::vector<int32_t> list[mpchol_handle::NQ][3];
     for (int p = 0; p < npair; ++p) {
         const int c = 2 * p;
+        for (int J = c + 1; J < nt; ++J) {
+            const int part = J == c + 1 ? 0 : J <= c + 3 ? 1 : 2;
+            for (int I = J; I < nt; ++I) {
+                const int q = uc[I + (size_t)J * nt];
+                list[q][part].push_back((I << 16) | J);
+                h->item_syrk[((size_t)p * NQ + q) * 3 + part] += (I == J);
+            }
+        }
         for (int q = 0; q < NQ; ++q)
             for (int part = 0; part < 3; ++part) {
-                const size_t o = ((size_t)p * NQ + q) * 3 + part;
-                h->item_off[o] = (int64_t)items.size();
-                const int jlo = part == 0 ? c + 1 : part == 1 ? c + 2 : c + 4;
-                const int jhi = part == 0 ? c + 1 : part == 1 ? c + 3 : nt - 1;
-                for (int J = jlo; J <= jhi && J < nt; ++J)
-                    for (int I = J; I < nt; ++I)
-                        if (update_class(h, I, J, int8_ok) == q) {
-                            items.push_back((I << 16) | J);
-                            h->item_syrk[o] += (I == J);
-                        }
+                auto &l = list[q][part];
+                h->item_off[((size_t)p * NQ + q) * 3 + part] = (int64_t)items.size();
+                items.insert(items.end(), l.begin(), l.end());
+                l.clear();
             }
     }
     h->item_off[(size_t)npair * NQ * 3] = (int64_t)items.size();
+    // consumers of panel tile (I, k): SYRK(I, I) reads the FP64 copy; tiles (I, J),
+    // k < J < I, as row operand; tiles (J, I), J > I, as column operand
     qmask.assign((size_t)nt * nt, 0);
     h->convert_col.assign(nt, 0);
-    for (int k = 0; k < nt; ++k)
-        for (int I = k + 1; I < nt; ++I) {
-            uint8_t msk = 1;  // SYRK(I,I) reads the FP64 copy
-            for (int J = k + 1; J < I; ++J) msk |= (uint8_t)(1u << update_class(h, I, J, int8_ok));
-            for (int J = I + 1; J < nt; ++J) msk |= (uint8_t)(1u << update_class(h, J, I, int8_ok));
+    for (int I = 1; I < nt; ++I) {
+        uint8_t msk = 1;
+        for (int J = I + 1; J < nt; ++J) msk |= (uint8_t)(1u << uc[J + (size_t)I * nt]);
+        for (int k = I - 1; k >= 0; --k) {
             qmask[I + (size_t)k * nt] = msk;
             if (!panel_direct(h->h_map[I + (size_t)k * nt], msk)) h->convert_col[k] = 1;
+            msk |= (uint8_t)(1u << uc[I + (size_t)k * nt]);
         }
+    }
 }
 
 static void fill_flop_stats(mpchol_handle *h)
@@ -632,8 +660,9 @@ static void fill_flop_stats(mpchol_handle *h)
     }
 }
 
-// Host-side map from norms by rule, then upload map + schedule and load.
-static int apply_map(mpchol_handle *h, int rule, double eps, const uint8_t *user_map)
+// Host-side map from norms by rule, then upload map + schedule and load (enqueued
+// only: the caller synchronizes before it uses the handle's staging again).
+static int enqueue_map(mpchol_handle *h, int rule, double eps, const uint8_t *user_map)
 {
     const int nt = h->nt;
     std::vector<uint8_t> m((size_t)nt * nt, 0);
@@ -654,8 +683,9 @@ static int apply_map(mpchol_handle *h, int rule, double eps, const uint8_t *user
         T.map = h->d_map;
         launch_features(T, h->d_fro2, h->d_amax, h->total_fro, eps, h->d_feats, h->st);
         launch_mlp_infer_map(T, h->d_params, h->d_feats, h->o.band, h->o.allowed, h->d_map, h->st);
-        HIPCHK(hipMemcpyAsync(m.data(), h->d_map, m.size(), hipMemcpyDeviceToHost, h->st));
+        HIPCHK(hipMemcpyAsync(h->pin_table(), h->d_map, m.size(), hipMemcpyDeviceToHost, h->st));
         HIPCHK(hipStreamSynchronize(h->st));
+        std::memcpy(m.data(), h->pin_table(), m.size());
         break;
     }
     default: return MPCHOL_EINVAL;
@@ -665,18 +695,27 @@ static int apply_map(mpchol_handle *h, int rule, double eps, const uint8_t *user
     std::vector<uint8_t> qmask;
     // the plain FP64 path (rule FP64) keeps every product on the FP64 MFMA
     build_schedule_counts(h, items, qmask, h->o.lo64 == MPCHOL_LO64_INT8 && rule != MPCHOL_RULE_FP64);
-    if (h->d_items) (void)hipFree(h->d_items);
-    h->d_items = nullptr;
-    if (!items.empty()) {
+    if (items.size() > h->items_cap) {  // once: every map of a handle has the same number of items
+        if (h->d_items) (void)hipFree(h->d_items);
+        h->d_items = nullptr;
+        h->items_cap = 0;
         int rc = dalloc(&h->d_items, items.size() * 4);
         if (rc) return rc;
-        HIPCHK(hipMemcpyAsync(h->d_items, items.data(), items.size() * 4, hipMemcpyHostToDevice, h->st));
+        h->items_cap = items.size();
     }
-    HIPCHK(hipMemcpyAsync(h->d_map, m.data(), m.size(), hipMemcpyHostToDevice, h->st));
-    HIPCHK(hipMemcpyAsync(h->d_qmask, qmask.data(), qmask.size(), hipMemcpyHostToDevice, h->st));
-    HIPCHK(hipMemsetAsync(h->d_tscale, 0, (size_t)nt * nt * 4, h->st));
+    const size_t nn = (size_t)nt * nt;
+    char *tab = h->pin_table();
+    std::memset(tab, 0, nn * 4);
+    std::memcpy(tab + nn * 4, m.data(), nn);
+    std::memcpy(tab + nn * 5, qmask.data(), nn);
+    HIPCHK(hipMemcpyAsync(h->d_tscale, tab, nn * 6, hipMemcpyHostToDevice, h->st));
+    if (!items.empty()) {
+        const void *src = items.data();  // a long list is copied as it is
+        if (items.size() * 4 <= mpchol_handle::PIN_ITEMS) src = std::memcpy(h->pin_items(), src, items.size() * 4);
+        HIPCHK(hipMemcpyAsync(h->d_items, src, items.size() * 4, hipMemcpyHostToDevice, h->st));
+        if (src == items.data()) HIPCHK(hipStreamSynchronize(h->st));  // `items` ends with this function
+    }
     launch_load(h->tiles(), h->source(), h->st);
-    HIPCHK(hipStreamSynchronize(h->st));
     HIPCHK(hipGetLastError());
     h->rule_used = rule;
     fill_flop_stats(h);
@@ -684,23 +723,43 @@ static int apply_map(mpchol_handle *h, int rule, double eps, const uint8_t *user
     return MPCHOL_OK;
 }
 
-static int compute_norms(mpchol_handle *h)
+static int apply_map(mpchol_handle *h, int rule, double eps, const uint8_t *user_map)
+{
+    int rc = enqueue_map(h, rule, eps, user_map);
+    if (rc) return rc;
+    HIPCHK(hipStreamSynchronize(h->st));
+    return MPCHOL_OK;
+}
+
+// Tile norms and their copy to the host, enqueued; finish_norms takes them over
+// once the stream has been synchronized.
+static int enqueue_norms(mpchol_handle *h)
+{
+    launch_norms(h->tiles(), h->source(), h->d_partial, h->d_fro2, h->d_amax, h->st);
+    HIPCHK(hipMemcpyAsync(h->pin_norms(), h->d_fro2, (size_t)2 * h->nt * h->nt * 8, hipMemcpyDeviceToHost, h->st));
+    HIPCHK(hipGetLastError());
+    return MPCHOL_OK;
+}
+
+static void finish_norms(mpchol_handle *h)
 {
     const int nt = h->nt;
-    HIPCHK(hipMemsetAsync(h->d_fro2, 0, (size_t)nt * nt * 8, h->st));
-    HIPCHK(hipMemsetAsync(h->d_amax, 0, (size_t)nt * nt * 8, h->st));
-    launch_norms(h->tiles(), h->source(), h->d_partial, h->d_fro2, h->d_amax, h->st);
-    h->h_fro2.assign((size_t)nt * nt, 0.0);
-    h->h_amax.assign((size_t)nt * nt, 0.0);
-    HIPCHK(hipMemcpyAsync(h->h_fro2.data(), h->d_fro2, (size_t)nt * nt * 8, hipMemcpyDeviceToHost, h->st));
-    HIPCHK(hipMemcpyAsync(h->h_amax.data(), h->d_amax, (size_t)nt * nt * 8, hipMemcpyDeviceToHost, h->st));
-    HIPCHK(hipStreamSynchronize(h->st));
-    HIPCHK(hipGetLastError());
+    const size_t nn = (size_t)nt * nt;
+    h->h_fro2.assign(h->pin_norms(), h->pin_norms() + nn);
+    h->h_amax.assign(h->pin_norms() + nn, h->pin_norms() + 2 * nn);
     double tot = 0.0;
     for (int J = 0; J < nt; ++J)
         for (int I = J; I < nt; ++I) tot += (I == J ? 1.0 : 2.0) * h->h_fro2[I + (size_t)J * nt];
     h->total_fro = std::sqrt(tot);
     h->stats.total_fro = h->total_fro;
+}
+
+static int compute_norms(mpchol_handle *h)
+{
+    int rc = enqueue_norms(h);
+    if (rc) return rc;
+    HIPCHK(hipStreamSynchronize(h->st));
+    finish_norms(h);
     return MPCHOL_OK;
 }
 
@@ -718,13 +777,16 @@ extern "C" int mpchol_precision_map(mpchol_t h, int32_t rule, double eps, const 
     if ((rule == MPCHOL_RULE_NORM || rule == MPCHOL_RULE_LEARNED) && !(eps > 0)) return MPCHOL_EINVAL;
     HIPCHK(hipSetDevice(h->dev));
     HIPCHK(hipEventRecord(h->ev[2], h->st));
-    int rc = compute_norms(h);
+    // only these rules look at the norms: for the others the one wait at the end does
+    const bool by_norms = rule == MPCHOL_RULE_NORM || rule == MPCHOL_RULE_LEARNED;
+    int rc = by_norms ? compute_norms(h) : enqueue_norms(h);
     if (rc) return rc;
     h->last_eps = eps;
-    rc = apply_map(h, rule, eps, user_map);
-    if (rc) return rc;
+    rc = enqueue_map(h, rule, eps, user_map);
     HIPCHK(hipEventRecord(h->ev[3], h->st));
-    HIPCHK(hipEventSynchronize(h->ev[3]));
+    HIPCHK(hipStreamSynchronize(h->st));
+    if (!by_norms) finish_norms(h);
+    if (rc) return rc;
     float ms = 0;
     HIPCHK(hipEventElapsedTime(&ms, h->ev[2], h->ev[3]));
     h->stats.t_map_ms = ms;
@@ -839,8 +901,7 @@ static int run_factor(mpchol_handle *h, int64_t *info)
     h->gev.clear();
     h->gev_class.clear();
     h->gev_flops.clear();
-    HIPCHK(hipMemsetAsync(h->d_info, 0xFF, 8, A));
-    HIPCHK(hipMemsetAsync(h->d_potrf, 0, (size_t)nt * potrf_ctl_words(h->b) * sizeof(int), A));
+    launch_factor_reset(h->d_info, h->d_potrf, (int64_t)nt * potrf_ctl_words(h->b), A);
     HIPCHK(hipEventRecord(h->ev[0], A));
     int rc = panel_pair(h, T, P, 0, A);
     if (rc) return rc;
@@ -857,9 +918,10 @@ static int run_factor(mpchol_handle *h, int64_t *info)
         HIPCHK(hipStreamWaitEvent(A, h->ev_panel, 0));
     }
     HIPCHK(hipEventRecord(h->ev[1], A));
-    unsigned long long hinfo = 0;
-    HIPCHK(hipMemcpyAsync(&hinfo, h->d_info, 8, hipMemcpyDeviceToHost, A));
+    HIPCHK(hipMemcpyAsync(h->pin, h->d_info, 8, hipMemcpyDeviceToHost, A));
     HIPCHK(hipStreamSynchronize(A));
+    unsigned long long hinfo;
+    std::memcpy(&hinfo, h->pin, 8);
     HIPCHK(hipGetLastError());
     if (hinfo == 0) {  // a wait inside a diagonal tile ran out
         snprintf(g_last_error, sizeof(g_last_error), "mpchol_factor: a diagonal tile's workgroups stopped waiting");
@@ -956,9 +1018,10 @@ extern "C" int mpchol_logdet(mpchol_t h, double *out)
     if (h->state != S_FACTORED) return MPCHOL_EORDER;
     HIPCHK(hipSetDevice(h->dev));
     launch_logdet(h->tiles(), h->d_scalar, h->st);
-    HIPCHK(hipMemcpyAsync(out, h->d_scalar, 8, hipMemcpyDeviceToHost, h->st));
+    HIPCHK(hipMemcpyAsync(h->pin + 8, h->d_scalar, 8, hipMemcpyDeviceToHost, h->st));
     HIPCHK(hipStreamSynchronize(h->st));
     HIPCHK(hipGetLastError());
+    std::memcpy(out, h->pin + 8, 8);
     return MPCHOL_OK;
 }
 
@@ -988,9 +1051,8 @@ static int residual_of(mpchol_handle *h, const Source &S, double total_fro, doub
     HIPCHK(hipEventRecord(h->ev[2], h->st));
     const bool all64 = std::all_of(h->h_map.begin(), h->h_map.end(), [](uint8_t c) { return c == P64; });
     launch_residual_items(h->tiles(), S, all64, h->d_all_items, (int)h->ntile, h->d_partial, h->d_tres2, h->st);
-    std::vector<double> r((size_t)nt * nt, 0.0);
-    HIPCHK(hipMemsetAsync(h->d_scalar, 0, 8, h->st));
-    HIPCHK(hipMemcpyAsync(r.data(), h->d_tres2, r.size() * 8, hipMemcpyDeviceToHost, h->st));
+    const double *r = h->pin_norms();  // the norms were taken over when they were computed
+    HIPCHK(hipMemcpyAsync(h->pin_norms(), h->d_tres2, (size_t)nt * nt * 8, hipMemcpyDeviceToHost, h->st));
     HIPCHK(hipEventRecord(h->ev[3], h->st));
     HIPCHK(hipStreamSynchronize(h->st));
     HIPCHK(hipGetLastError());
@@ -1066,38 +1128,31 @@ extern "C" int mpchol_backward_error_matrix(mpchol_t h, const double *A, int64_t
     if (h->state != S_FACTORED) return MPCHOL_EORDER;
     HIPCHK(hipSetDevice(h->dev));
     const int nt = h->nt;
-    double *tmp = nullptr, *fro2 = nullptr, *amax = nullptr;
-    auto cleanup = [&]() {
-        if (tmp) (void)hipFree(tmp);
-        if (fro2) (void)hipFree(fro2);
-        if (amax) (void)hipFree(amax);
-    };
+    double *tmp = nullptr;
     Source S{};
     S.dense = A;
     S.ld = lda;
-    int rc = dalloc(&fro2, (size_t)nt * nt * 8);
-    if (!rc) rc = dalloc(&amax, (size_t)nt * nt * 8);
-    if (!rc && !on_device) {
+    int rc = MPCHOL_OK;
+    if (!on_device) {
         const size_t bytes = (size_t)lda * (size_t)(h->n - 1) * 8 + (size_t)h->n * 8;
         rc = dalloc(&tmp, bytes);
         if (!rc && hipMemcpyAsync(tmp, A, bytes, hipMemcpyHostToDevice, h->st) != hipSuccess) rc = MPCHOL_EHIP;
         S.dense = tmp;
     }
-    if (!rc && hipMemsetAsync(fro2, 0, (size_t)nt * nt * 8, h->st) != hipSuccess) rc = MPCHOL_EHIP;
-    std::vector<double> f2((size_t)nt * nt, 0.0);
+    double tot = 0.0;
     if (!rc) {
-        launch_norms(h->tiles(), S, h->d_partial, fro2, amax, h->st);
-        if (hipMemcpyAsync(f2.data(), fro2, f2.size() * 8, hipMemcpyDeviceToHost, h->st) != hipSuccess ||
+        // A's norms beside the handle's own, which stay: in the residual's result
+        // (written afterwards) and the features (rebuilt by each of their users)
+        launch_norms(h->tiles(), S, h->d_partial, h->d_tres2, (double *)h->d_feats, h->st);
+        if (hipMemcpyAsync(h->pin_norms(), h->d_tres2, (size_t)nt * nt * 8, hipMemcpyDeviceToHost, h->st) != hipSuccess ||
             hipStreamSynchronize(h->st) != hipSuccess || hipGetLastError() != hipSuccess)
             rc = MPCHOL_EHIP;
+        else
+            for (int J = 0; J < nt; ++J)
+                for (int I = J; I < nt; ++I) tot += (I == J ? 1.0 : 2.0) * h->pin_norms()[I + (size_t)J * nt];
     }
-    if (!rc) {
-        double tot = 0.0;
-        for (int J = 0; J < nt; ++J)
-            for (int I = J; I < nt; ++I) tot += (I == J ? 1.0 : 2.0) * f2[I + (size_t)J * nt];
-        rc = (tot > 0.0) ? residual_of(h, S, std::sqrt(tot), berr, tile_res2) : MPCHOL_EINVAL;
-    }
-    cleanup();
+    if (!rc) rc = (tot > 0.0) ? residual_of(h, S, std::sqrt(tot), berr, tile_res2) : MPCHOL_EINVAL;
+    if (tmp) (void)hipFree(tmp);
     return rc;
 }
 
@@ -1145,14 +1200,20 @@ extern "C" int mpchol_sample(mpchol_t h, int32_t ndraws, uint64_t seed, float *Y
     if (!h || !Y || ndraws <= 0 || ldy < h->n) return MPCHOL_EINVAL;
     if (h->state != S_FACTORED) return MPCHOL_EORDER;
     HIPCHK(hipSetDevice(h->dev));
-    float *Z = nullptr;
-    int rc = dalloc(&Z, (size_t)h->n * ndraws * 4);
-    if (rc) return rc;
-    launch_normal_matrix(seed, h->n, ndraws, Z, h->n, h->st);
-    launch_lower_apply(h->tiles(), Z, h->n, Y, ldy, ndraws, h->st);
-    hipError_t e = hipStreamSynchronize(h->st);
-    (void)hipFree(Z);
-    if (e != hipSuccess || hipGetLastError() != hipSuccess) return MPCHOL_EHIP;
+    // normals in the panel copies, which are free between factorizations, as many
+    // draws at a time as they hold (over 1,500 for any tile size); all passes of a
+    // call are enqueued together, so that calls from several threads cannot mix
+    {
+        std::lock_guard<std::mutex> lk(h->sample_mu);
+        float *Z = (float *)h->p64;
+        const int64_t chunk = (int64_t)NSET * h->nt * h->b * h->b * 2 / h->n / 128 * 128;
+        for (int64_t d0 = 0; d0 < ndraws; d0 += chunk) {
+            const int nd = (int)std::min<int64_t>(chunk, ndraws - d0);
+            launch_normal_columns(seed, h->n, d0, nd, Z, h->n, h->st);
+            launch_lower_apply(h->tiles(), Z, h->n, Y + d0 * ldy, ldy, nd, h->st);
+        }
+    }
+    if (hipStreamSynchronize(h->st) != hipSuccess || hipGetLastError() != hipSuccess) return MPCHOL_EHIP;
     return MPCHOL_OK;
 }
 

@@ -214,3 +214,56 @@ def test_sample_z_block_shapes(orc, n, tile, nd, pad):
     Zd = Z[:, :n].double().contiguous()
     want, size = Zd @ L, Zd.abs() @ L.abs()  # L holds the factor's columns as rows
     assert torch.all((Y[:, :n] - want).abs() <= n * 2.0 ** -24 * size + 1e-30)
+
+
+@pytest.mark.parametrize("n,tile,nd", [(100, 128, 4000), (129, 128, 3073), (700, 256, 3500)])
+def test_sample_in_several_passes(n, tile, nd):
+    """More draws than one pass of mpchol_sample holds (1,536 x tile / 128 at
+    least), from two threads on one handle: each the same draws as the
+    allocation-free entry, bit for bit."""
+    import threading
+
+    torch = torch_cuda()
+    mod = M()
+    h = mod.mpchol_create(n, tile)
+    try:
+        sigma, x = synth.workload(int(np.ceil(np.sqrt(n))))
+        mod.mpchol_set_generator(h, sigma[:n], x[:n], 5.0, 1e-8)
+        mod.mpchol_precision_map(h, mod.RULE_FP64)
+        assert mod.mpchol_factor(h) == 0
+        Y = torch.full((2, nd, n), 7.0, device="cuda")
+        want = torch.full((2, nd, n), 9.0, device="cuda")
+        torch.cuda.synchronize()
+        ts = [threading.Thread(target=mod.mpchol_sample, args=(h, nd, 3 + i, Y[i].T, n)) for i in range(2)]
+        for t in ts:
+            t.start()
+        for t in ts:
+            t.join()
+        for i in range(2):
+            mod.mpchol_sample_noalloc(h, nd, 3 + i, want[i].T, n)
+        torch.cuda.synchronize()
+    finally:
+        mod.mpchol_destroy(h)
+    assert torch.equal(Y, want)
+
+
+@pytest.mark.parametrize("n,tile", [(300, 128), (12032, 128)])
+def test_maps_in_turn_on_one_handle(n, tile):
+    """Norms read with the map (rules that look at them) and after it (those that
+    do not), schedules below and above the staging size (94 tiles a side): the
+    FP64 factor is the same before and after a mixed one, norms and flops too."""
+    mod = M()
+    h = mod.mpchol_create(n, tile)
+    seen = []
+    try:
+        sigma, x = synth.workload(int(np.ceil(np.sqrt(n))))
+        mod.mpchol_set_generator(h, sigma[:n], x[:n], 5.0, 1e-8)
+        for rule in (mod.RULE_FP64, mod.RULE_NORM, mod.RULE_FP64):
+            mod.mpchol_precision_map(h, rule, 1e-8)
+            assert mod.mpchol_factor(h) == 0
+            st = mod.mpchol_get_stats(h)
+            seen.append((mod.mpchol_logdet(h), st["total_fro"], st["flops_per_class"][0]))
+            assert mod.mpchol_backward_error_estimate(h, 1, 5) <= (1e-14 if rule == mod.RULE_FP64 else 1e-8)
+    finally:
+        mod.mpchol_destroy(h)
+    assert seen[0] == seen[2] and seen[1][1] == seen[0][1] and seen[1][2] <= seen[0][2]
