@@ -9,19 +9,26 @@
 // (forward) or columns (backward) for up to 16 right-hand sides.  It walks the
 // 64-wide blocks of the solution in the order in which they become known,
 // keeps its sums in registers, then solves its own diagonal block and hands the
-// result to the others through B itself.  The factor's elements go from memory
+// result to the others through a mailbox.  The factor's elements go from memory
 // to registers, each used once, the next block in flight while the current one
 // is waited for, so the streaming hides behind the chain or the chain behind it
-// (N = 16,384, 16 right-hand sides: 2.17 ms, 8.4 us per 128 rows and direction;
-// N = 1,024, one: 4.3 -> 0.1 ms).
+// (N = 16,384: 16 right-hand sides 2.16 -> 1.78 ms, 6.9 us per 128 rows and
+// direction, where counts handed the blocks on and eight waves broadcast each
+// solved value; mixed classes 2.42 -> 1.76; one right-hand side 1.50 -> 1.32).
 //
 // Order and progress: a workgroup takes its place in the chain from a ticket
 // counter, so it only ever waits for workgroups that started before it: however
-// few of them fit on the GPU, the earliest one can always finish.  Solution
-// values and the count of finished blocks are written and read with
-// device-scope accesses; a workgroup's stores have completed (vmcnt 0, then the
-// barrier) before the count is raised.  A wait that lasts longer than
-// WAIT_TICKS leaves NaN in the rows it could not solve and ends the launch.
+// few of them fit on the GPU, the earliest one can always finish.  The mailbox
+// has a place for every value of the solution, marked EMPTY before the launch,
+// and is written and read with device-scope accesses.  The workgroups next in the
+// chain poll the values themselves (a count raised once they are visible, polled,
+// and the values read after it are three trips to memory instead of one); the
+// others, further back, wait for a count of finished blocks, raised when a
+// workgroup's stores have completed (vmcnt 0, then the barrier), and poll it at
+// leisure.  A wait that lasts longer than WAIT_TICKS leaves NaN in the rows it
+// could not solve and ends the launch.
+#include <type_traits>
+
 #include "common.h"
 #include "launch.h"
 
@@ -37,6 +44,8 @@ constexpr int STEPS = HB / 4;            // K steps of four per block, elements 
 constexpr int NCOPY = 16, STRIDE = 32;   // copies of the finished count, one cache line each
 constexpr int CTL = 32 + NCOPY * STRIDE; // words per chunk of right-hand sides and direction
 constexpr long long WAIT_TICKS = 3000000000ll;  // 30 s of the 100 MHz counter
+constexpr int NEAR = 4;                  // blocks before its own that a workgroup polls for themselves
+constexpr unsigned long long EMPTY = 0x7FF85EED0BADF00Dull;  // a NaN that no stored solution value has
 
 struct Ctl {
     unsigned *ticket;  // next place in the chain (shared by the chunks of a launch)
@@ -44,44 +53,157 @@ struct Ctl {
     int *done;         // finished blocks: NCOPY copies
 };
 
-__device__ inline double ld_dev(const double *p)
+__device__ inline unsigned long long ld_mail(const unsigned long long *p)
 {
-    return __longlong_as_double(
-        (long long)__hip_atomic_load((const unsigned long long *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ inline void st_dev(double *p, double v)
+__device__ inline void st_mail(unsigned long long *p, double v)
 {
-    __hip_atomic_store((unsigned long long *)p, (unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
+    unsigned long long u = (unsigned long long)__double_as_longlong(v);
+    if (u == EMPTY) u ^= 1;  // stays a NaN
+    __hip_atomic_store(p, u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // all of this wave's global stores have completed
 __device__ inline void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-__device__ inline double bcast(double v, int lane)
+// f(integral_constant<int, I>) for I = 0 .. N - 1 (the DPP control is a constant)
+template <int I, int N, typename F> __device__ inline void static_for(F f)
 {
-    const uint64_t u = (uint64_t)__double_as_longlong(v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
-    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<I + 1, N>(f);
+    }
+}
+
+// One column of the triangle: v[t][p] -= (lane JJ of the row of 16's v[S][p]) * l[t]
+// for the 16-row tiles t behind S in the order of the solve, then for S itself: DPP
+// multiply-adds, 5 cycles each (as broadcasts and multiply-adds of their own a
+// step costs the vector unit three times that).  The s_nop covers the wait states
+// between the last writes of v[S] and their DPP reads, which the compiler does
+// not see here.
+#define MPC_FM(d, s, l) "\n\tv_fmac_f64_dpp %[" d "], -%[" s "], %[" l "] row_newbcast:%[jj] row_mask:0xf bank_mask:0xf"
+template <int JJ, int NB> __device__ inline void column(double (&x)[1], double *const (&y)[3], const double (&l)[4])
+{
+    if constexpr (NB == 0)
+        asm("s_nop 1" MPC_FM("x", "x", "k") : [x] "+v"(x[0]) : [k] "v"(l[0]), [jj] "n"(JJ));
+    else if constexpr (NB == 1)
+        asm("s_nop 1" MPC_FM("a", "x", "ka") MPC_FM("x", "x", "k")
+            : [x] "+v"(x[0]), [a] "+v"(y[0][0])
+            : [k] "v"(l[0]), [ka] "v"(l[1]), [jj] "n"(JJ));
+    else if constexpr (NB == 2)
+        asm("s_nop 1" MPC_FM("a", "x", "ka") MPC_FM("b", "x", "kb") MPC_FM("x", "x", "k")
+            : [x] "+v"(x[0]), [a] "+v"(y[0][0]), [b] "+v"(y[1][0])
+            : [k] "v"(l[0]), [ka] "v"(l[1]), [kb] "v"(l[2]), [jj] "n"(JJ));
+    else
+        asm("s_nop 1" MPC_FM("a", "x", "ka") MPC_FM("b", "x", "kb") MPC_FM("c", "x", "kc") MPC_FM("x", "x", "k")
+            : [x] "+v"(x[0]), [a] "+v"(y[0][0]), [b] "+v"(y[1][0]), [c] "+v"(y[2][0])
+            : [k] "v"(l[0]), [ka] "v"(l[1]), [kb] "v"(l[2]), [kc] "v"(l[3]), [jj] "n"(JJ));
+}
+template <int JJ, int NB> __device__ inline void column(double (&x)[2], double *const (&y)[3], const double (&l)[4])
+{
+    if constexpr (NB == 0)
+        asm("s_nop 1" MPC_FM("x", "x", "k") MPC_FM("z", "z", "k")
+            : [x] "+v"(x[0]), [z] "+v"(x[1])
+            : [k] "v"(l[0]), [jj] "n"(JJ));
+    else if constexpr (NB == 1)
+        asm("s_nop 1" MPC_FM("a", "x", "ka") MPC_FM("d", "z", "ka") MPC_FM("x", "x", "k") MPC_FM("z", "z", "k")
+            : [x] "+v"(x[0]), [z] "+v"(x[1]), [a] "+v"(y[0][0]), [d] "+v"(y[0][1])
+            : [k] "v"(l[0]), [ka] "v"(l[1]), [jj] "n"(JJ));
+    else if constexpr (NB == 2)
+        asm("s_nop 1" MPC_FM("a", "x", "ka") MPC_FM("d", "z", "ka") MPC_FM("b", "x", "kb") MPC_FM("e", "z", "kb")
+            MPC_FM("x", "x", "k") MPC_FM("z", "z", "k")
+            : [x] "+v"(x[0]), [z] "+v"(x[1]), [a] "+v"(y[0][0]), [d] "+v"(y[0][1]), [b] "+v"(y[1][0]), [e] "+v"(y[1][1])
+            : [k] "v"(l[0]), [ka] "v"(l[1]), [kb] "v"(l[2]), [jj] "n"(JJ));
+    else
+        asm("s_nop 1" MPC_FM("a", "x", "ka") MPC_FM("d", "z", "ka") MPC_FM("b", "x", "kb") MPC_FM("e", "z", "kb")
+            MPC_FM("c", "x", "kc") MPC_FM("f", "z", "kc") MPC_FM("x", "x", "k") MPC_FM("z", "z", "k")
+            : [x] "+v"(x[0]), [z] "+v"(x[1]), [a] "+v"(y[0][0]), [d] "+v"(y[0][1]), [b] "+v"(y[1][0]), [e] "+v"(y[1][1]),
+              [c] "+v"(y[2][0]), [f] "+v"(y[2][1])
+            : [k] "v"(l[0]), [ka] "v"(l[1]), [kb] "v"(l[2]), [kc] "v"(l[3]), [jj] "n"(JJ));
+}
+#undef MPC_FM
+
+// One wave solves a 64 x 64 unit triangle for P right-hand sides per row of 16
+// lanes: v[t][p], rows 16 t + gi; dl: column c at dl[c * LDD + row], zero on and
+// beyond the diagonal.  Columns in groups of 12 to 16 entries a lane, the next
+// group's on their way from LDS meanwhile.
+constexpr int NG = 11;
+__device__ constexpr int group_at(int g) { return g < 8 ? 4 * g : g < 10 ? 32 + 8 * (g - 8) : 48 + 16 * (g - 10); }
+
+template <bool FWD, int P> __device__ inline void solve64(double (&v)[4][P], const double *dl, int gi)
+{
+    double l[2][16][4];  // [set][column][own tile, then those behind it]
+    auto load = [&](auto ig) {
+        constexpr int g = decltype(ig)::value;
+        static_for<0, group_at(g + 1) - group_at(g)>([&](auto ic) {
+            constexpr int k = decltype(ic)::value, at = group_at(g) + k, c = FWD ? at : HB - 1 - at, S = c / 16;
+            constexpr int NB = FWD ? 3 - S : S;
+#pragma unroll
+            for (int t = 0; t <= NB; ++t) l[g & 1][k][t] = dl[c * LDD + 16 * (FWD ? S + t : S - t) + gi];
+        });
+    };
+    load(std::integral_constant<int, 0>{});
+    static_for<0, NG>([&](auto ig) {
+        constexpr int g = decltype(ig)::value;
+        if constexpr (g + 1 < NG) load(std::integral_constant<int, g + 1>{});
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<0, group_at(g + 1) - group_at(g)>([&](auto ic) {
+            constexpr int k = decltype(ic)::value, at = group_at(g) + k, c = FWD ? at : HB - 1 - at, S = c / 16;
+            constexpr int NB = FWD ? 3 - S : S, D = FWD ? 1 : -1;
+            double *const y[3] = {v[NB > 0 ? S + D : S], v[NB > 1 ? S + 2 * D : S], v[NB > 2 ? S + 3 * D : S]};
+            column<c % 16, NB>(v[S], y, l[g & 1][k]);
+        });
+        __builtin_amdgcn_sched_barrier(0);
+    });
+}
+
+// v / d with r = 1 / d at hand: the quotient corrected by its remainder, where
+// nothing in it can leave the range of normal numbers (both in_range).
+__device__ inline bool in_range(double v)
+{
+    const unsigned e = ((unsigned)((unsigned long long)__double_as_longlong(v) >> 52)) & 0x7FFu;
+    return e - 523u < 1000u;  // 2^-500 <= |v| < 2^500
+}
+__device__ inline double div_by(double v, double d, double r)
+{
+    const double q = v * r;
+    return fma(fma(-q, d, v), r, q);
+}
+
+// a wait has run out, here or elsewhere in this direction
+__device__ inline bool out_of_time(const Ctl &c, long long t0)
+{
+    if (!__hip_atomic_load(c.stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) && wall_clock64() - t0 <= WAIT_TICKS)
+        return false;
+    __hip_atomic_store(c.stop, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return true;
 }
 
 // thread 0: waits until `need` blocks are finished; their number, or -1
-__device__ inline int wait_count(const Ctl &c, int copy, int need, bool far)
+__device__ inline int wait_count(const Ctl &c, int copy, int need)
 {
     const int *p = c.done + copy * STRIDE;
     int v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (v >= need) return v;
     const long long t0 = wall_clock64();
     for (unsigned k = 1;; ++k) {
-        if (far) __builtin_amdgcn_s_sleep(16);  // about 1024 cycles: not the next one to run
+        __builtin_amdgcn_s_sleep(16);  // about 1024 cycles: not the next one to run
         v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (v >= need) return v;
-        if ((k & 255) == 0 && (__hip_atomic_load(c.stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ||
-                               wall_clock64() - t0 > WAIT_TICKS)) {
-            __hip_atomic_store(c.stop, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            return -1;
-        }
+        if ((k & 255) == 0 && out_of_time(c, t0)) return -1;
+    }
+}
+
+// one value of the mailbox, waited for; false if it did not come
+__device__ inline bool receive(const Ctl &c, const unsigned long long *p, unsigned long long &u)
+{
+    if (u != EMPTY) return true;
+    const long long t0 = wall_clock64();
+    for (unsigned k = 1;; ++k) {
+        u = ld_mail(p);
+        if (u != EMPTY) return true;
+        if ((k & 255) == 0 && out_of_time(c, t0)) return false;
     }
 }
 
@@ -97,94 +219,82 @@ __device__ inline TileRef tile_ref(const Tiles &T, int I, int J)
 }
 
 // STEPS raw codes of a lane, widened only when used so that the loads stay in
-// flight.  PAIR (backward): consecutive rows, two codes at off[s].
+// flight.  PAIR (backward): consecutive rows, two to a load.
 template <bool PAIR> struct Raw {
     uint64_t u[STEPS];
 };
+// single rows: the aligned 8 bytes that hold each, by the same load for every class
 __device__ inline void fetch(const TileRef &R, int off0, int step, Raw<false> &r)
 {
-    switch (R.cls) {
-    case P64:
+    const int sh = class_shift(R.cls);
 #pragma unroll
-        for (int s = 0; s < STEPS; ++s) r.u[s] = ((const uint64_t *)R.p)[off0 + s * step];
-        break;
-    case P32:
-#pragma unroll
-        for (int s = 0; s < STEPS; ++s) r.u[s] = ((const uint32_t *)R.p)[off0 + s * step];
-        break;
-    case P16:
-#pragma unroll
-        for (int s = 0; s < STEPS; ++s) r.u[s] = ((const uint16_t *)R.p)[off0 + s * step];
-        break;
-    default:
-#pragma unroll
-        for (int s = 0; s < STEPS; ++s) r.u[s] = ((const uint8_t *)R.p)[off0 + s * step];
-        break;
-    }
+    for (int s = 0; s < STEPS; ++s) r.u[s] = *(const uint64_t *)(R.p + (((off0 + s * step) << sh) & ~7));
 }
-typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
-// pairs of rows 8 apart: off0 is even and tiles are 16-byte aligned
+// pairs of rows 8 apart (off0 even), by the same 16-byte load for every class
 __device__ inline void fetch(const TileRef &R, int off0, Raw<true> &r)
 {
-    switch (R.cls) {
-    case P64:
+    const int sh = class_shift(R.cls);
 #pragma unroll
-        for (int s = 0; s < STEPS / 2; ++s) {
-            const u64x2 v = *(const u64x2 *)((const uint64_t *)R.p + off0 + 8 * s);
-            r.u[2 * s] = v[0];
-            r.u[2 * s + 1] = v[1];
-        }
-        break;
-    case P32:
-#pragma unroll
-        for (int s = 0; s < STEPS / 2; ++s) {
-            const uint64_t v = *(const uint64_t *)((const uint32_t *)R.p + off0 + 8 * s);
-            r.u[2 * s] = v & 0xFFFFFFFFu;
-            r.u[2 * s + 1] = v >> 32;
-        }
-        break;
-    case P16:
-#pragma unroll
-        for (int s = 0; s < STEPS / 2; ++s) {
-            const uint32_t v = *(const uint32_t *)((const uint16_t *)R.p + off0 + 8 * s);
-            r.u[2 * s] = v & 0xFFFFu;
-            r.u[2 * s + 1] = v >> 16;
-        }
-        break;
-    default:
-#pragma unroll
-        for (int s = 0; s < STEPS / 2; ++s) {
-            const uint16_t v = *(const uint16_t *)((const uint8_t *)R.p + off0 + 8 * s);
-            r.u[2 * s] = v & 0xFFu;
-            r.u[2 * s + 1] = v >> 8;
-        }
-        break;
+    for (int s = 0; s < STEPS / 2; ++s) {
+        const ulonglong2 v = load_pair16(R.p, (off0 + 8 * s) << sh);
+        r.u[2 * s] = v.x;
+        r.u[2 * s + 1] = v.y;
     }
 }
-__device__ inline double widen(uint64_t u, const TileRef &R, int lo16)
+
+// The STEPS values of a lane; a loop per class, so that no branch stands between
+// the products.  gi (single rows) or gg (pairs) places the codes in the bytes read
+// with them: columns, blocks and a wave's rows start at multiples of 16 values.
+template <int CLS, bool PAIR>
+__device__ inline void widen(const Raw<PAIR> &r, int gi, int gg, int lo16, int t, double (&a)[STEPS])
 {
-    return R.cls == P64 ? __longlong_as_double((long long)u) : decode_class((uint32_t)u, R.cls, lo16, R.t);
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+        if (CLS == P64) {
+            a[s] = __longlong_as_double((long long)r.u[s]);
+        } else {
+            constexpr int SH = CLS == P32 ? 2 : CLS == P16 ? 1 : 0, BITS = 8 << SH;
+            uint32_t c;
+            if (PAIR) {
+                const uint64_t u = pair_codes(make_ulonglong2(r.u[s & ~1], r.u[s | 1]), (2 * gg + 4 * (s & ~1)) << SH);
+                c = (uint32_t)(u >> (BITS * (s & 1)));
+            } else {
+                c = (uint32_t)(r.u[s] >> (8 * ((gi << SH) & 7)));
+            }
+            a[s] = decode_class(BITS == 32 ? c : c & ((1u << (BITS & 31)) - 1), CLS, lo16, t);
+        }
+    }
 }
 
 // The sums of a lane.  ONE (a single right-hand side): row gi of the wave's 16,
-// the terms of K group gg; else MFMA accumulators, rows gg + 4v, right-hand side gi.
+// the terms of K group gg; else MFMA accumulators, rows gg + 4v, right-hand side
+// gi: two of them in turn, so that a wave ahead in priority always has a product
+// to issue and is not held up by the other wave on its SIMD.
 template <bool ONE> struct Sum {
-    double4_t v;
-    __device__ inline void zero() { v = (double4_t){0.0, 0.0, 0.0, 0.0}; }
-    __device__ inline void add(double a, const double *x, int k, int gi)
+    double4_t v, w;
+    __device__ inline void zero() { v = w = (double4_t){0.0, 0.0, 0.0, 0.0}; }
+    __device__ inline void add(int s, double a, double x)
     {
-        if (ONE) v[0] += a * x[k];
-        else v = __builtin_amdgcn_mfma_f64_16x16x4f64(a, x[k * LDX + gi], v, 0, 0, 0);
+        if (ONE) {
+            if (s & 1) w[0] += a * x;
+            else v[0] += a * x;
+        } else {
+            if (s & 1) w = __builtin_amdgcn_mfma_f64_16x16x4f64(a, x, w, 0, 0, 0);
+            else v = __builtin_amdgcn_mfma_f64_16x16x4f64(a, x, v, 0, 0, 0);
+        }
     }
+    __device__ inline double sum(int i) const { return v[i] + w[i]; }
 };
 
 }  // namespace
 
-// Finished counts, tickets and stop words of both directions to zero (a
-// kernel, so that a captured solve replays).
-__global__ __launch_bounds__(256) void solve_reset_kernel(int *ctl, int words)
+// Finished counts, tickets and stop words of both directions to zero, their
+// mailboxes to EMPTY (a kernel, so that a captured solve replays).
+__global__ __launch_bounds__(256) void solve_reset_kernel(int *ctl, int words, unsigned long long *mail, int64_t places)
 {
-    for (int i = blockIdx.x * 256 + threadIdx.x; i < words; i += gridDim.x * 256) ctl[i] = 0;
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x, nt = (int64_t)gridDim.x * 256;
+    for (int64_t i = t; i < words; i += nt) ctl[i] = 0;
+    for (int64_t i = t; i < places; i += nt) mail[i] = EMPTY;
 }
 
 // FWD: rows row0 .. row0 + 127 of L y = b, blocks in increasing order; else
@@ -194,17 +304,21 @@ __global__ __launch_bounds__(256) void solve_reset_kernel(int *ctl, int words)
 // broadcast and one fused multiply-add per step on the chain, the divisions
 // outside it.
 template <bool FWD, bool ONE>
-__global__ __launch_bounds__(NTH) void solve_kernel(Tiles T, double *B, int64_t ldb, int nrhs, int *ctl)
+__global__ __launch_bounds__(NTH) void solve_kernel(Tiles T, double *B, int64_t ldb, int nrhs, int *ctl,
+                                                     unsigned long long *mail)
 {
     __shared__ double xs[2][HB * LDX];
     __shared__ double xh[HB * LDX];        // this workgroup's first solved half
     __shared__ double ds[2][HB * LDD];     // scaled diagonal blocks, ds[h][c * LDD + lane]
     __shared__ double rs[NR][HB + 1];      // right-hand side of the half being solved
-    __shared__ double dg[2 * HB];
-    __shared__ int s_word;
+    __shared__ double dg[2 * HB], rg[2 * HB];  // diagonal and its reciprocal
+    __shared__ int s_word, s_late;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, gi = lane & 15, gg = lane >> 4;
     const int b = T.b, nchunk = (nrhs + NR - 1) / NR, nblk = (int)((T.n + 127) / 128);
-    if (tid == 0) s_word = (int)atomicAdd((unsigned *)ctl, 1u);
+    if (tid == 0) {
+        s_word = (int)atomicAdd((unsigned *)ctl, 1u);
+        s_late = 0;
+    }
     __syncthreads();
     const int place = s_word;
     __syncthreads();
@@ -216,6 +330,8 @@ __global__ __launch_bounds__(NTH) void solve_kernel(Tiles T, double *B, int64_t 
     const int64_t row0 = (int64_t)blk * 128;
     const int I = (int)(row0 / b), lr = (int)(row0 - (int64_t)I * b);
     double *Bc = B + (int64_t)j0 * ldb;
+    constexpr int PER = HB * (ONE ? 1 : NR);  // places of a 64-block: right-hand side by right-hand side
+    unsigned long long *mc = mail + (int64_t)chunk * 2 * nblk * PER;
 
     // own right-hand side, diagonal blocks and the block between them, all read ahead of the chain
     double rb[4];
@@ -227,8 +343,14 @@ __global__ __launch_bounds__(NTH) void solve_kernel(Tiles T, double *B, int64_t 
     }
     const TileRef D = tile_ref(T, I, I);
     const double *Dd = (const double *)D.p + lr + (int64_t)lr * b;
-    if (tid < 2 * HB) dg[tid] = Dd[tid + (int64_t)tid * b];
-    __syncthreads();
+    bool plain = true;
+    if (tid < 2 * HB) {
+        const double d = Dd[tid + (int64_t)tid * b];
+        dg[tid] = d;
+        rg[tid] = 1.0 / d;
+        plain = in_range(d);
+    }
+    plain = __syncthreads_and(plain);
     for (int e = tid; e < 2 * HB * HB; e += NTH) {
         const int h = e / (HB * HB), r = e % HB, q = (e / HB) % HB;
         const double l = Dd[h * HB + r + (int64_t)(h * HB + q) * b];
@@ -237,20 +359,23 @@ __global__ __launch_bounds__(NTH) void solve_kernel(Tiles T, double *B, int64_t 
     }
     // the waves of the second half to be solved (rows 64.. forward, columns 0..63 backward)
     const bool second = FWD ? wave >= WAVES / 2 : wave < WAVES / 2;
-    Raw<!FWD> mid;
-    if constexpr (FWD) {
-        if (second) fetch(D, lr + wave * 16 + gi + (lr + gg) * b, 4 * b, mid);
-    } else {
-        if (second) fetch(D, lr + HB + 2 * gg + (lr + wave * 16 + gi) * b, mid);
-    }
-
+    // the rows solved first go first: what they wait for is on the chain
+    if (!second) __builtin_amdgcn_s_setprio(2);
     Sum<ONE> acc;
     acc.zero();
     const int first = FWD ? 0 : 2 * nblk - 1, count = 2 * seq;  // blocks before this workgroup's own
-    auto ref = [&](int k) {  // the tile holding step k's block
-        const int64_t q0 = (int64_t)(FWD ? k : first - k) * HB;
-        const int K = (int)(q0 / b);
-        return FWD ? tile_ref(T, I, K) : tile_ref(T, K, I);
+    // the tile holding step k's block; its class is read once per tile, as a read of
+    // it waits for the pieces sent for before
+    int at = -1;
+    TileRef Rt = D;
+    auto ref = [&](int k) {
+        const int K = (int)((int64_t)(FWD ? k : first - k) * HB / b);
+        if (K != at) {
+            at = K;
+            Rt = FWD ? tile_ref(T, I, K) : tile_ref(T, K, I);
+            Rt.cls = __builtin_amdgcn_readfirstlane(Rt.cls);
+        }
+        return Rt;
     };
     auto fetch_step = [&](int k, const TileRef &R, Raw<!FWD> &r) {
         const int64_t q0 = (int64_t)(FWD ? k : first - k) * HB;
@@ -259,49 +384,90 @@ __global__ __launch_bounds__(NTH) void solve_kernel(Tiles T, double *B, int64_t 
         else fetch(R, lq + 2 * gg + (lr + wave * 16 + gi) * b, r);
     };
     auto product = [&](const Raw<!FWD> &r, const TileRef &R, const double *x) {
+        // all of the operands first: neither a branch on the class nor a wait between the products
+        double a[STEPS], xk[STEPS];
 #pragma unroll
         for (int s = 0; s < STEPS; ++s) {
             const int k = FWD ? 4 * s + gg : 8 * (s >> 1) + 2 * gg + (s & 1);
-            acc.add(widen(r.u[s], R, T.lo16), x, k, gi);
+            xk[s] = x[ONE ? k : k * LDX + gi];
+        }
+        switch (R.cls) {
+        case P64: widen<P64>(r, gi, gg, T.lo16, R.t, a); break;
+        case P32: widen<P32>(r, gi, gg, T.lo16, R.t, a); break;
+        case P16: widen<P16>(r, gi, gg, T.lo16, R.t, a); break;
+        default: widen<P8>(r, gi, gg, T.lo16, R.t, a); break;
+        }
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s) acc.add(s, a[s], xk[s]);
+    };
+    auto give_up = [&]() {
+        for (int e = tid; e < 128 * nr; e += NTH) {
+            const int64_t i = row0 + e % 128;
+            if (i < T.n) Bc[i + (int64_t)(e / 128) * ldb] = __builtin_nan("");
         }
     };
     int seen = 0;
-    Raw<!FWD> ra, rn;
-    TileRef Ra = D, Rn = D;
-    if (count > 0) {
-        Ra = ref(0);
-        fetch_step(0, Ra, ra);
-    }
-    for (int k = 0; k < count; ++k) {
-        if (k + 1 < count) {
-            Rn = ref(k + 1);
-            fetch_step(k + 1, Rn, rn);
+    struct Piece {
+        Raw<!FWD> r;
+        TileRef R;
+    } p0, p1, p2;
+    auto start = [&](int k, Piece &p) {
+        if (k < count) {
+            p.R = ref(k);
+            fetch_step(k, p.R, p.r);
         }
-        if (k >= seen) {
-            if (tid == 0) s_word = wait_count(c, copy, k + 1, count - k > 4);
+    };
+    // step k with its piece in use, the one of step k + 2 sent for behind the values
+    // just received: loads return in order, and a poll behind a piece on its way
+    // from memory would wait for that first
+    auto step = [&](int k, Piece &use, Piece &next) -> bool {
+        if (count - k > NEAR && k >= seen) {
+            if (tid == 0) s_word = wait_count(c, copy, k + 1);
             __syncthreads();
             seen = s_word;
             if (seen < 0) {
-                for (int e = tid; e < 128 * nr; e += NTH) {
-                    const int64_t i = row0 + e % 128;
-                    if (i < T.n) st_dev(Bc + i + (int64_t)(e / 128) * ldb, __builtin_nan(""));
-                }
-                return;
+                give_up();
+                return false;
             }
         }
         double *x = xs[k & 1];
-        const int64_t q0 = (int64_t)(FWD ? k : first - k) * HB;
-        for (int e = tid; e < (ONE ? HB : HB * NR); e += NTH) {
-            const int r = e % HB, q = e / HB;
-            const double v = (q < nr && q0 + r < T.n) ? ld_dev(Bc + q0 + r + (int64_t)q * ldb) : 0.0;
-            x[ONE ? r : r * LDX + q] = v;
-        }
+        const unsigned long long *m = mc + (int64_t)(FWD ? k : first - k) * PER;
+        constexpr int EPT = (PER + NTH - 1) / NTH;
+        unsigned long long u[EPT];
+#pragma unroll
+        for (int j = 0; j < EPT; ++j)
+            if (PER >= NTH || tid < PER) u[j] = ld_mail(m + tid + NTH * j);
+#pragma unroll
+        for (int j = 0; j < EPT; ++j)
+            if (PER >= NTH || tid < PER) {
+                const int e = tid + NTH * j;
+                if (!receive(c, m + e, u[j])) s_late = 1;
+                x[ONE ? e : (e % HB) * LDX + e / HB] = __longlong_as_double((long long)u[j]);
+            }
         __syncthreads();
-        product(ra, Ra, x);
-        ra = rn;
-        Ra = Rn;
+        if (s_late) {
+            give_up();
+            return false;
+        }
+        start(k + 2, next);
+        if (!second || k + 1 < count) product(use.r, use.R, x);  // the last one: below
+        return true;
+    };
+    start(0, p0);
+    start(1, p1);
+    for (int k = 0; k < count; k += 3) {
+        if (!step(k, p0, p2)) return;
+        if (k + 1 < count && !step(k + 1, p1, p0)) return;
+        if (k + 2 < count && !step(k + 2, p2, p1)) return;
     }
 
+    // the block between the halves, in flight while the first is solved
+    Raw<!FWD> mid;
+    if constexpr (FWD) {
+        if (second) fetch(D, lr + wave * 16 + gi + (lr + gg) * b, 4 * b, mid);
+    } else {
+        if (second) fetch(D, lr + HB + 2 * gg + (lr + wave * 16 + gi) * b, mid);
+    }
     // the two halves of the own block
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
@@ -311,47 +477,85 @@ __global__ __launch_bounds__(NTH) void solve_kernel(Tiles T, double *B, int64_t 
         if (mine) {
             const int w = wave - (FWD ? half : 1 - half) * (WAVES / 2);
             if (ONE) {
-                double s = acc.v[0];
+                double s = acc.sum(0);
                 s += __shfl_xor(s, 16);
                 s += __shfl_xor(s, 32);
                 if (gg == 0) rs[0][w * 16 + gi] = rb[0] - s;
             } else {
 #pragma unroll
-                for (int v = 0; v < 4; ++v) rs[gi][w * 16 + gg + 4 * v] = rb[v] - acc.v[v];
+                for (int v = 0; v < 4; ++v) rs[gi][w * 16 + gg + 4 * v] = rb[v] - acc.sum(v);
             }
         }
         __syncthreads();
-        if (!ONE || wave == 0) {
-            constexpr int NQ = ONE ? 1 : NR / WAVES;
-            double v[NQ];
-            const double d = dg[h * HB + lane];
+        if (half == 0 && second && count > 0) {  // their last step, beside the solve of the first half
+            const double *x = xs[1];
+            if (count % 3 == 1) product(p0.r, p0.R, x);
+            else if (count % 3 == 2) product(p1.r, p1.R, x);
+            else product(p2.r, p2.R, x);
+        }
+        // two waves of the rows solved first (one for ONE), eight right-hand sides each
+        const int sw = wave - (FWD ? 0 : WAVES / 2);
+        constexpr int NQ = ONE ? 1 : 2;
+        const int q0 = ONE ? 0 : sw * 8 + gg * 2;
+        const bool solver = sw == 0 || (!ONE && sw == 1);
+        double v[4][NQ];
+        if (solver) {
+            double d[4], rd[4];
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                v[q] = rs[wave * NQ + q][lane];
-                if (!FWD) v[q] = v[q] / d;
+            for (int t = 0; t < 4; ++t) {
+                d[t] = dg[h * HB + 16 * t + gi];
+                rd[t] = rg[h * HB + 16 * t + gi];
             }
-            const double *dl = ds[h] + lane;
+            auto divide = [&]() {
+                bool fits = plain;
 #pragma unroll
-            for (int t = 0; t < HB - 1; ++t) {
-                const int cc = FWD ? t : HB - 1 - t;
-                const double l = dl[cc * LDD];
+                for (int t = 0; t < 4; ++t)
 #pragma unroll
-                for (int q = 0; q < NQ; ++q) v[q] -= l * bcast(v[q], cc);
-            }
-            const int64_t i = row0 + h * HB + lane;
+                    for (int q = 0; q < NQ; ++q) fits &= in_range(v[t][q]) || v[t][q] == 0.0;
+                if (__all(fits)) {
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                const int rq = wave * NQ + q;
-                if (FWD) v[q] = v[q] / d;
-                if (i < T.n && rq < nr) st_dev(Bc + i + (int64_t)rq * ldb, v[q]);
-                xh[ONE ? lane : lane * LDX + rq] = v[q];
-            }
-            stores_done();
+                    for (int t = 0; t < 4; ++t)
+#pragma unroll
+                        for (int q = 0; q < NQ; ++q) v[t][q] = div_by(v[t][q], d[t], rd[t]);
+                } else {
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+#pragma unroll
+                        for (int q = 0; q < NQ; ++q) v[t][q] = v[t][q] / d[t];
+                }
+            };
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) v[t][q] = rs[q0 + q][16 * t + gi];
+            if (!FWD) divide();
+            solve64<FWD, NQ>(v, ds[h], gi);
+            if (FWD) divide();
+            unsigned long long *m = mc + (row0 / HB + h) * PER + gi;
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int q = 0; q < NQ; ++q)
+                    if (!ONE || gg == 0) {
+                        st_mail(m + (q0 + q) * HB + 16 * t, v[t][q]);
+                        xh[ONE ? 16 * t + gi : (16 * t + gi) * LDX + q0 + q] = v[t][q];
+                    }
         }
         __syncthreads();
-        if (tid < NCOPY)
-            __hip_atomic_store(c.done + tid * STRIDE, count + half + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (solver) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    const int64_t i = row0 + h * HB + 16 * t + gi;
+                    if (i < T.n && q0 + q < nr && (!ONE || gg == 0)) Bc[i + (int64_t)(q0 + q) * ldb] = v[t][q];
+                }
+        }
     }
+    stores_done();
+    __syncthreads();
+    if (tid < NCOPY)
+        __hip_atomic_store(c.done + tid * STRIDE, count + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Right-hand sides per launch: 16 chunks share a launch, each with its own chain.
@@ -359,22 +563,27 @@ constexpr int MAXCHUNK = 16;
 
 size_t solve_ctl_bytes() { return (size_t)2 * (32 + MAXCHUNK * NCOPY * STRIDE) * sizeof(int); }
 
-void launch_solve(const Tiles &T, double *B, int64_t ldb, int nrhs, int *ctl, hipStream_t st)
+// mail: 2 * 16 * MAXCHUNK doubles per row of the tiles (4 KB) of scratch
+void launch_solve(const Tiles &T, double *B, int64_t ldb, int nrhs, int *ctl, double *mail, hipStream_t st)
 {
     const int words = (int)(solve_ctl_bytes() / sizeof(int));
     const unsigned nblk = (unsigned)((T.n + 127) / 128);
+    unsigned long long *mf = (unsigned long long *)mail;
     for (int j0 = 0; j0 < nrhs; j0 += MAXCHUNK * NR) {
         const int nr = nrhs - j0 < MAXCHUNK * NR ? nrhs - j0 : MAXCHUNK * NR;
         double *Bj = B + (int64_t)j0 * ldb;
-        const unsigned grid = nblk * (unsigned)((nr + NR - 1) / NR);
+        const unsigned chunks = (unsigned)((nr + NR - 1) / NR), grid = nblk * chunks;
+        const int64_t places = (int64_t)nblk * 128 * (nr == 1 ? 1 : NR * chunks);  // of one direction
         int *bwd = ctl + words / 2;
-        solve_reset_kernel<<<16, 256, 0, st>>>(ctl, words);
+        unsigned long long *mb = mf + places;
+        const int64_t fill = (2 * places + 1023) / 1024;
+        solve_reset_kernel<<<(unsigned)(fill < 16 ? 16 : fill > 2048 ? 2048 : fill), 256, 0, st>>>(ctl, words, mf, 2 * places);
         if (nr == 1) {
-            solve_kernel<true, true><<<grid, NTH, 0, st>>>(T, Bj, ldb, nr, ctl);
-            solve_kernel<false, true><<<grid, NTH, 0, st>>>(T, Bj, ldb, nr, bwd);
+            solve_kernel<true, true><<<grid, NTH, 0, st>>>(T, Bj, ldb, nr, ctl, mf);
+            solve_kernel<false, true><<<grid, NTH, 0, st>>>(T, Bj, ldb, nr, bwd, mb);
         } else {
-            solve_kernel<true, false><<<grid, NTH, 0, st>>>(T, Bj, ldb, nr, ctl);
-            solve_kernel<false, false><<<grid, NTH, 0, st>>>(T, Bj, ldb, nr, bwd);
+            solve_kernel<true, false><<<grid, NTH, 0, st>>>(T, Bj, ldb, nr, ctl, mf);
+            solve_kernel<false, false><<<grid, NTH, 0, st>>>(T, Bj, ldb, nr, bwd, mb);
         }
     }
 }

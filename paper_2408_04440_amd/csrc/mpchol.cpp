@@ -101,7 +101,7 @@ struct mpchol_handle {
     char *pin_table() const { return pin + 64 + (size_t)nt * nt * 16; }
     char *pin_items() const { return pin_table() + ((size_t)nt * nt * 6 + 63) / 64 * 64; }
     size_t pin_bytes() const { return 64 + (size_t)nt * nt * 22 + 64 + PIN_ITEMS; }
-    std::mutex sample_mu;
+    std::mutex p64_mu;  // p64 as scratch between factorizations (draws, solves): one call's launches at a time
     double *d_partial = nullptr, *d_tres2 = nullptr;
     // backward-error estimator scratch
     double *d_est = nullptr;
@@ -1179,7 +1179,11 @@ extern "C" int mpchol_solve(mpchol_t h, int32_t nrhs, double *B, int64_t ldb)
     if (h->state != S_FACTORED) return MPCHOL_EORDER;
     HIPCHK(hipSetDevice(h->dev));
     HIPCHK(hipEventRecord(h->ev[2], h->st));
-    launch_solve(h->tiles(), B, ldb, nrhs, h->d_solve, h->st);
+    {
+        // mailbox: the panel copies (48 KB per tile column of 128 at least, 4 KB a row wanted)
+        std::lock_guard<std::mutex> lk(h->p64_mu);
+        launch_solve(h->tiles(), B, ldb, nrhs, h->d_solve, h->p64, h->st);
+    }
     HIPCHK(hipEventRecord(h->ev[3], h->st));
     HIPCHK(hipGetLastError());
     return MPCHOL_OK;
@@ -1204,7 +1208,7 @@ extern "C" int mpchol_sample(mpchol_t h, int32_t ndraws, uint64_t seed, float *Y
     // draws at a time as they hold (over 1,500 for any tile size); all passes of a
     // call are enqueued together, so that calls from several threads cannot mix
     {
-        std::lock_guard<std::mutex> lk(h->sample_mu);
+        std::lock_guard<std::mutex> lk(h->p64_mu);
         float *Z = (float *)h->p64;
         const int64_t chunk = (int64_t)NSET * h->nt * h->b * h->b * 2 / h->n / 128 * 128;
         for (int64_t d0 = 0; d0 < ndraws; d0 += chunk) {

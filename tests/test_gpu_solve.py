@@ -51,3 +51,55 @@ def test_solve_edges(n, tile, nrhs, pad, mixed):
     scale = np.linalg.norm(Lg) ** 2 * np.linalg.norm(X) + np.linalg.norm(B)
     log(f"  solve n={n} tile={tile} nrhs={nrhs} mixed={mixed}: {np.linalg.norm(R) / scale:.2e}")
     assert np.linalg.norm(R) <= 4 * n * 2.0 ** -53 * scale
+
+
+@pytest.mark.parametrize("n,tile,exp2,nrhs", [(300, 128, 0, 3), (300, 128, -1010, 16), (300, 128, 980, 17),
+                                              (1000, 256, -1004, 1), (1000, 256, 990, 1)])
+def test_solve_scaled(n, tile, exp2, nrhs):
+    """Diagonals of the factor inside and outside the range in which quotients come
+    from reciprocals (2^-500 to 2^500), the bound of test_solve_edges on
+    everything scaled back (powers of two: exact)."""
+    torch = torch_cuda()
+    mod = M()
+    S = (synth.int_lower(n, 11) / (1.0 + np.arange(n))[None, :] + 3.0 * np.eye(n)) * 2.0 ** (exp2 // 2)
+    B = synth.rhs(n, nrhs)
+    h = mod.mpchol_create(n, tile)
+    try:
+        mod.mpchol_set_matrix(h, S @ S.T)
+        mod.mpchol_precision_map(h, mod.RULE_FP64)
+        assert mod.mpchol_factor(h) == 0
+        Lg = factor_dense(h, n) * 2.0 ** -(exp2 // 2)
+        Bt = torch.tensor(np.ascontiguousarray(B.T), device="cuda") * 2.0 ** (exp2 // 2)
+        mod.mpchol_solve(h, Bt.T, n)
+        X = Bt.cpu().numpy().T * 2.0 ** (exp2 // 2)
+    finally:
+        mod.mpchol_destroy(h)
+    u = 2.0 ** -53
+    res = np.linalg.norm(B - Lg @ (Lg.T @ X))
+    assert res <= 4 * n * u * (np.linalg.norm(Lg) ** 2 * np.linalg.norm(X) + np.linalg.norm(B))
+
+
+def test_solve_hands_on_any_nan():
+    """A right-hand side with NaN payloads (the mailbox's own mark among them) ends
+    as NaN where it reaches; the other right-hand sides are as without them."""
+    torch = torch_cuda()
+    mod = M()
+    n = 700
+    S = synth.int_lower(n, 11) / (1.0 + np.arange(n))[None, :] + 3.0 * np.eye(n)
+    h = mod.mpchol_create(n, 128)
+    try:
+        mod.mpchol_set_matrix(h, S @ S.T)
+        mod.mpchol_precision_map(h, mod.RULE_FP64)
+        assert mod.mpchol_factor(h) == 0
+        B = torch.tensor(np.ascontiguousarray(synth.rhs(n, 5).T), device="cuda")
+        clean = B.clone()
+        marks = torch.tensor(np.array([0x7FF85EED0BADF00D, 0xFFF85EED0BADF00D], dtype=np.uint64).view(np.float64),
+                             device="cuda")
+        B[1, 0], B[3, 130], B[3, 131] = marks[0], marks[1], marks[0]
+        mod.mpchol_solve(h, B.T, n)
+        mod.mpchol_solve(h, clean.T, n)
+        torch.cuda.synchronize()
+    finally:
+        mod.mpchol_destroy(h)
+    assert torch.equal(B[[0, 2, 4]], clean[[0, 2, 4]])
+    assert torch.isnan(B[1, 0]) and torch.isnan(B[3, 130])
