@@ -1,5 +1,7 @@
 // Emulation draws Y = L Z from the stored factor (Sec. III.B), with the
 // Philox4x32-10 / Box-Muller normal generator.
+#include <type_traits>
+
 #include "common.h"
 #include "launch.h"
 
@@ -87,18 +89,27 @@ void launch_normal_columns(uint64_t seed, int64_t n, int64_t d0, int nd, float *
 // What bounds it: the FP32 MFMA for many draws (64 x 64 outputs a wave, 16
 // products per eight LDS reads), the factor's bytes for few.  Raw codes of the
 // next K slice stay in registers while the current one is multiplied and are
-// converted only when staged; two consecutive rows per load.  The last tile rows,
-// with the most tiles to walk, take the first blocks.  (Four waves of 64 x 64 in
-// place of sixteen of 32 x 32, N = 16,384, 1000 draws: 4.92 -> 2.97 ms, 90 TFLOP/s;
-// one draw: 1.94 -> 0.50 ms, 2.1 TB/s of the factor; an order in which the strips
-// of equal length met on the same compute units took 5.2 ms.)
+// converted only when staged, by a loop per class; every class takes the same
+// 16-byte loads, so that no branch, and no wait, stands between them.  The last
+// tile rows, with the most tiles to walk, take the first blocks.  (Four waves of
+// 64 x 64 in place of sixteen of 32 x 32, N = 16,384, 1000 draws: 4.92 -> 2.97 ms;
+// an order in which the strips of equal length met on the same compute units took
+// 5.2 ms.  Without class branches between the loads and conversions: 2.97 -> 2.88
+// ms, 93 TFLOP/s; one draw 0.51 -> 0.46 ms, 2.3 TB/s of the factor; N = 32,768
+// under the norm rule, 100 draws 2.85 -> 2.48, 1000 draws 13.6 -> 11.7.)
 constexpr int ANT = 256;
 
-__device__ inline float widen32(uint64_t raw, int cls, int lo16, int t)
+// Two consecutive values of a stored tile, byte the offset of the first within it.
+template <int CLS> __device__ inline float2 widen32(ulonglong2 v, int byte, int lo16, int t)
 {
-    if (cls == P64) return (float)__longlong_as_double((long long)raw);
-    if (cls == P32) return __uint_as_float((uint32_t)raw);
-    return (float)decode_class((uint32_t)raw, cls, lo16, t);
+    if (CLS == P64)
+        return make_float2((float)__longlong_as_double((long long)v.x), (float)__longlong_as_double((long long)v.y));
+    const uint64_t u = pair_codes(v, byte);
+    const uint32_t w = (uint32_t)u;
+    if (CLS == P32) return make_float2(__uint_as_float(w), __uint_as_float((uint32_t)(u >> 32)));
+    constexpr int BITS = CLS == P16 ? 16 : 8;
+    constexpr uint32_t MASK = (1u << BITS) - 1;
+    return make_float2((float)decode_class(w & MASK, CLS, lo16, t), (float)decode_class((w >> BITS) & MASK, CLS, lo16, t));
 }
 
 template <int BM, int BN, int AK>
@@ -128,53 +139,23 @@ __global__ __launch_bounds__(ANT) void lower_apply_kernel(Tiles T, const float *
         for (int n = 0; n < NB; ++n) acc[m][n] = (float4_t){0.f, 0.f, 0.f, 0.f};
     const int nkt = b / AK, total = (I + 1) * nkt;
     // slice q: tile q / nkt of the row, columns (q % nkt) * AK
-    uint64_t ra[2 * APER];
+    ulonglong2 ra[APER];
     float rb[BPER];
-    int ca = 0, ta = 0;
+    int ca = 0, ta = 0, next = 0;
     const int r2 = 2 * (tid % (BM / 2)), c0 = tid / (BM / 2);  // A: rows r2, r2 + 1 of columns c0 + ACOL c
     const int kb = tid % AK, n0 = tid / AK;                    // B: K element kb of draws n0 + BCOL c
     const float *zb = Z + (int64_t)(s0 + n0) * ldz + kb;
     const bool whole = s0 + BN <= ndraws;
+    auto class_at = [&](int K) { return (I == K) ? (int)P64 : (int)T.map[I + (int64_t)K * T.nt]; };
     auto gload = [&](int q) {
         const int K = q / nkt, k0 = (q - K * nkt) * AK;
-        ca = (I == K) ? P64 : T.map[I + (int64_t)K * T.nt];
+        ca = __builtin_amdgcn_readfirstlane(next);  // read a slice ahead
+        next = class_at(min(q + 1, total - 1) / nkt);
         ta = T.tscale[I + (int64_t)K * T.nt];
         const char *sa = T.slots + tile_index(I, K) * T.slot_bytes;
-        const int off = tm * BM + r2 + (k0 + c0) * b;  // within one tile: below b * b
-        switch (ca) {
-        case P64:
+        const int off = tm * BM + r2 + (k0 + c0) * b, sh = class_shift(ca);  // within one tile: below b * b
 #pragma unroll
-            for (int c = 0; c < APER; ++c) {
-                const ulonglong2 v = *(const ulonglong2 *)((const uint64_t *)sa + off + ACOL * c * b);
-                ra[2 * c] = v.x;
-                ra[2 * c + 1] = v.y;
-            }
-            break;
-        case P32:
-#pragma unroll
-            for (int c = 0; c < APER; ++c) {
-                const uint64_t v = *(const uint64_t *)((const uint32_t *)sa + off + ACOL * c * b);
-                ra[2 * c] = v & 0xFFFFFFFFu;
-                ra[2 * c + 1] = v >> 32;
-            }
-            break;
-        case P16:
-#pragma unroll
-            for (int c = 0; c < APER; ++c) {
-                const uint32_t v = *(const uint32_t *)((const uint16_t *)sa + off + ACOL * c * b);
-                ra[2 * c] = v & 0xFFFFu;
-                ra[2 * c + 1] = v >> 16;
-            }
-            break;
-        default:
-#pragma unroll
-            for (int c = 0; c < APER; ++c) {
-                const uint16_t v = *(const uint16_t *)((const uint8_t *)sa + off + ACOL * c * b);
-                ra[2 * c] = v & 0xFFu;
-                ra[2 * c + 1] = v >> 8;
-            }
-            break;
-        }
+        for (int c = 0; c < APER; ++c) ra[c] = load_pair16(sa, (off + ACOL * c * b) << sh);
         const int64_t zk = (int64_t)K * b + k0;
         if (whole && zk + AK <= T.n) {
 #pragma unroll
@@ -188,14 +169,23 @@ __global__ __launch_bounds__(ANT) void lower_apply_kernel(Tiles T, const float *
             }
         }
     };
-    auto sstore = [&](int buf) {
+    auto astore = [&](auto cls, int buf) {  // a loop per class: no branch between its conversions
+        constexpr int CLS = decltype(cls)::value;
 #pragma unroll
-        for (int c = 0; c < APER; ++c)
-            *(float2 *)&As[buf][c0 + ACOL * c][r2] =
-                make_float2(widen32(ra[2 * c], ca, T.lo16, ta), widen32(ra[2 * c + 1], ca, T.lo16, ta));
+        for (int c = 0; c < APER; ++c)  // strips and columns start at multiples of 32 values
+            *(float2 *)&As[buf][c0 + ACOL * c][r2] = widen32<CLS>(ra[c], r2 << class_shift(CLS), T.lo16, ta);
+    };
+    auto sstore = [&](int buf) {
+        switch (ca) {
+        case P64: astore(std::integral_constant<int, P64>{}, buf); break;
+        case P32: astore(std::integral_constant<int, P32>{}, buf); break;
+        case P16: astore(std::integral_constant<int, P16>{}, buf); break;
+        default: astore(std::integral_constant<int, P8>{}, buf); break;
+        }
 #pragma unroll
         for (int c = 0; c < BPER; ++c) Bs[buf][kb][n0 + BCOL * c] = rb[c];
     };
+    next = class_at(0);
     gload(0);
     sstore(0);
     __syncthreads();
@@ -243,8 +233,8 @@ static void launch_apply(const Tiles &T, const float *Z, int64_t ldz, float *Y, 
 // them, so that no products are spent on absent columns.  A strip of 128 rows
 // walks up to n columns in sequence; where they are too few to fill the GPU
 // twice over and even out their lengths (fewer than 1024 workgroups), strips of
-// 32 rows do (N = 32,400, 100 draws: 5.4 against 2.8 ms; N = 16,384, 512: 2.0
-// against 1.9).
+// 32 rows do (N = 32,400, 100 draws: 5.4 against 2.5 ms; N = 16,384, 512: 2.0
+// against 1.8).
 void launch_lower_apply(const Tiles &T, const float *Z, int64_t ldz, float *Y, int64_t ldy, int ndraws, hipStream_t st)
 {
     if (ndraws <= 16) launch_apply<32, 16, 64>(T, Z, ldz, Y, ldy, ndraws, st);
