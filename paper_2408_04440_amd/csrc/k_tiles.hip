@@ -2,6 +2,7 @@
 // norms, the sender-side conversion of a factored panel, log-determinant
 // reduction and factor export.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "launch.h"
@@ -162,28 +163,40 @@ __global__ __launch_bounds__(256) void convert_kernel(Tiles T, Panel P, int k, c
         for (int q = 0; q < 4; ++q) P.pscale[I * 4 + q] = tq[q];
     }
 
-    for (int e = threadIdx.x; e < 4096; e += 256) {
-        int r = e & 63, c = e >> 6;
-        int64_t off = (int64_t)(sr * 64 + r) + (int64_t)(sc * 64 + c) * b;
-        double X = x64[off];
-        double Sv;
-        if (cls == P64) {
-            Sv = X;
-            ((double *)slot)[off] = Sv;
-        } else if (cls == P32) {
-            float f = (float)X;
-            Sv = (double)f;
-            ((float *)slot)[off] = f;
-        } else {
-            double xf = (double)(float)X;
-            uint32_t code = encode_class(xf, cls, lo16, ts);
-            Sv = decode_class(code, cls, lo16, ts);
-            if (cls == P16) ((uint16_t *)slot)[off] = (uint16_t)code;
-            else ((uint8_t *)slot)[off] = (uint8_t)code;
+    // 16 values a thread, all read before the first is used
+    const int r = threadIdx.x & 63, c0 = threadIdx.x >> 6;
+    const int off0 = sr * 64 + r + (sc * 64 + c0) * b;  // within one tile
+    double X[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) X[j] = x64[off0 + 4 * j * b];
+    auto store = [&](auto q) {
+        constexpr int CLS = decltype(q)::value;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int off = off0 + 4 * j * b;
+            double Sv = X[j];
+            if (CLS == P64) {
+                ((double *)slot)[off] = Sv;
+            } else if (CLS == P32) {
+                const float f = (float)X[j];
+                Sv = (double)f;
+                ((float *)slot)[off] = f;
+            } else {
+                const uint32_t code = encode_class((double)(float)X[j], CLS, lo16, ts);
+                Sv = decode_class(code, CLS, lo16, ts);
+                if (CLS == P16) ((uint16_t *)slot)[off] = (uint16_t)code;
+                else ((uint8_t *)slot)[off] = (uint8_t)code;
+            }
+            xs[c0 + 4 * j][r] = Sv;
+            if (mask & 1) x64[off] = Sv;
+            if ((mask & 2) && !T.lo32) P.p32[(int64_t)I * bb + off] = (float)Sv;
         }
-        xs[c][r] = Sv;
-        if (mask & 1) x64[off] = Sv;
-        if ((mask & 2) && !T.lo32) P.p32[(int64_t)I * bb + off] = (float)Sv;
+    };
+    switch (cls) {
+    case P64: store(std::integral_constant<int, P64>{}); break;
+    case P32: store(std::integral_constant<int, P32>{}); break;
+    case P16: store(std::integral_constant<int, P16>{}); break;
+    default: store(std::integral_constant<int, P8>{}); break;
     }
     const bool split = (mask & 2) && T.lo32;
     const bool mx = (mask & 8) && T.lo8;
@@ -200,23 +213,41 @@ __global__ __launch_bounds__(256) void convert_kernel(Tiles T, Panel P, int k, c
             }
             __syncthreads();
         }
-        for (int e = threadIdx.x; e < 4096; e += 256) {
-            int c = e & 63, r = e >> 6;
-            double Sv = xs[c][r];
-            int64_t roff = (int64_t)(sr * 64 + r) * b + (sc * 64 + c);
-            if (mask & 4) P.p16[(int64_t)I * bb + roff] = (uint16_t)encode_class(Sv, P16, lo16, tq[P16]);
-            if (mask & 8)
-                P.p8[(int64_t)I * bb + roff] = (uint8_t)encode_class(Sv, P8, lo16, mx ? xt[r][c >> 5] : tq[P8]);
+        // four consecutive columns of a row per thread and round: whole words out
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int c = 4 * (threadIdx.x & 15), rr = (threadIdx.x >> 4) + 16 * j;
+            const int64_t roff = (int64_t)I * bb + (int64_t)(sr * 64 + rr) * b + (sc * 64 + c);
+            double Sv[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) Sv[i] = xs[c + i][rr];
+            if (mask & 4) {
+                uint32_t u[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) u[i] = encode_class(Sv[i], P16, lo16, tq[P16]);
+                *(uint2 *)(P.p16 + roff) = make_uint2(u[0] | u[1] << 16, u[2] | u[3] << 16);
+            }
+            if (mask & 8) {
+                const int t = mx ? xt[rr][c >> 5] : tq[P8];
+                uint32_t u[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) u[i] = encode_class(Sv[i], P8, lo16, t);
+                *(uint32_t *)(P.p8 + roff) = u[0] | u[1] << 8 | u[2] << 16 | u[3] << 24;
+            }
             if (split) {  // FP32 copy as hi + mid + lo, each step exact in FP32
-                const float f = (float)Sv;
-                const uint16_t hi = f32_to_bf16(f);
-                const float r1 = f - bf16_to_f32(hi);
-                const uint16_t mid = f32_to_bf16(r1);
-                const uint16_t lo = f32_to_bf16(r1 - bf16_to_f32(mid));
-                uint16_t *d = P.p32s + (int64_t)I * 3 * bb + roff;
-                d[0] = hi;
-                d[bb] = mid;
-                d[2 * bb] = lo;
+                uint32_t hi[4], mid[4], lo[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float f = (float)Sv[i];
+                    hi[i] = f32_to_bf16(f);
+                    const float r1 = f - bf16_to_f32((uint16_t)hi[i]);
+                    mid[i] = f32_to_bf16(r1);
+                    lo[i] = f32_to_bf16(r1 - bf16_to_f32((uint16_t)mid[i]));
+                }
+                uint16_t *d = P.p32s + (int64_t)I * 2 * bb + roff;  // roff holds I * bb already
+                *(uint2 *)d = make_uint2(hi[0] | hi[1] << 16, hi[2] | hi[3] << 16);
+                *(uint2 *)(d + bb) = make_uint2(mid[0] | mid[1] << 16, mid[2] | mid[3] << 16);
+                *(uint2 *)(d + 2 * bb) = make_uint2(lo[0] | lo[1] << 16, lo[2] | lo[3] << 16);
             }
         }
     }
