@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 import synth
-from _gpu import M, factor_dense, log, same_factor_residuals, tile_rel, tile_residual_levels, torch_cuda
+from _gpu import M, factor_dense, log, same_factor_residuals, tile_rel, tile_residual_levels
 
 pytestmark = pytest.mark.gpu
 
@@ -337,7 +337,7 @@ def test_estimate_is_its_probes_residual(n, tile, eps):
     same 64 probes, E = Sigma - L L^T with the GPU's own factor.  Sums of at most
     n terms: an entry of E v is off by 2 n u (|L| |L|^T + |Sigma|) |v| on either
     side, so the estimate by 4 n u sqrt(n) (trace + ||Sigma||_F) / ||Sigma||_F."""
-    torch = torch_cuda()
+    torch = __import__("_gpu").torch_cuda()
     mod = M()
     sigma, x = synth.workload(int(np.ceil(np.sqrt(n))))
     sigma, x = sigma[:n], x[:n]
