@@ -155,7 +155,7 @@ __global__ __launch_bounds__(256) void scan_finish_kernel(Tiles T, Source S, con
 // ---------------------------------------------------------------- L^T V, L W
 // LT:  W[c of tile column K] = sum_{I >= K} L_IK(:, c)^T V[rows of I],
 // !LT: Z[r of tile row I]    = sum_{K <= I} L_IK(r, :) W[rows of K]:
-// strips of BM outputs, four waves of BM outputs x 16 probes, the sum taken ER
+// strips of BM outputs (32 or 64), four waves of BM outputs x 16 probes, the sum taken ER
 // rows (columns) of the stored tiles at a time on the FP64 MFMA.  What bounds it:
 // the latency of the pieces, then the MFMA.  Two steps' pieces of L and probes are
 // on their way in registers while a third is multiplied from LDS; they are widened
@@ -163,20 +163,21 @@ __global__ __launch_bounds__(256) void scan_finish_kernel(Tiles T, Source S, con
 // takes a long strip and then the short one from the other end, so that all blocks
 // are equally long.  All strips walk the probes from the same end, so that the L2
 // serves each piece to the blocks that meet there.  (N = 32,768: 4.4 (LT) and
-// 5.4 -> 2.1 ms each, 33 TFLOP/s; strips of 64 took 3.6 and 3.3 ms.)
-constexpr int BM = 32;                  // outputs per strip
-constexpr int LPT = ER * BM / 256 / 2;  // row pairs of the L piece per thread
+// 5.4 -> 2.1 ms each, 33 TFLOP/s.)
 constexpr int QPT = ER * EK / 256;      // elements of the probe piece per thread
-constexpr int LDK = ER + 2, LDR = BM + 16;  // 32 lanes of a read meet each of the 64 banks once
-static_assert(ER * BM % 512 == 0 && ER * EK % 256 == 0, "staging split");
+constexpr int LDK = ER + 2;  // 32 lanes of a read meet each of the 64 banks once
+static_assert(ER * EK % 256 == 0, "staging split");
 
-template <bool LT>
+template <bool LT, int BM>
 __global__ __launch_bounds__(256) void factor_apply_kernel(Tiles T, const double *__restrict__ X, int64_t ldx,
                                                            double *__restrict__ Y, int strips, bool pair)
 {
     // LT: rows of a tile are the summed index, consecutive in memory and in LDS
     // (ls[c][r]); otherwise the outputs are (ls[k][r])
+    constexpr int LDR = BM + 16;
     __shared__ __align__(16) double ls[2][LT ? BM * LDK : ER * LDR], xs[2][EK * LDK];
+    constexpr int LPT = ER * BM / 256 / 2;  // row pairs of the L piece per thread
+    static_assert(ER * BM % 512 == 0, "staging split");
     constexpr int MB = BM / 16, FAST = LT ? ER : BM;  // row index runs over FAST
     constexpr int COL = 2 * 256 / FAST;               // columns per round of loads
     const int b = T.b, per = b / BM, nrs = b / ER;
@@ -296,12 +297,12 @@ __global__ __launch_bounds__(256) void factor_apply_kernel(Tiles T, const double
 
 // Pairs of strips where they still make two blocks per compute unit; with fewer
 // strips the longest one decides, and single strips start them all at once.
-template <bool LT>
+template <bool LT, int BM>
 static void factor_apply(const Tiles &T, const double *X, int64_t ldx, double *Y, hipStream_t st)
 {
     const int strips = T.nt * (T.b / BM);  // even: b is a multiple of 128
     const bool pair = strips >= 1024;
-    factor_apply_kernel<LT><<<(unsigned)(pair ? strips / 2 : strips), 256, 0, st>>>(T, X, ldx, Y, strips, pair);
+    factor_apply_kernel<LT, BM><<<(unsigned)(pair ? strips / 2 : strips), 256, 0, st>>>(T, X, ldx, Y, strips, pair);
 }
 
 // Widen FP32 normals to FP64 probes, zero beyond n.
@@ -375,8 +376,16 @@ void launch_estimate(const Tiles &T, const Source &S, bool sorted, uint64_t seed
         const dim3 g((unsigned)((np + 255) / 256), (unsigned)((np + 16383) / 16384));
         for (int q0 = 0; q0 < EK; q0 += DQ) sigma_v_kernel<<<g, 256, 0, st>>>(T, S, V + q0 * np, np, SV + q0 * np);
     }
-    factor_apply<true>(T, V, np, W, st);
-    factor_apply<false>(T, W, np, Z, st);
+    // strips of 64 halve the readings of the probes, but few of them leave the GPU
+    // uneven (both products, strips of 32 and 64: N = 32,768 4.2 and 5.6 ms, 49,152
+    // 9.2 and 8.9, 65,536 16.0 and 13.8, 129,600 60.5 and 54.8)
+    if (np >= 49152) {
+        factor_apply<true, 64>(T, V, np, W, st);
+        factor_apply<false, 64>(T, W, np, Z, st);
+    } else {
+        factor_apply<true, 32>(T, V, np, W, st);
+        factor_apply<false, 32>(T, W, np, Z, st);
+    }
     residual_part_kernel<<<estimate_chunks(T.n), SC, 0, st>>>(SV, Z, T.n, np, Fin);
     residual_sum_kernel<<<1, 256, 0, st>>>(Fin, estimate_chunks(T.n), out);
 }

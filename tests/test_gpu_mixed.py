@@ -362,3 +362,41 @@ def test_estimate_is_its_probes_residual(n, tile, eps):
     tol = 4 * n * 2.0 ** -53 * np.sqrt(n) * (float(S.trace()) + fro) / fro
     log(f"  n={n} tile={tile}: {est:.6e} {want:.6e} tol {tol:.1e}")
     assert abs(est - want) <= tol
+
+
+@pytest.mark.parametrize("n,tile,eps", [(49152, 2048, 1e-4), (65600, 1024, 1e-4)])
+def test_estimate_on_wide_strips(n, tile, eps):
+    """As above where the products take strips of 64 (single, and in pairs with an
+    odd number of tiles), Sigma V formed in blocks of rows."""
+    torch = __import__("_gpu").torch_cuda()
+    mod = M()
+    sigma, x = synth.workload(int(np.ceil(np.sqrt(n))))
+    sigma, x = sigma[:n], x[:n]
+    h = mod.mpchol_create(n, tile)
+    try:
+        mod.mpchol_set_generator(h, sigma, x, 5.0, 1e-8)
+        mod.mpchol_precision_map(h, mod.RULE_NORM, eps)
+        assert mod.mpchol_factor(h) == 0
+        Lt = torch.zeros((n, n), dtype=torch.float64, device="cuda")
+        mod.mpchol_get_factor(h, Lt.T, n)
+        z = torch.empty(64 * n, dtype=torch.float32, device="cuda")
+        mod.mpchol_normal_draws(h, 64 * n, 11, z)
+        est = mod.mpchol_backward_error_estimate(h, 1, 11)
+    finally:
+        mod.mpchol_destroy(h)
+    s, xs = torch.tensor(sigma, device="cuda"), torch.tensor(x, device="cuda")
+    V = z.view(64, n).double()
+    SV, fro2 = torch.empty_like(V), 0.0
+    for i in range(0, n, 4096):
+        j = slice(i, min(n, i + 4096))
+        S = s[j, None] * s[None, :] * torch.exp(-(xs[j, None] - xs[None, :]).abs() / 5.0)
+        S[:, j].diagonal().add_(1e-8)
+        SV[:, j] = V @ S.T
+        fro2 += float(S.square().sum())
+    fro, trace = fro2 ** 0.5, float((s * s).sum()) + 1e-8 * n
+    want = float((SV - (V @ Lt.T) @ Lt).norm()) / (8.0 * fro)
+    tol = 4 * n * 2.0 ** -53 * np.sqrt(n) * (trace + fro) / fro
+    log(f"  n={n} tile={tile}: {est:.6e} {want:.6e} tol {tol:.1e}")
+    assert abs(est - want) <= tol
+    del Lt
+    torch.cuda.empty_cache()
