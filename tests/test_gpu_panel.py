@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import synth
-from _gpu import M, factor_dense
+from _gpu import M, factor_dense, torch_cuda
 
 pytestmark = pytest.mark.gpu
 
@@ -60,3 +60,28 @@ def test_update_block_shapes(tile, n):
         assert np.array_equal(factor_dense(h, n), L0)
     finally:
         mod.mpchol_destroy(h)
+
+
+@pytest.mark.parametrize("n,tile,pad,shift", [(1, 128, 0, 0), (127, 128, 1, 0), (129, 128, 0, 0), (300, 128, 1, 1),
+                                              (300, 128, 0, 1), (1030, 512, 2, 0)])
+def test_get_factor_layouts(n, tile, pad, shift):
+    """The dense copy in every class at odd sizes, leading dimensions and bases: the
+    same values through each layout, zero above the diagonal, nothing else touched."""
+    torch = torch_cuda()
+    mod = M()
+    nt = -(-n // tile)
+    um = np.asfortranarray(np.tril((np.arange(nt * nt).reshape(nt, nt) % 4).astype(np.uint8), -1))
+    L0 = synth.int_lower(n, 9)
+    h = mod.mpchol_create(n, tile)
+    try:
+        mod.mpchol_set_matrix(h, L0 @ L0.T)
+        mod.mpchol_precision_map(h, mod.RULE_USER, 1e-9, um)
+        assert mod.mpchol_factor(h) == 0
+        buf = torch.full((shift + n * (n + pad),), 7.0, dtype=torch.float64, device="cuda")
+        Lt = buf[shift:].view(n, n + pad)
+        mod.mpchol_get_factor(h, Lt.T, n)
+        torch.cuda.synchronize()
+    finally:
+        mod.mpchol_destroy(h)
+    assert np.array_equal(Lt[:, :n].cpu().numpy().T, L0)
+    assert torch.all(Lt[:, n:] == 7.0) and torch.all(buf[:shift] == 7.0)
