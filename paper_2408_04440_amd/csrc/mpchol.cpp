@@ -24,8 +24,7 @@ namespace {
 enum State { S_CREATED = 0, S_SOURCE = 1, S_LOADED = 2, S_FACTORED = 3, S_FAILED = 4 };
 
 // Panel copy sets, indexed by panel column mod NSET: the two pairs whose
-// low-class updates are applied together, and the pair the look-ahead
-// stream is factoring.
+// low-class updates are applied together, and the pair being factored.
 constexpr int NSET = 6;
 
 double unit_roundoff(int q, int lo16)
