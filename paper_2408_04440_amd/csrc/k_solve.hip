@@ -25,7 +25,8 @@
 // and the values read after it are three trips to memory instead of one); the
 // others, further back, wait for a count of finished blocks, raised when a
 // workgroup's stores have completed (vmcnt 0, then the barrier), and poll it at
-// leisure.  A wait that lasts longer than WAIT_TICKS leaves NaN in the rows it
+// leisure.  Workgroups that follow on the values alone can be done before the one
+// they got them from has raised the count, so it only ever goes up.  A wait that lasts longer than WAIT_TICKS leaves NaN in the rows it
 // could not solve and ends the launch.
 #include <type_traits>
 
@@ -178,6 +179,12 @@ __device__ inline bool out_of_time(const Ctl &c, long long t0)
         return false;
     __hip_atomic_store(c.stop, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return true;
+}
+
+// Raises a count of finished blocks to v, whatever a later workgroup has made of it.
+__host__ __device__ inline void raise_count(int *p, int v)
+{
+    __hip_atomic_fetch_max(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // thread 0: waits until `need` blocks are finished; their number, or -1
@@ -554,8 +561,7 @@ __global__ __launch_bounds__(NTH) void solve_kernel(Tiles T, double *B, int64_t 
     }
     stores_done();
     __syncthreads();
-    if (tid < NCOPY)
-        __hip_atomic_store(c.done + tid * STRIDE, count + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid < NCOPY) raise_count(c.done + tid * STRIDE, count + 2);
 }
 
 // Right-hand sides per launch: 16 chunks share a launch, each with its own chain.

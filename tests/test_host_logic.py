@@ -201,3 +201,26 @@ def test_residue_conversions():
     for w, c in zip(want[::2], cases[::2]):
         p = int(c.split()[-1])
         assert -(p // 2) <= w <= (p - 1) // 2
+
+
+# ---------------------------------------------------------------- the solve's chain
+def test_finished_count_of_the_solve_never_goes_down():
+    """Places of the chain that follow on the values alone may publish before the
+    place they got them from: the count then stays, as a place m further back
+    waits for 2 m - 4 finished blocks and no later one need come."""
+    import itertools
+    import shutil
+    import subprocess
+
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    out = os.path.join(root, "_build", "solve_count_check")
+    os.makedirs(os.path.dirname(out), exist_ok=True)
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not shutil.which(hipcc) and not os.path.exists(hipcc):
+        pytest.skip("hipcc not available")
+    subprocess.check_call([hipcc, "-O2", "-std=c++17", "-x", "hip", "--offload-arch=gfx950", "-Xclang", "-target-feature",
+                           "-Xclang", "-packed-fp32-ops", os.path.join(root, "tests", "solve_count_check.cpp"), "-o", out],
+                          stderr=subprocess.DEVNULL)
+    for order in itertools.permutations(range(4)):
+        got = [int(v) for v in subprocess.run([out, *map(str, order)], capture_output=True, text=True, check=True).stdout.split()]
+        assert got == [2 * max(order[:i + 1]) + 2 for i in range(4)], (order, got)
