@@ -108,15 +108,21 @@ __device__ inline void sqrt_rcp(double d, double &s, double &r)
     r = h + h;
 }
 
-// acc[ct] += X(rows 16w.., k) Y(rows 16ct.., k)^T over columns k0 .. k1 - 1 (a
-// multiple of 16) of the LDS blocks.  Operands swapped: a lane holds row gi of its wave's 16 and
-// columns gg + 4v of each 16-column tile.
-__device__ inline void mma64(double4_t (&acc)[4], const double *X, const double *Y, int wave, int gi, int gg,
+// v[ct] += X(rows 16w.., k) Y(rows 16ct.., k)^T over columns k0 .. k1 - 1 (a
+// multiple of 16) of the LDS blocks, summed from zero and added once: a v that
+// starts at a block of the matrix is then rounded at its size once per call, not
+// once per product, and the error does not grow with the tile (1024: 6 to 2 u).
+// Operands swapped: a lane holds row gi of its wave's 16 and columns gg + 4v of
+// each 16-column tile.
+__device__ inline void mma64(double4_t (&v)[4], const double *X, const double *Y, int wave, int gi, int gg,
                              int k0 = 0, int k1 = 64)
 {
     struct Ops {
         double x[2], y[2][4];
     } u, w;
+    double4_t acc[4];
+#pragma unroll
+    for (int ct = 0; ct < 4; ++ct) acc[ct] = (double4_t){0.0, 0.0, 0.0, 0.0};
     auto load = [&](int k, Ops &o) {
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
@@ -141,6 +147,8 @@ __device__ inline void mma64(double4_t (&acc)[4], const double *X, const double 
         if (k + 16 < k1) load(k + 16, u);
         mma(w);
     }
+#pragma unroll
+    for (int ct = 0; ct < 4; ++ct) v[ct] += acc[ct];
 }
 
 // Panel p of X = -acc L^-T for a wave's 16 rows: L the lower 64 x 64 block in
@@ -182,13 +190,13 @@ __device__ inline void wave_trsm16(double4_t (&acc)[4], int p, const double *L, 
     }
 #pragma unroll
     for (int r = 1; r < 4; ++r) {
-        acc[r - 1] = acc[r];
+        double4_t sum = {0.0, 0.0, 0.0, 0.0};  // added once, as in mma64
         if (p + r < 4) {
 #pragma unroll
             for (int t = 0; t < 4; ++t)
-                acc[r - 1] =
-                    __builtin_amdgcn_mfma_f64_16x16x4f64(Lp[(4 * t + gg) * LD64 + 16 * r], a[t], acc[r - 1], 0, 0, 0);
+                sum = __builtin_amdgcn_mfma_f64_16x16x4f64(Lp[(4 * t + gg) * LD64 + 16 * r], a[t], sum, 0, 0, 0);
         }
+        acc[r - 1] = acc[r] + sum;
     }
 }
 

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import synth
-from _gpu import M, factor_dense, torch_cuda
+from _gpu import M, factor_dense, log, torch_cuda
 
 pytestmark = pytest.mark.gpu
 
@@ -85,3 +85,35 @@ def test_get_factor_layouts(n, tile, pad, shift):
         mod.mpchol_destroy(h)
     assert np.array_equal(Lt[:, :n].cpu().numpy().T, L0)
     assert torch.all(Lt[:, n:] == 7.0) and torch.all(buf[:shift] == 7.0)
+
+
+@pytest.mark.parametrize("tile,n", [(256, 1024), (512, 1024), (1024, 1024), (2048, 2048), (1024, 2048)])
+def test_factor_error_does_not_grow_with_the_tile(tile, n):
+    """A - L L^T in long double on entries that stay large under elimination: the
+    last 256 of the diagonal, and (i + n/2, i), whose rows are 0.9 alike.  A value
+    of size A is to be rounded once per 64 columns and at most 24 times within its
+    own block of 64, each with a standard deviation of at most u A / sqrt(3); the
+    sums of 64 products, about A 32 / n each, add less than (u A)^2 to the
+    variance.  (Rounded at every product: 2 to 5 times this bound.)"""
+    rng = np.random.default_rng(17)
+    X = rng.standard_normal((n, 2 * n))
+    X[n // 2:] = 0.9 * X[:n // 2] + np.sqrt(0.19) * X[n // 2:]
+    A = X @ X.T / (2 * n)
+    A = (A + A.T) / 2
+    mod = M()
+    h = mod.mpchol_create(n, tile)
+    try:
+        mod.mpchol_set_matrix(h, A)
+        mod.mpchol_precision_map(h, mod.RULE_FP64)
+        assert mod.mpchol_factor(h) == 0
+        L = factor_dense(h, n).astype(np.longdouble)
+    finally:
+        mod.mpchol_destroy(h)
+    last, half = np.arange(n - 256, n), np.arange(n // 2 - 128, n // 2)
+    for rows, cols in ((last, last), (half + n // 2, half)):
+        res = A[rows, cols] - (L[rows] * L[cols]).sum(axis=1)
+        size = np.sqrt(A[rows, rows] * A[cols, cols])
+        rms = float(np.sqrt(np.mean((res / size) ** 2))) * 2.0 ** 53
+        bound = np.sqrt((cols.max() / 64 + 24) / 3 + 1)
+        log(f"  n={n} tile={tile}: {rms:.2f} u, bound {bound:.2f} u")
+        assert rms <= bound
