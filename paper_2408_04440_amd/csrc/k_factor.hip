@@ -94,6 +94,11 @@ __device__ inline double div_by(double x, double d, double r)
     return __builtin_fma(__builtin_fma(-q, d, x), r, q);
 }
 
+// A diagonal element d of L as the substitutions keep it: 0 in place of infinity
+// (an infinite entry of the matrix).  With r = 1 / d = 0 div_by then gives 0, as
+// x / d does; with d itself its remainder would be 0 * infinity.
+__device__ inline double as_divisor(double d) { return d == __builtin_inf() ? 0.0 : d; }
+
 // s = sqrt(d) and r = 1 / s to about 47 bits, for d in [2^-900, 2^900]: one
 // step of Goldschmidt's iteration from the hardware's estimate, the root then
 // corrected by its exact remainder (a perfect square gives its root exactly).
@@ -158,7 +163,8 @@ __device__ inline void mma64(double4_t (&v)[4], const double *X, const double *Y
 // the code (a diagonal workgroup runs it once, and four copies cost more in
 // instruction fetches than the moves).  Every lane gathers its row of the panel
 // (the four lane groups hold the same rows) and substitutes column by column
-// against broadcasts of the diagonal block's rows from other lanes; the
+// against broadcasts of the diagonal block's rows from other lanes (the diagonal
+// as as_divisor gives it); the
 // panel's product with the rest of L goes to the later sums on the MFMA.
 // put(t, v): lane (gi, gg) delivers X(gi, 16 p + 4 t + gg).
 template <typename Put>
@@ -430,7 +436,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
 #pragma unroll
             for (int q = 0; q < 4; ++q) l[q] = ld_dev((const double *)(pl + (16 * p + 4 * q) * cs + lin8));
 #pragma unroll
-            for (int q = 0; q < 4; ++q) Bs[(16 * p + wave + 4 * q) * LD64 + lane] = l[q];
+            for (int q = 0; q < 4; ++q)
+                Bs[(16 * p + wave + 4 * q) * LD64 + lane] = lane == 16 * p + wave + 4 * q ? as_divisor(l[q]) : l[q];
             const double rl = 1.0 / d;
             __syncthreads();
             wave_trsm16(acc1, p, Bs, rl, scratch[wave], gi, gg, [&](int t, double v) {
@@ -523,7 +530,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void t
     load_diag(0);
     for (int cb = 0; cb < b; cb += 64) {
 #pragma unroll
-        for (int q = 0; q < 16; ++q) Ls[(wave + 4 * q) * LD64 + lane] = lv[q];
+        for (int q = 0; q < 16; ++q) Ls[(wave + 4 * q) * LD64 + lane] = lane == wave + 4 * q ? as_divisor(lv[q]) : lv[q];
         if (wave == 0) inv[lane] = 1.0 / dv;
         // right-hand side, read ahead of the products
         double4_t w[4], acc[4];

@@ -117,3 +117,30 @@ def test_factor_error_does_not_grow_with_the_tile(tile, n):
         bound = np.sqrt((cols.max() / 64 + 24) / 3 + 1)
         log(f"  n={n} tile={tile}: {rms:.2f} u, bound {bound:.2f} u")
         assert rms <= bound
+
+
+@pytest.mark.parametrize("tile,n,col", [(128, 300, 5), (128, 300, 100), (256, 600, 70), (256, 600, 599), (512, 1100, 511)])
+def test_infinite_diagonal_entry(tile, n, col):
+    """A quotient by an infinite pivot is 0, in the pivot's own block of 64, in the
+    tile's other blocks and in the panel below: the other rows and columns are
+    the factor of the matrix without that one."""
+    mod = M()
+    L0 = synth.int_lower(n, 6)
+    A = L0 @ L0.T + n * np.eye(n)
+    others = np.delete(np.arange(n), col)
+    want = np.zeros((n, n))
+    want[np.ix_(others, others)] = np.linalg.cholesky(A[np.ix_(others, others)])
+    want[col, :col] = np.linalg.solve(want[:col, :col], A[:col, col]) if col else 0.0
+    A[col, col] = np.inf
+    h = mod.mpchol_create(n, tile)
+    try:
+        mod.mpchol_set_matrix(h, A)
+        mod.mpchol_precision_map(h, mod.RULE_FP64)
+        assert mod.mpchol_factor(h) == 0
+        assert mod.mpchol_logdet(h) == np.inf
+        got = factor_dense(h, n)
+    finally:
+        mod.mpchol_destroy(h)
+    assert got[col, col] == np.inf and np.all(got[col + 1:, col] == 0.0)
+    got[col, col] = 0.0
+    assert np.abs(got - want).max() <= n * 2.0 ** -53 * np.sqrt(np.diagonal(A)[others].max())
