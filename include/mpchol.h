@@ -207,7 +207,12 @@ int mpchol_logdet(mpchol_t h, double *out);
 
 /* Overwrite device B (n x nrhs, ldb >= n, FP64) with Sigma^-1 B by forward
  * and backward tile substitution; diagonal blocks in FP64, off-diagonal
- * updates read each tile in its stored precision, exactly widened to FP64. */
+ * updates read each tile in its stored precision, exactly widened to FP64.
+ * Only enqueues.  Workgroups wait for each other inside the kernels, 30 s at
+ * most; where such a wait ends without its value (a GPU that was stopped
+ * meanwhile), rows of B are left as NaN, and the next logdet, sample,
+ * backward_error (_matrix, _estimate), get_tile_scales or get_stats call on the
+ * handle returns MPCHOL_EHIP, once. */
 int mpchol_solve(mpchol_t h, int32_t nrhs, double *B, int64_t ldb);
 
 /* Emulation draws (Sec. III.B): device Y (n x ndraws, ldy >= n, FP32) =

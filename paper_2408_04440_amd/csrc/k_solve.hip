@@ -26,8 +26,8 @@
 // others, further back, wait for a count of finished blocks, raised when a
 // workgroup's stores have completed (vmcnt 0, then the barrier), and poll it at
 // leisure.  Workgroups that follow on the values alone can be done before the one
-// they got them from has raised the count, so it only ever goes up.  A wait that lasts longer than WAIT_TICKS leaves NaN in the rows it
-// could not solve and ends the launch.
+// they got them from has raised the count, so it only ever goes up.  A wait that lasts longer than its limit leaves NaN in the rows it
+// could not solve, ends the launch and sets the caller's word.
 #include <type_traits>
 
 #include "common.h"
@@ -52,6 +52,8 @@ struct Ctl {
     unsigned *ticket;  // next place in the chain (shared by the chunks of a launch)
     int *stop;         // set when a wait ran out
     int *done;         // finished blocks: NCOPY copies
+    int *late;         // host memory: the same, for the caller
+    long long wait;    // the limit, in ticks
 };
 
 __device__ inline unsigned long long ld_mail(const unsigned long long *p)
@@ -175,9 +177,10 @@ __device__ inline double div_by(double v, double d, double r)
 // a wait has run out, here or elsewhere in this direction
 __device__ inline bool out_of_time(const Ctl &c, long long t0)
 {
-    if (!__hip_atomic_load(c.stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) && wall_clock64() - t0 <= WAIT_TICKS)
+    if (!__hip_atomic_load(c.stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) && wall_clock64() - t0 <= c.wait)
         return false;
     __hip_atomic_store(c.stop, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(c.late, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     return true;
 }
 
@@ -312,7 +315,7 @@ __global__ __launch_bounds__(256) void solve_reset_kernel(int *ctl, int words, u
 // outside it.
 template <bool FWD, bool ONE>
 __global__ __launch_bounds__(NTH) void solve_kernel(Tiles T, double *B, int64_t ldb, int nrhs, int *ctl,
-                                                     unsigned long long *mail)
+                                                     unsigned long long *mail, int *late, long long wait)
 {
     __shared__ double xs[2][HB * LDX];
     __shared__ double xh[HB * LDX];        // this workgroup's first solved half
@@ -331,7 +334,7 @@ __global__ __launch_bounds__(NTH) void solve_kernel(Tiles T, double *B, int64_t 
     __syncthreads();
     const int chunk = place % nchunk, seq = place / nchunk;
     const int blk = FWD ? seq : nblk - 1 - seq;
-    const Ctl c{(unsigned *)ctl, ctl + 1, ctl + 32 + chunk * (NCOPY * STRIDE)};
+    const Ctl c{(unsigned *)ctl, ctl + 1, ctl + 32 + chunk * (NCOPY * STRIDE), late, wait};
     const int copy = seq % NCOPY;
     const int j0 = chunk * NR, nr = min(NR, nrhs - j0);
     const int64_t row0 = (int64_t)blk * 128;
@@ -570,7 +573,7 @@ constexpr int MAXCHUNK = 16;
 size_t solve_ctl_bytes() { return (size_t)2 * (32 + MAXCHUNK * NCOPY * STRIDE) * sizeof(int); }
 
 // mail: 2 * 16 * MAXCHUNK doubles per row of the tiles (4 KB) of scratch
-void launch_solve(const Tiles &T, double *B, int64_t ldb, int nrhs, int *ctl, double *mail, hipStream_t st)
+void launch_solve(const Tiles &T, double *B, int64_t ldb, int nrhs, int *ctl, double *mail, int *late, hipStream_t st)
 {
     const int words = (int)(solve_ctl_bytes() / sizeof(int));
     const unsigned nblk = (unsigned)((T.n + 127) / 128);
@@ -585,11 +588,11 @@ void launch_solve(const Tiles &T, double *B, int64_t ldb, int nrhs, int *ctl, do
         const int64_t fill = (2 * places + 1023) / 1024;
         solve_reset_kernel<<<(unsigned)(fill < 16 ? 16 : fill > 2048 ? 2048 : fill), 256, 0, st>>>(ctl, words, mf, 2 * places);
         if (nr == 1) {
-            solve_kernel<true, true><<<grid, NTH, 0, st>>>(T, Bj, ldb, nr, ctl, mf);
-            solve_kernel<false, true><<<grid, NTH, 0, st>>>(T, Bj, ldb, nr, bwd, mb);
+            solve_kernel<true, true><<<grid, NTH, 0, st>>>(T, Bj, ldb, nr, ctl, mf, late, WAIT_TICKS);
+            solve_kernel<false, true><<<grid, NTH, 0, st>>>(T, Bj, ldb, nr, bwd, mb, late, WAIT_TICKS);
         } else {
-            solve_kernel<true, false><<<grid, NTH, 0, st>>>(T, Bj, ldb, nr, ctl, mf);
-            solve_kernel<false, false><<<grid, NTH, 0, st>>>(T, Bj, ldb, nr, bwd, mb);
+            solve_kernel<true, false><<<grid, NTH, 0, st>>>(T, Bj, ldb, nr, ctl, mf, late, WAIT_TICKS);
+            solve_kernel<false, false><<<grid, NTH, 0, st>>>(T, Bj, ldb, nr, bwd, mb, late, WAIT_TICKS);
         }
     }
 }

@@ -98,9 +98,10 @@ int launch_cov_samples(const Tiles &T, const double *xi, int64_t ldxi, int64_t m
 int estimate_probes();
 
 // ---- solve (k_solve.hip): ctl = solve_ctl_bytes(), mail = 4 KB per row of the tiles of
-// scratch, cleared by the launch
+// scratch, cleared by the launch; *late (host memory that the device writes) becomes 1
+// where a wait ran out and NaN was left in B
 size_t solve_ctl_bytes();
-void launch_solve(const Tiles &T, double *B, int64_t ldb, int nrhs, int *ctl, double *mail, hipStream_t st);
+void launch_solve(const Tiles &T, double *B, int64_t ldb, int nrhs, int *ctl, double *mail, int *late, hipStream_t st);
 
 // ---- sample (k_apply.hip)
 void launch_normal_draws(uint64_t seed, int64_t count, float *z, uint32_t *raw, hipStream_t st);

@@ -92,10 +92,11 @@ struct mpchol_handle {
     std::vector<uint8_t> convert_col;  // per column: some panel tile needs the conversion
     int32_t *d_all_items = nullptr;  // every lower tile, for the residual
     size_t items_cap = 0;
-    // pinned staging: 64 bytes of scalars (factor info, logdet), the norms, the
-    // table of d_tscale, and up to PIN_ITEMS bytes of schedule
+    // pinned staging: 64 bytes of scalars (factor info, logdet, the solves' word), the
+    // norms, the table of d_tscale, and up to PIN_ITEMS bytes of schedule
     static constexpr size_t PIN_ITEMS = 256 << 10;
     char *pin = nullptr;
+    int *late() const { return (int *)(pin + 16); }  // set by a solve whose wait ran out
     double *pin_norms() const { return (double *)(pin + 64); }
     char *pin_table() const { return pin + 64 + (size_t)nt * nt * 16; }
     char *pin_items() const { return pin_table() + ((size_t)nt * nt * 6 + 63) / 64 * 64; }
@@ -362,6 +363,7 @@ int mpchol_create(mpchol_t *hp, int64_t n, int32_t tile, const mpchol_opts *o)
         h->pin = nullptr;
         rc = MPCHOL_ENOMEM;
     }
+    if (h->pin) std::memset(h->pin, 0, 64);
     if (rc == MPCHOL_OK) H(hipStreamCreateWithFlags(&h->st2, hipStreamNonBlocking), "hipStreamCreateWithFlags");
     if (rc == MPCHOL_OK) H(hipEventCreateWithFlags(&h->ev_next, hipEventDisableTiming), "hipEventCreateWithFlags");
     if (rc == MPCHOL_OK) H(hipEventCreateWithFlags(&h->ev_panel, hipEventDisableTiming), "hipEventCreateWithFlags");
@@ -1011,6 +1013,16 @@ extern "C" int mpchol_factor(mpchol_t h, int64_t *info)
     return rc;
 }
 
+// A solve only enqueues; one whose wait ran out is reported, once, by the next call
+// on the factor that has synchronized the stream.
+static int late_solve(mpchol_handle *h)
+{
+    if (!__atomic_exchange_n(h->late(), 0, __ATOMIC_RELAXED)) return MPCHOL_OK;
+    snprintf(g_last_error, sizeof(g_last_error),
+             "mpchol_solve: workgroups of an earlier solve stopped waiting; its right-hand sides hold NaN");
+    return MPCHOL_EHIP;
+}
+
 extern "C" int mpchol_logdet(mpchol_t h, double *out)
 {
     if (!h || !out) return MPCHOL_EINVAL;
@@ -1021,7 +1033,7 @@ extern "C" int mpchol_logdet(mpchol_t h, double *out)
     HIPCHK(hipStreamSynchronize(h->st));
     HIPCHK(hipGetLastError());
     std::memcpy(out, h->pin + 8, 8);
-    return MPCHOL_OK;
+    return late_solve(h);
 }
 
 extern "C" int mpchol_get_factor(mpchol_t h, double *L, int64_t ldl)
@@ -1041,7 +1053,7 @@ extern "C" int mpchol_get_tile_scales(mpchol_t h, int32_t *t)
     HIPCHK(hipSetDevice(h->dev));
     HIPCHK(hipMemcpyAsync(t, h->d_tscale, (size_t)h->nt * h->nt * 4, hipMemcpyDeviceToHost, h->st));
     HIPCHK(hipStreamSynchronize(h->st));
-    return MPCHOL_OK;
+    return late_solve(h);
 }
 
 static int residual_of(mpchol_handle *h, const Source &S, double total_fro, double *berr, double *tile_res2)
@@ -1109,7 +1121,8 @@ extern "C" int mpchol_backward_error_estimate(mpchol_t h, int32_t sets, uint64_t
     if (!h || !est || sets <= 0) return MPCHOL_EINVAL;
     if (h->state != S_FACTORED) return MPCHOL_EORDER;
     HIPCHK(hipSetDevice(h->dev));
-    return estimate(h, sets, seed, est);
+    const int rc = estimate(h, sets, seed, est);
+    return rc ? rc : late_solve(h);
 }
 
 extern "C" int mpchol_backward_error(mpchol_t h, double *berr, double *tile_res2)
@@ -1117,7 +1130,8 @@ extern "C" int mpchol_backward_error(mpchol_t h, double *berr, double *tile_res2
     if (!h || !berr) return MPCHOL_EINVAL;
     if (h->state != S_FACTORED) return MPCHOL_EORDER;
     HIPCHK(hipSetDevice(h->dev));
-    return residual(h, berr, tile_res2);
+    const int rc = residual(h, berr, tile_res2);
+    return rc ? rc : late_solve(h);
 }
 
 extern "C" int mpchol_backward_error_matrix(mpchol_t h, const double *A, int64_t lda, int32_t on_device, double *berr,
@@ -1152,7 +1166,7 @@ extern "C" int mpchol_backward_error_matrix(mpchol_t h, const double *A, int64_t
     }
     if (!rc) rc = (tot > 0.0) ? residual_of(h, S, std::sqrt(tot), berr, tile_res2) : MPCHOL_EINVAL;
     if (tmp) (void)hipFree(tmp);
-    return rc;
+    return rc ? rc : late_solve(h);
 }
 
 extern "C" int mpchol_set_verify(mpchol_t h, int32_t mode, double eps)
@@ -1169,7 +1183,7 @@ extern "C" int mpchol_get_stats(mpchol_t h, mpchol_stats *s)
     HIPCHK(hipSetDevice(h->dev));
     HIPCHK(hipStreamSynchronize(h->st));
     *s = h->stats;
-    return MPCHOL_OK;
+    return late_solve(h);
 }
 
 extern "C" int mpchol_solve(mpchol_t h, int32_t nrhs, double *B, int64_t ldb)
@@ -1181,7 +1195,7 @@ extern "C" int mpchol_solve(mpchol_t h, int32_t nrhs, double *B, int64_t ldb)
     {
         // mailbox: the panel copies (48 KB per tile column of 128 at least, 4 KB a row wanted)
         std::lock_guard<std::mutex> lk(h->p64_mu);
-        launch_solve(h->tiles(), B, ldb, nrhs, h->d_solve, h->p64, h->st);
+        launch_solve(h->tiles(), B, ldb, nrhs, h->d_solve, h->p64, h->late(), h->st);
     }
     HIPCHK(hipEventRecord(h->ev[3], h->st));
     HIPCHK(hipGetLastError());
@@ -1217,7 +1231,7 @@ extern "C" int mpchol_sample(mpchol_t h, int32_t ndraws, uint64_t seed, float *Y
         }
     }
     if (hipStreamSynchronize(h->st) != hipSuccess || hipGetLastError() != hipSuccess) return MPCHOL_EHIP;
-    return MPCHOL_OK;
+    return late_solve(h);
 }
 
 extern "C" int mpchol_sample_noalloc(mpchol_t h, int32_t ndraws, uint64_t seed, float *Y, int64_t ldy)
