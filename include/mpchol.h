@@ -22,6 +22,11 @@
  *     host scalar (logdet, backward_error, get_stats, factor's info)
  *     synchronize that stream; the others only enqueue.
  *   - A handle is single-threaded: calls on one handle must not overlap.
+ *   - mpchol_solve, mpchol_sample_z, mpchol_get_factor and mpchol_normal_draws can
+ *     be recorded into HIP graphs on the handle's stream; replays, on any
+ *     stream, may overlap those calls and each other (two replays of one
+ *     recording may not), and must have ended before a call that loads,
+ *     factors or replaces the matrix.
  *   - Call order: create -> set_matrix | set_generator -> precision_map ->
  *     factor -> {logdet, solve, sample, backward_error, get_factor}.  A call
  *     made out of order returns MPCHOL_EORDER and changes nothing.
@@ -208,7 +213,10 @@ int mpchol_logdet(mpchol_t h, double *out);
 /* Overwrite device B (n x nrhs, ldb >= n, FP64) with Sigma^-1 B by forward
  * and backward tile substitution; diagonal blocks in FP64, off-diagonal
  * updates read each tile in its stored precision, exactly widened to FP64.
- * Only enqueues.  Workgroups wait for each other inside the kernels, 30 s at
+ * Only enqueues.  A solve recorded into a HIP graph allocates scratch of its own,
+ * kept until the handle is destroyed: 2 n doubles, or 32 n per 16 right-hand
+ * sides (256 at most), n rounded up to 128, and 64 KB (MPCHOL_ENOMEM without it).
+ * Workgroups wait for each other inside the kernels, 30 s at
  * most; where such a wait ends without its value (a GPU that was stopped
  * meanwhile), rows of B are left as NaN, and the next logdet, sample,
  * backward_error (_matrix, _estimate), get_tile_scales or get_stats call on the

@@ -572,7 +572,17 @@ constexpr int MAXCHUNK = 16;
 
 size_t solve_ctl_bytes() { return (size_t)2 * (32 + MAXCHUNK * NCOPY * STRIDE) * sizeof(int); }
 
-// mail: 2 * 16 * MAXCHUNK doubles per row of the tiles (4 KB) of scratch
+// Places of one direction's mailbox for nr right-hand sides of a launch.
+static int64_t solve_places(int64_t n, int nr)
+{
+    return (n + 127) / 128 * 128 * (nr == 1 ? 1 : NR * ((nr + NR - 1) / NR));
+}
+
+size_t solve_mail_bytes(int64_t n, int nrhs)
+{
+    return (size_t)solve_places(n, nrhs < MAXCHUNK * NR ? nrhs : MAXCHUNK * NR) * 2 * sizeof(double);
+}
+
 void launch_solve(const Tiles &T, double *B, int64_t ldb, int nrhs, int *ctl, double *mail, int *late, hipStream_t st)
 {
     const int words = (int)(solve_ctl_bytes() / sizeof(int));
@@ -582,7 +592,7 @@ void launch_solve(const Tiles &T, double *B, int64_t ldb, int nrhs, int *ctl, do
         const int nr = nrhs - j0 < MAXCHUNK * NR ? nrhs - j0 : MAXCHUNK * NR;
         double *Bj = B + (int64_t)j0 * ldb;
         const unsigned chunks = (unsigned)((nr + NR - 1) / NR), grid = nblk * chunks;
-        const int64_t places = (int64_t)nblk * 128 * (nr == 1 ? 1 : NR * chunks);  // of one direction
+        const int64_t places = solve_places(T.n, nr);
         int *bwd = ctl + words / 2;
         unsigned long long *mb = mf + places;
         const int64_t fill = (2 * places + 1023) / 1024;

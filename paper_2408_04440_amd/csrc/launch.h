@@ -97,10 +97,11 @@ int launch_cov_samples(const Tiles &T, const double *xi, int64_t ldxi, int64_t m
                        double *scratch, double *orig, hipStream_t st);
 int estimate_probes();
 
-// ---- solve (k_solve.hip): ctl = solve_ctl_bytes(), mail = 4 KB per row of the tiles of
-// scratch, cleared by the launch; *late (host memory that the device writes) becomes 1
+// ---- solve (k_solve.hip): ctl = solve_ctl_bytes(), mail = solve_mail_bytes() of scratch (4 KB
+// per row of the matrix, rounded up to 128 rows, at most), cleared by the launch; *late (host memory that the device writes) becomes 1
 // where a wait ran out and NaN was left in B
 size_t solve_ctl_bytes();
+size_t solve_mail_bytes(int64_t n, int nrhs);
 void launch_solve(const Tiles &T, double *B, int64_t ldb, int nrhs, int *ctl, double *mail, int *late, hipStream_t st);
 
 // ---- sample (k_apply.hip)

@@ -102,6 +102,7 @@ struct mpchol_handle {
     char *pin_items() const { return pin_table() + ((size_t)nt * nt * 6 + 63) / 64 * 64; }
     size_t pin_bytes() const { return 64 + (size_t)nt * nt * 22 + 64 + PIN_ITEMS; }
     std::mutex p64_mu;  // p64 as scratch between factorizations (draws, solves): one call's launches at a time
+    std::vector<char *> recorded;  // scratch of the solves recorded into graphs
     double *d_partial = nullptr, *d_tres2 = nullptr;
     // backward-error estimator scratch
     double *d_est = nullptr;
@@ -240,6 +241,8 @@ static void release(mpchol_handle *h)
     for (auto e : h->gev) (void)hipEventDestroy(e);
     if (h->ev_next) (void)hipEventDestroy(h->ev_next);
     if (h->ev_panel) (void)hipEventDestroy(h->ev_panel);
+    for (char *p : h->recorded)
+        if (p) (void)hipFree(p);
     if (h->st2) (void)hipStreamDestroy(h->st2);
 }
 
@@ -1191,13 +1194,33 @@ extern "C" int mpchol_solve(mpchol_t h, int32_t nrhs, double *B, int64_t ldb)
     if (!h || !B || nrhs <= 0 || ldb < h->n) return MPCHOL_EINVAL;
     if (h->state != S_FACTORED) return MPCHOL_EORDER;
     HIPCHK(hipSetDevice(h->dev));
-    HIPCHK(hipEventRecord(h->ev[2], h->st));
-    {
-        // mailbox: the panel copies (48 KB per tile column of 128 at least, 4 KB a row wanted)
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (h->st) HIPCHK(hipStreamIsCapturing(h->st, &cs));
+    if (cs == hipStreamCaptureStatusActive) {
+        // recorded: replays run on any stream, beside other calls and other replays, so
+        // this solve gets a mailbox and counts of its own, as long as the handle lives
+        char *own = nullptr;
+        const size_t mail = solve_mail_bytes(h->n, nrhs);
+        {
+            std::lock_guard<std::mutex> lk(h->p64_mu);
+            try {
+                h->recorded.push_back(nullptr);
+            } catch (const std::bad_alloc &) {
+                return MPCHOL_ENOMEM;
+            }
+            hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // an allocation is no part of the recording
+            HIPCHK(hipThreadExchangeStreamCaptureMode(&mode));
+            const int rc = dalloc(&own, mail + solve_ctl_bytes());
+            HIPCHK(hipThreadExchangeStreamCaptureMode(&mode));
+            if (rc) return rc;
+            h->recorded.back() = own;
+        }
+        launch_solve(h->tiles(), B, ldb, nrhs, (int *)(own + mail), (double *)own, h->late(), h->st);
+    } else {
+        // mailbox: the panel copies, 48 b >= 6 KB per row of the tiles where 4 KB are wanted
         std::lock_guard<std::mutex> lk(h->p64_mu);
         launch_solve(h->tiles(), B, ldb, nrhs, h->d_solve, h->p64, h->late(), h->st);
     }
-    HIPCHK(hipEventRecord(h->ev[3], h->st));
     HIPCHK(hipGetLastError());
     return MPCHOL_OK;
 }

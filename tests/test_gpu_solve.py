@@ -103,3 +103,54 @@ def test_solve_hands_on_any_nan():
         mod.mpchol_destroy(h)
     assert torch.equal(B[[0, 2, 4]], clean[[0, 2, 4]])
     assert torch.isnan(B[1, 0]) and torch.isnan(B[3, 130])
+
+
+def _int_handle(mod, n, tile, stream=None):
+    S = synth.int_lower(n, 11) / (1.0 + np.arange(n))[None, :] + 3.0 * np.eye(n)
+    h = mod.mpchol_create(n, tile, stream=stream)
+    mod.mpchol_set_matrix(h, S @ S.T)
+    mod.mpchol_precision_map(h, mod.RULE_FP64)
+    assert mod.mpchol_factor(h) == 0
+    return h
+
+
+@pytest.mark.parametrize("n,tile,nrhs", [(3600, 256, (1, 3)), (2000, 128, (17, 16))])
+def test_recorded_solves_replay_side_by_side(n, tile, nrhs):
+    """Two solves recorded into graphs, replayed on streams of their own beside
+    each other and beside the handle's own draws and solves: every result is the
+    one that the call gives alone, bit for bit, in every round."""
+    torch = torch_cuda()
+    mod = M()
+    home, s1, s2 = (torch.cuda.Stream() for _ in range(3))
+    h = _int_handle(mod, n, tile, stream=home)
+    try:
+        rhs = [torch.tensor(np.ascontiguousarray(synth.rhs(n, k + i).T[i:]), device="cuda") for i, k in enumerate((*nrhs, 2))]
+        want = [b.clone() for b in rhs]
+        Y, Yw = (torch.zeros((64, n), device="cuda") for _ in range(2))
+        torch.cuda.synchronize()
+        for b in want:
+            mod.mpchol_solve(h, b.T, n)
+        mod.mpchol_sample(h, 64, 5, Yw.T, n)
+        B = [b.clone() for b in rhs]
+        graphs = []
+        for b in B[:2]:
+            torch.cuda.synchronize()
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g, stream=home):
+                mod.mpchol_solve(h, b.T, n)
+            graphs.append(g)
+        for _ in range(8):
+            for b, r in zip(B, rhs):
+                b.copy_(r)
+            Y.zero_()
+            torch.cuda.synchronize()
+            for g, s in zip(graphs, (s1, s2)):
+                with torch.cuda.stream(s):
+                    g.replay()
+            mod.mpchol_solve(h, B[2].T, n)
+            mod.mpchol_sample(h, 64, 5, Y.T, n)
+            torch.cuda.synchronize()
+            assert all(torch.equal(b, w) for b, w in zip(B, want)) and torch.equal(Y, Yw)
+        assert np.isfinite(mod.mpchol_logdet(h))
+    finally:
+        mod.mpchol_destroy(h)
