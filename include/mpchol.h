@@ -21,7 +21,10 @@
  *   - All device work is ordered on the handle's stream.  Calls that return a
  *     host scalar (logdet, backward_error, get_stats, factor's info)
  *     synchronize that stream; the others only enqueue.
- *   - A handle is single-threaded: calls on one handle must not overlap.
+ *   - Calls on one handle must not overlap, except those that only read the
+ *     factor and return nothing to the host: mpchol_solve, mpchol_sample,
+ *     mpchol_sample_z, mpchol_get_factor and mpchol_normal_draws may be made by
+ *     several threads at once.
  *   - mpchol_solve, mpchol_sample_z, mpchol_get_factor and mpchol_normal_draws can
  *     be recorded into HIP graphs on the handle's stream; replays, on any
  *     stream, may overlap those calls and each other (two replays of one

@@ -101,7 +101,11 @@ struct mpchol_handle {
     char *pin_table() const { return pin + 64 + (size_t)nt * nt * 16; }
     char *pin_items() const { return pin_table() + ((size_t)nt * nt * 6 + 63) / 64 * 64; }
     size_t pin_bytes() const { return 64 + (size_t)nt * nt * 22 + 64 + PIN_ITEMS; }
-    std::mutex p64_mu;  // p64 as scratch between factorizations (draws, solves): one call's launches at a time
+    // p64 as scratch between factorizations (draws, solves): one call's launches at a
+    // time, and, where every thread has a stream of its own behind the handle's
+    // (hipStreamPerThread), each call behind the last one's
+    std::mutex p64_mu;
+    hipEvent_t ev_p64 = nullptr;
     std::vector<char *> recorded;  // scratch of the solves recorded into graphs
     double *d_partial = nullptr, *d_tres2 = nullptr;
     // backward-error estimator scratch
@@ -241,6 +245,7 @@ static void release(mpchol_handle *h)
     for (auto e : h->gev) (void)hipEventDestroy(e);
     if (h->ev_next) (void)hipEventDestroy(h->ev_next);
     if (h->ev_panel) (void)hipEventDestroy(h->ev_panel);
+    if (h->ev_p64) (void)hipEventDestroy(h->ev_p64);
     for (char *p : h->recorded)
         if (p) (void)hipFree(p);
     if (h->st2) (void)hipStreamDestroy(h->st2);
@@ -370,6 +375,7 @@ int mpchol_create(mpchol_t *hp, int64_t n, int32_t tile, const mpchol_opts *o)
     if (rc == MPCHOL_OK) H(hipStreamCreateWithFlags(&h->st2, hipStreamNonBlocking), "hipStreamCreateWithFlags");
     if (rc == MPCHOL_OK) H(hipEventCreateWithFlags(&h->ev_next, hipEventDisableTiming), "hipEventCreateWithFlags");
     if (rc == MPCHOL_OK) H(hipEventCreateWithFlags(&h->ev_panel, hipEventDisableTiming), "hipEventCreateWithFlags");
+    if (rc == MPCHOL_OK) H(hipEventCreateWithFlags(&h->ev_p64, hipEventDisableTiming), "hipEventCreateWithFlags");
     if (rc == MPCHOL_OK && h->d_ozc) {
         OzakiConst kc;
         ozaki_const_init(&kc);
@@ -1189,6 +1195,16 @@ extern "C" int mpchol_get_stats(mpchol_t h, mpchol_stats *s)
     return late_solve(h);
 }
 
+// Launches of an eager call that uses p64 as scratch.
+template <typename Launch> static int with_p64(mpchol_handle *h, Launch launch)
+{
+    std::lock_guard<std::mutex> lk(h->p64_mu);
+    if (h->st == hipStreamPerThread) HIPCHK(hipStreamWaitEvent(h->st, h->ev_p64, 0));
+    launch();
+    if (h->st == hipStreamPerThread) HIPCHK(hipEventRecord(h->ev_p64, h->st));
+    return MPCHOL_OK;
+}
+
 extern "C" int mpchol_solve(mpchol_t h, int32_t nrhs, double *B, int64_t ldb)
 {
     if (!h || !B || nrhs <= 0 || ldb < h->n) return MPCHOL_EINVAL;
@@ -1218,8 +1234,10 @@ extern "C" int mpchol_solve(mpchol_t h, int32_t nrhs, double *B, int64_t ldb)
         launch_solve(h->tiles(), B, ldb, nrhs, (int *)(own + mail), (double *)own, h->late(), h->st);
     } else {
         // mailbox: the panel copies, 48 b >= 6 KB per row of the tiles where 4 KB are wanted
-        std::lock_guard<std::mutex> lk(h->p64_mu);
-        launch_solve(h->tiles(), B, ldb, nrhs, h->d_solve, h->p64, h->late(), h->st);
+        const int rc = with_p64(h, [&] {
+            launch_solve(h->tiles(), B, ldb, nrhs, h->d_solve, h->p64, h->late(), h->st);
+        });
+        if (rc) return rc;
     }
     HIPCHK(hipGetLastError());
     return MPCHOL_OK;
@@ -1243,8 +1261,7 @@ extern "C" int mpchol_sample(mpchol_t h, int32_t ndraws, uint64_t seed, float *Y
     // normals in the panel copies, which are free between factorizations, as many
     // draws at a time as they hold (over 1,500 for any tile size); all passes of a
     // call are enqueued together, so that calls from several threads cannot mix
-    {
-        std::lock_guard<std::mutex> lk(h->p64_mu);
+    const int rc = with_p64(h, [&] {
         float *Z = (float *)h->p64;
         const int64_t chunk = (int64_t)NSET * h->nt * h->b * h->b * 2 / h->n / 128 * 128;
         for (int64_t d0 = 0; d0 < ndraws; d0 += chunk) {
@@ -1252,7 +1269,8 @@ extern "C" int mpchol_sample(mpchol_t h, int32_t ndraws, uint64_t seed, float *Y
             launch_normal_columns(seed, h->n, d0, nd, Z, h->n, h->st);
             launch_lower_apply(h->tiles(), Z, h->n, Y + d0 * ldy, ldy, nd, h->st);
         }
-    }
+    });
+    if (rc) return rc;
     if (hipStreamSynchronize(h->st) != hipSuccess || hipGetLastError() != hipSuccess) return MPCHOL_EHIP;
     return late_solve(h);
 }

@@ -154,3 +154,33 @@ def test_recorded_solves_replay_side_by_side(n, tile, nrhs):
         assert np.isfinite(mod.mpchol_logdet(h))
     finally:
         mod.mpchol_destroy(h)
+
+
+def test_threads_with_streams_of_their_own():
+    """A handle on hipStreamPerThread: solves and draws of two threads run on two
+    streams; their shared scratch keeps them apart."""
+    import threading
+
+    torch = torch_cuda()
+    mod = M()
+    n, rounds = 3000, 12
+    h = _int_handle(mod, n, 128, stream=2)  # hipStreamPerThread
+    try:
+        b = torch.tensor(np.ascontiguousarray(synth.rhs(n, 5).T), device="cuda")
+        want, B = b.clone(), b.repeat(rounds, 1, 1)
+        Yw, Y = torch.zeros((128, n), device="cuda"), torch.zeros((rounds, 128, n), device="cuda")
+        torch.cuda.synchronize()
+        mod.mpchol_solve(h, want.T, n)
+        mod.mpchol_sample(h, 128, 5, Yw.T, n)
+        torch.cuda.synchronize()
+        # get_stats waits for the solves: the runtime does not, once their thread and its stream are gone
+        ts = [threading.Thread(target=lambda: [mod.mpchol_solve(h, B[i].T, n) for i in range(rounds)] + [mod.mpchol_get_stats(h)]),
+              threading.Thread(target=lambda: [mod.mpchol_sample(h, 128, 5, Y[i].T, n) for i in range(rounds)])]
+        for t in ts:
+            t.start()
+        for t in ts:
+            t.join()
+        torch.cuda.synchronize()
+    finally:
+        mod.mpchol_destroy(h)
+    assert all(torch.equal(B[i], want) and torch.equal(Y[i], Yw) for i in range(rounds))
