@@ -267,3 +267,32 @@ def test_maps_in_turn_on_one_handle(n, tile):
     finally:
         mod.mpchol_destroy(h)
     assert seen[0] == seen[2] and seen[1][1] == seen[0][1] and seen[1][2] <= seen[0][2]
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("n,tile,nd", [(600, 128, 1), (600, 128, 16), (600, 128, 17), (1100, 256, 64), (600, 128, 65),
+                                       (9000, 256, 1900)])
+def test_sample_z_block_shapes_in_every_class(n, tile, nd, bf16):
+    """The block shapes again with every class below the diagonal (16-bit as FP16
+    or BF16) and a factor of small integers, which all of them hold: the same
+    bound, n u of FP32 relative to |L| |z|."""
+    torch = torch_cuda()
+    mod = M()
+    nt = -(-n // tile)
+    um = np.asfortranarray(np.tril(((np.arange(nt)[:, None] + 2 * np.arange(nt)[None, :]) % 4).astype(np.uint8), -1))
+    assert set(um[np.tril_indices(nt, -1)]) == {0, 1, 2, 3}
+    L0 = torch.tensor(synth.int_lower(n, 9), device="cuda")
+    h = mod.mpchol_create(n, tile, lo16=mod.LO16_BF16 if bf16 else mod.LO16_F16)
+    try:
+        mod.mpchol_set_matrix(h, (L0 @ L0.T.contiguous()).T)
+        assert np.array_equal(mod.mpchol_precision_map(h, mod.RULE_USER, 1e-9, um), um)
+        assert mod.mpchol_factor(h) == 0
+        Z = torch.randn((nd, n), generator=torch.Generator("cuda").manual_seed(7), device="cuda")
+        Y = torch.full((nd, n), 7.0, device="cuda")
+        mod.mpchol_sample_z(h, Z.T, Y.T, n)
+        torch.cuda.synchronize()
+    finally:
+        mod.mpchol_destroy(h)
+    Zd = Z.double()
+    want, size = Zd @ L0.T.contiguous(), Zd.abs() @ L0.abs().T.contiguous()
+    assert torch.all((Y - want).abs() <= n * 2.0 ** -24 * size + 1e-30)
