@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace mpc {
 
 enum { P64 = 0, P32 = 1, P16 = 2, P8 = 3 };
@@ -15,6 +17,30 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
 // index of lower tile (I, J), I >= J, in the packed tile array
 __host__ __device__ inline int64_t tile_index(int I, int J) { return (int64_t)I * (I + 1) / 2 + J; }
+
+// ---------------------------------------------------------------- helpers
+// f(integral_constant<int, I>) for I = 0 .. N - 1 (a DPP control or a root is a constant).
+template <int I, int N, typename F> __device__ inline void static_for(F f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<I + 1, N>(f);
+    }
+}
+
+// All of this wave's global stores have completed.
+__device__ inline void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// The longest wait of a workgroup for another of its launch: 30 s of the 100 MHz counter.
+constexpr long long WAIT_TICKS = 3000000000ll;
+
+// x / d given r, 1 / d to at least half of its bits: one correction by the
+// exact remainder, which returns an exactly representable quotient exactly.
+__device__ inline double div_by(double x, double d, double r)
+{
+    const double q = x * r;
+    return fma(fma(-q, d, x), r, q);
+}
 
 // ---------------------------------------------------------------- formats
 // FP32 -> FP16 bits, round to nearest even (the IEEE conversion).
@@ -99,17 +125,6 @@ __device__ inline double decode_class(uint32_t bits, int q, int lo16, int t)
     if (q == P16) f = lo16 == LO16_BF16 ? bf16_to_f32((uint16_t)bits) : f16_to_f32((uint16_t)bits);
     else f = e4m3_to_f32((uint8_t)bits);
     return ldexp((double)f, -t);
-}
-
-// Element (r, c) of a stored tile (column-major, leading dimension b) widened to FP64.
-__device__ inline double load_stored(const void *tile, int cls, int lo16, int t, int64_t off)
-{
-    switch (cls) {
-    case P64: return ((const double *)tile)[off];
-    case P32: return (double)((const float *)tile)[off];
-    case P16: return decode_class(((const uint16_t *)tile)[off], P16, lo16, t);
-    default: return decode_class(((const uint8_t *)tile)[off], P8, lo16, t);
-    }
 }
 
 // Two consecutive stored values (element offset even) without a branch on the

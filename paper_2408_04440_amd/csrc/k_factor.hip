@@ -1,8 +1,6 @@
 // The factorization's tasks (Sec. V.A): POTRF of a diagonal tile, TRSM of the
 // panel below it, and the SYRK/GEMM trailing update grouped per precision
 // class, all for gfx950.
-#include <type_traits>
-
 #include "common.h"
 #include "gemm_core.h"
 #include "launch.h"
@@ -27,15 +25,6 @@ __device__ inline void wave_sync()
 template <int N> __device__ inline double row_bcast(double v)
 {
     return __longlong_as_double(__builtin_amdgcn_update_dpp(0ll, __double_as_longlong(v), 0x150 + N, 0xf, 0xf, true));
-}
-
-// f(integral_constant<int, I>) for I = 0 .. N - 1 (the DPP control is a constant).
-template <int I, int N, typename F> __device__ inline void static_for(F f)
-{
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for<I + 1, N>(f);
-    }
 }
 
 // t[j] -= m * (lane j of the row of 16's s) for j = C + 1 .. 15: one DPP
@@ -81,17 +70,6 @@ template <int C> __device__ inline void row_update(double (&t)[16], double s, do
     else if constexpr (C == 12) MPC_ROW_ASM(MPC_FROM_13);
     else if constexpr (C == 13) MPC_ROW_ASM(MPC_FROM_14);
     else if constexpr (C == 14) MPC_ROW_ASM(MPC_FROM_15);
-}
-
-// All of this wave's global stores have completed.
-__device__ inline void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
-// x / d given r, 1 / d to at least half of its bits: one correction by the
-// exact remainder, which returns an exactly representable quotient exactly.
-__device__ inline double div_by(double x, double d, double r)
-{
-    const double q = x * r;
-    return __builtin_fma(__builtin_fma(-q, d, x), r, q);
 }
 
 // A diagonal element d of L as the substitutions keep it: 0 in place of infinity
@@ -311,8 +289,6 @@ __device__ inline void block_potrf64(double *S, int wave, int lane, int64_t col0
 // counter in column order, and every block depends on blocks with earlier
 // tickets only, so the earliest workgroup can always finish.  A wait that lasts
 // longer than WAIT_TICKS sets *info to 0, which the host reports as an error.
-constexpr long long WAIT_TICKS = 3000000000ll;  // 30 s of the 100 MHz counter
-
 __device__ inline double ld_dev(const double *p)
 {
     return __longlong_as_double(

@@ -107,14 +107,6 @@ template <> struct Root<12> {
     static constexpr double s[12] = {0.0, 0.5, 0.8660254037844386, 1.0, 0.8660254037844386, 0.5, 0.0, -0.5, -0.8660254037844386, -1.0, -0.8660254037844386, -0.5};
 };
 
-template <int I, int N, typename F> __device__ inline void static_for(F f)
-{
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for<I + 1, N>(f);
-    }
-}
-
 // R-point DFT in place in registers: V[q] = sum_r v[r] e^{-2 pi i q r / R}.
 // Composite R = R1 R2: R2 transforms of length R1, the roots of R, R1 of length R2.
 template <int R> __device__ inline void dft(double2 (&v)[R]);

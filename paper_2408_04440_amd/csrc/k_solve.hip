@@ -28,8 +28,6 @@
 // leisure.  Workgroups that follow on the values alone can be done before the one
 // they got them from has raised the count, so it only ever goes up.  A wait that lasts longer than its limit leaves NaN in the rows it
 // could not solve, ends the launch and sets the caller's word.
-#include <type_traits>
-
 #include "common.h"
 #include "launch.h"
 
@@ -44,7 +42,6 @@ constexpr int LDX = NR + 1, LDD = HB + 1;
 constexpr int STEPS = HB / 4;            // K steps of four per block, elements per lane and block
 constexpr int NCOPY = 16, STRIDE = 32;   // copies of the finished count, one cache line each
 constexpr int CTL = 32 + NCOPY * STRIDE; // words per chunk of right-hand sides and direction
-constexpr long long WAIT_TICKS = 3000000000ll;  // 30 s of the 100 MHz counter
 constexpr int NEAR = 4;                  // blocks before its own that a workgroup polls for themselves
 constexpr unsigned long long EMPTY = 0x7FF85EED0BADF00Dull;  // a NaN that no stored solution value has
 
@@ -65,18 +62,6 @@ __device__ inline void st_mail(unsigned long long *p, double v)
     unsigned long long u = (unsigned long long)__double_as_longlong(v);
     if (u == EMPTY) u ^= 1;  // stays a NaN
     __hip_atomic_store(p, u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// all of this wave's global stores have completed
-__device__ inline void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
-// f(integral_constant<int, I>) for I = 0 .. N - 1 (the DPP control is a constant)
-template <int I, int N, typename F> __device__ inline void static_for(F f)
-{
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for<I + 1, N>(f);
-    }
 }
 
 // One column of the triangle: v[t][p] -= (lane JJ of the row of 16's v[S][p]) * l[t]
@@ -161,19 +146,13 @@ template <bool FWD, int P> __device__ inline void solve64(double (&v)[4][P], con
     });
 }
 
-// v / d with r = 1 / d at hand: the quotient corrected by its remainder, where
-// nothing in it can leave the range of normal numbers (both in_range).
+// Quotients by reciprocals (div_by) where nothing in them can leave the range of
+// normal numbers: dividend and divisor both in_range.
 __device__ inline bool in_range(double v)
 {
     const unsigned e = ((unsigned)((unsigned long long)__double_as_longlong(v) >> 52)) & 0x7FFu;
     return e - 523u < 1000u;  // 2^-500 <= |v| < 2^500
 }
-__device__ inline double div_by(double v, double d, double r)
-{
-    const double q = v * r;
-    return fma(fma(-q, d, v), r, q);
-}
-
 // a wait has run out, here or elsewhere in this direction
 __device__ inline bool out_of_time(const Ctl &c, long long t0)
 {
