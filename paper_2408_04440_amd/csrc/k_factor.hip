@@ -72,7 +72,7 @@ template <int C> __device__ inline void row_update(double (&t)[16], double s, do
     else if constexpr (C == 14) MPC_ROW_ASM(MPC_FROM_15);
 }
 
-// A diagonal element d of L as the substitutions keep it: 0 in place of infinity
+// A diagonal element d of L as the substitutions divide by it: 0 in place of infinity
 // (an infinite entry of the matrix).  With r = 1 / d = 0 div_by then gives 0, as
 // x / d does; with d itself its remainder would be 0 * infinity.
 __device__ inline double as_divisor(double d) { return d == __builtin_inf() ? 0.0 : d; }
@@ -135,19 +135,19 @@ __device__ inline void mma64(double4_t (&v)[4], const double *X, const double *Y
 }
 
 // Panel p of X = -acc L^-T for a wave's 16 rows: L the lower 64 x 64 block in
-// LDS (its columns 16 p .. 16 p + 15 are read), rl = 1 / L(16 p + gi, 16 p + gi),
+// LDS (its columns 16 p .. 16 p + 15 are read), d = L(16 p + gi, 16 p + gi) as
+// as_divisor gives it, rl = 1 / L(16 p + gi, 16 p + gi),
 // acc the negated 16 x 64 right-hand side, acc[0] the current 16 columns: the
 // later panels' sums move up by one, so that the four panels share one copy of
 // the code (a diagonal workgroup runs it once, and four copies cost more in
 // instruction fetches than the moves).  Every lane gathers its row of the panel
 // (the four lane groups hold the same rows) and substitutes column by column
-// against broadcasts of the diagonal block's rows from other lanes (the diagonal
-// as as_divisor gives it); the
+// against broadcasts of the diagonal block's rows from other lanes; the
 // panel's product with the rest of L goes to the later sums on the MFMA.
 // put(t, v): lane (gi, gg) delivers X(gi, 16 p + 4 t + gg).
 template <typename Put>
-__device__ inline void wave_trsm16(double4_t (&acc)[4], int p, const double *L, double rl, double *scratch, int gi,
-                                   int gg, Put put)
+__device__ inline void wave_trsm16(double4_t (&acc)[4], int p, const double *L, double d, double rl, double *scratch,
+                                   int gi, int gg, Put put)
 {
     const double *Lp = L + 16 * p * LD64 + 16 * p + gi;
     double x[16], ld[16];  // lane gi: its row, and row gi of the panel's 16 x 16 diagonal block
@@ -161,7 +161,7 @@ __device__ inline void wave_trsm16(double4_t (&acc)[4], int p, const double *L, 
     for (int c = 0; c < 16; ++c) x[c] = scratch[gi * 17 + c];
     static_for<0, 16>([&](auto C) {
         constexpr int c = C;
-        x[c] = div_by(x[c], row_bcast<c>(ld[c]), row_bcast<c>(rl));
+        x[c] = div_by(x[c], row_bcast<c>(d), row_bcast<c>(rl));
         row_update<c>(x, ld[c], x[c]);
     });
     double a[4];
@@ -412,11 +412,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
 #pragma unroll
             for (int q = 0; q < 4; ++q) l[q] = ld_dev((const double *)(pl + (16 * p + 4 * q) * cs + lin8));
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                Bs[(16 * p + wave + 4 * q) * LD64 + lane] = lane == 16 * p + wave + 4 * q ? as_divisor(l[q]) : l[q];
+            for (int q = 0; q < 4; ++q) Bs[(16 * p + wave + 4 * q) * LD64 + lane] = l[q];
             const double rl = 1.0 / d;
             __syncthreads();
-            wave_trsm16(acc1, p, Bs, rl, scratch[wave], gi, gg, [&](int t, double v) {
+            wave_trsm16(acc1, p, Bs, as_divisor(d), rl, scratch[wave], gi, gg, [&](int t, double v) {
                 st_dev((double *)(px + (16 * p + 4 * t) * cs + own8), v);
                 if (diag) A[(16 * p + 4 * t + gg) * LD64 + wave * 16 + gi] = v;
             });
@@ -482,7 +481,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void t
 {
     __builtin_amdgcn_s_setprio(3);  // the panel chain: issue ahead of update waves sharing the SIMD
     __shared__ double Ls[64 * LD64];
-    __shared__ double inv[64], scratch[4][16 * 17];
+    __shared__ double dia[64], inv[64], scratch[4][16 * 17];
     const int b = T.b, I = k + 1 + blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, gi = lane & 15, gg = lane >> 4;
     const bool wf32 = T.map[I + (int64_t)k * T.nt] != P64;
@@ -506,8 +505,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void t
     load_diag(0);
     for (int cb = 0; cb < b; cb += 64) {
 #pragma unroll
-        for (int q = 0; q < 16; ++q) Ls[(wave + 4 * q) * LD64 + lane] = lane == wave + 4 * q ? as_divisor(lv[q]) : lv[q];
-        if (wave == 0) inv[lane] = 1.0 / dv;
+        for (int q = 0; q < 16; ++q) Ls[(wave + 4 * q) * LD64 + lane] = lv[q];
+        if (wave == 0) {
+            dia[lane] = as_divisor(dv);
+            inv[lane] = 1.0 / dv;
+        }
         // right-hand side, read ahead of the products
         double4_t w[4], acc[4];
         if (wf32) {
@@ -567,7 +569,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void t
         if (cb + 64 < b) load_diag(cb + 64);
 #pragma unroll 1
         for (int p = 0; p < 4; ++p)
-            wave_trsm16(acc, p, Ls, inv[16 * p + gi], scratch[wave], gi, gg, [&](int t, double v) {
+            wave_trsm16(acc, p, Ls, dia[16 * p + gi], inv[16 * p + gi], scratch[wave], gi, gg, [&](int t, double v) {
                 const int c = cb + 16 * p + 4 * t;
                 *(double *)(X + c * cs + own8) = v;
                 if (direct) *(double *)(W + c * cs + own8) = v;
