@@ -91,21 +91,15 @@ __device__ inline void sqrt_rcp(double d, double &s, double &r)
     r = h + h;
 }
 
-// v[ct] += X(rows 16w.., k) Y(rows 16ct.., k)^T over columns k0 .. k1 - 1 (a
-// multiple of 16) of the LDS blocks, summed from zero and added once: a v that
-// starts at a block of the matrix is then rounded at its size once per call, not
-// once per product, and the error does not grow with the tile (1024: 6 to 2 u).
-// Operands swapped: a lane holds row gi of its wave's 16 and columns gg + 4v of
-// each 16-column tile.
-__device__ inline void mma64(double4_t (&v)[4], const double *X, const double *Y, int wave, int gi, int gg,
+// acc[ct] += X(rows 16w.., k) Y(rows 16ct.., k)^T over columns k0 .. k1 - 1 (a
+// multiple of 16) of the LDS blocks.  Operands swapped: a lane holds row gi of its wave's 16 and
+// columns gg + 4v of each 16-column tile.
+__device__ inline void mma64(double4_t (&acc)[4], const double *X, const double *Y, int wave, int gi, int gg,
                              int k0 = 0, int k1 = 64)
 {
     struct Ops {
         double x[2], y[2][4];
     } u, w;
-    double4_t acc[4];
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct) acc[ct] = (double4_t){0.0, 0.0, 0.0, 0.0};
     auto load = [&](int k, Ops &o) {
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
@@ -130,8 +124,20 @@ __device__ inline void mma64(double4_t (&v)[4], const double *X, const double *Y
         if (k + 16 < k1) load(k + 16, u);
         mma(w);
     }
+}
+
+// v = a block of the matrix less products: those of 64 columns are summed from zero
+// and added once, so that v is rounded at its size once per 64 columns, not once per
+// product, and the error does not grow with the tile (1024: 6 to 2 u).
+__device__ inline void zero64(double4_t (&v)[4])
+{
 #pragma unroll
-    for (int ct = 0; ct < 4; ++ct) v[ct] += acc[ct];
+    for (int ct = 0; ct < 4; ++ct) v[ct] = (double4_t){0.0, 0.0, 0.0, 0.0};
+}
+__device__ inline void add64(double4_t (&v)[4], const double4_t (&sum)[4])
+{
+#pragma unroll
+    for (int ct = 0; ct < 4; ++ct) v[ct] += sum[ct];
 }
 
 // Panel p of X = -acc L^-T for a wave's 16 rows: L the lower 64 x 64 block in
@@ -174,7 +180,7 @@ __device__ inline void wave_trsm16(double4_t (&acc)[4], int p, const double *L, 
     }
 #pragma unroll
     for (int r = 1; r < 4; ++r) {
-        double4_t sum = {0.0, 0.0, 0.0, 0.0};  // added once, as in mma64
+        double4_t sum = {0.0, 0.0, 0.0, 0.0};  // added once, as in add64
         if (p + r < 4) {
 #pragma unroll
             for (int t = 0; t < 4; ++t)
@@ -347,9 +353,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
     auto at = [&](int r, int c) { return (char *)tile + (int64_t)(64 * r) * 8 + 64 * c * cs; };
     const uint32_t own8 = (wave * 16 + gi + gg * b) * 8, lin8 = (lane + wave * b) * 8;
     // the blocks themselves start the sums, negated; the mirrored block above the diagonal becomes zero
-    double4_t acc1[4], acc2[4];
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct) acc1[ct] = acc2[ct] = (double4_t){0.0, 0.0, 0.0, 0.0};
+    double4_t acc1[4], acc2[4], sum[4];
+    zero64(acc1);
+    zero64(acc2);
     if (ca >= 0) {
 #pragma unroll
         for (int q = 0; q < 16; ++q) acc1[q / 4][q % 4] = -*(const double *)(at(i, ca) + 4 * q * cs + own8);
@@ -394,14 +400,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
         }
         __syncthreads();
         if (j + 1 < ca && j + 1 < have) load(j + 1);
-        mma64(acc1, A, Bs, wave, gi, gg);
-        if (diag) mma64(acc2, A, A, wave, gi, gg);
+        zero64(sum);
+        mma64(sum, A, Bs, wave, gi, gg);
+        add64(acc1, sum);
+        if (diag) {
+            zero64(sum);
+            mma64(sum, A, A, wave, gi, gg);
+            add64(acc2, sum);
+        }
     }
 
     if (ca >= 0) {
         const char *pl = at(ca, ca);
         char *px = at(i, ca);
         __syncthreads();  // the last products have been read from LDS
+        zero64(sum);
 #pragma unroll 1
         for (int p = 0; p < 4; ++p) {  // panel p of L(ca, ca) into Bs, then this block's panel
             if (tid == 0) s_word = wait_prog(prog, ca, 4 * ca + p + 1, ca, 4 * ca + p + 1, info);
@@ -421,9 +434,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
             });
             if (diag) {
                 __syncthreads();
-                mma64(acc2, A, A, wave, gi, gg, 16 * p, 16 * p + 16);
+                mma64(sum, A, A, wave, gi, gg, 16 * p, 16 * p + 16);
             }
         }
+        if (diag) add64(acc2, sum);
         stores_done();
         __syncthreads();
         if (tid == 0) __hip_atomic_store(prog + i, 4 * ca + 4, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
