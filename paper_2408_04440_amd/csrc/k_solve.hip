@@ -12,9 +12,9 @@
 // result to the others through a mailbox.  The factor's elements go from memory
 // to registers, each used once, the next block in flight while the current one
 // is waited for, so the streaming hides behind the chain or the chain behind it
-// (N = 16,384: 16 right-hand sides 2.16 -> 1.78 ms, 6.9 us per 128 rows and
+// (N = 16,384: 16 right-hand sides 2.16 -> 1.80 ms, 7.0 us per 128 rows and
 // direction, where counts handed the blocks on and eight waves broadcast each
-// solved value; mixed classes 2.42 -> 1.76; one right-hand side 1.50 -> 1.32).
+// solved value; mixed classes 2.42 -> 1.80; one right-hand side 1.50 -> 1.38).
 //
 // Order and progress: a workgroup takes its place in the chain from a ticket
 // counter, so it only ever waits for workgroups that started before it: however
@@ -255,24 +255,77 @@ __device__ inline void widen(const Raw<PAIR> &r, int gi, int gg, int lo16, int t
     }
 }
 
-// The sums of a lane.  ONE (a single right-hand side): row gi of the wave's 16,
-// the terms of K group gg; else MFMA accumulators, rows gg + 4v, right-hand side
-// gi: two of them in turn, so that a wave ahead in priority always has a product
-// to issue and is not held up by the other wave on its SIMD.
-template <bool ONE> struct Sum {
-    double4_t v, w;
-    __device__ inline void zero() { v = w = (double4_t){0.0, 0.0, 0.0, 0.0}; }
-    __device__ inline void add(int s, double a, double x)
+// a and b with b's first and a's second 32 lanes exchanged, or b's even and a's odd rows of 16.
+template <int LANES> __device__ inline void swap_lanes(double &a, double &b)
+{
+    const unsigned long long u = (unsigned long long)__double_as_longlong(a), v = (unsigned long long)__double_as_longlong(b);
+    const auto lo = LANES == 32 ? __builtin_amdgcn_permlane32_swap((unsigned)u, (unsigned)v, false, false)
+                                : __builtin_amdgcn_permlane16_swap((unsigned)u, (unsigned)v, false, false);
+    const auto hi = LANES == 32 ? __builtin_amdgcn_permlane32_swap((unsigned)(u >> 32), (unsigned)(v >> 32), false, false)
+                                : __builtin_amdgcn_permlane16_swap((unsigned)(u >> 32), (unsigned)(v >> 32), false, false);
+    a = __longlong_as_double((long long)((unsigned long long)hi[0] << 32 | lo[0]));
+    b = __longlong_as_double((long long)((unsigned long long)hi[1] << 32 | lo[1]));
+}
+template <int LANES> __device__ inline double swap_add(double a, double b)
+{
+    swap_lanes<LANES>(a, b);
+    return a + b;
+}
+// over the four rows of 16 lanes
+__device__ inline double sum_rows(double v)
+{
+    v = swap_add<32>(v, v);
+    return swap_add<16>(v, v);
+}
+
+// The running value of a lane: products less right-hand side.  ONE (a single
+// right-hand side): row gi of the wave's 16, the same in every row of lanes; else MFMA
+// accumulators, rows gg + 4v, right-hand side gi.  The products of a block of 64 are
+// summed from zero, in runs of neighbours, and added once: the terms of such a sum
+// nearly cancel from one to the next (a solve undoes what the correlation of
+// neighbours did), and sums over every other term, or every other four, lose what
+// cancels (N = 1,444, correlation length 20: 9 times the error, and 2% of the time
+// saved, 5% with one right-hand side).
+template <bool FWD, bool ONE> struct Sum {
+    double4_t t;
+    // column (row) of the block that a[s] belongs to
+    static __device__ inline int place(int s, int gg)
     {
-        if (ONE) {
-            if (s & 1) w[0] += a * x;
-            else v[0] += a * x;
+        if (ONE) return FWD ? 16 * gg + s : 8 * (s >> 1) + 2 * gg + (s & 1);
+        return FWD ? 4 * s + gg : 8 * (s >> 1) + 4 * (s & 1) + 2 * (gg & 1) + (gg >> 1);
+    }
+    // a: the lane's elements as they were read
+    __device__ inline void add(double (&a)[STEPS], const double (&x)[STEPS])
+    {
+        if constexpr (!ONE) {
+            double4_t v = {0.0, 0.0, 0.0, 0.0}, w = v;  // the halves of the block, in turn: always a product to issue
+            if constexpr (!FWD) {  // pairs of rows: four neighbours to a product
+#pragma unroll
+                for (int s = 0; s < STEPS; s += 2) swap_lanes<32>(a[s], a[s + 1]);
+            }
+#pragma unroll
+            for (int s = 0; s < STEPS / 2; ++s) {
+                v = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], x[s], v, 0, 0, 0);
+                w = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s + STEPS / 2], x[s + STEPS / 2], w, 0, 0, 0);
+            }
+            t += v + w;
+        } else if constexpr (FWD) {
+            double v = 0.0, w = 0.0;
+#pragma unroll
+            for (int s = 0; s < STEPS / 2; ++s) {
+                v += a[s] * x[s];
+                w += a[s + STEPS / 2] * x[s + STEPS / 2];
+            }
+            t[0] += sum_rows(v + w);
         } else {
-            if (s & 1) w = __builtin_amdgcn_mfma_f64_16x16x4f64(a, x, w, 0, 0, 0);
-            else v = __builtin_amdgcn_mfma_f64_16x16x4f64(a, x, v, 0, 0, 0);
+            double p[STEPS / 2];  // pairs; then runs of eight rows, a different one in each row of lanes
+#pragma unroll
+            for (int j = 0; j < STEPS / 2; ++j) p[j] = a[2 * j] * x[2 * j] + a[2 * j + 1] * x[2 * j + 1];
+            const double q0 = swap_add<16>(swap_add<32>(p[0], p[1]), swap_add<32>(p[2], p[3]));
+            const double q1 = swap_add<16>(swap_add<32>(p[4], p[5]), swap_add<32>(p[6], p[7]));
+            t[0] += sum_rows(q0 + q1);
         }
     }
-    __device__ inline double sum(int i) const { return v[i] + w[i]; }
 };
 
 }  // namespace
@@ -323,12 +376,12 @@ __global__ __launch_bounds__(NTH) void solve_kernel(Tiles T, double *B, int64_t 
     unsigned long long *mc = mail + (int64_t)chunk * 2 * nblk * PER;
 
     // own right-hand side, diagonal blocks and the block between them, all read ahead of the chain
-    double rb[4];
+    Sum<FWD, ONE> acc;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const int r = ONE ? gi : gg + 4 * v, q = ONE ? 0 : gi;
         const int64_t i = row0 + wave * 16 + r;
-        rb[v] = (i < T.n && q < nr && (!ONE || v == 0)) ? Bc[i + (int64_t)q * ldb] : 0.0;
+        acc.t[v] = (i < T.n && q < nr && (!ONE || v == 0)) ? -Bc[i + (int64_t)q * ldb] : 0.0;
     }
     const TileRef D = tile_ref(T, I, I);
     const double *Dd = (const double *)D.p + lr + (int64_t)lr * b;
@@ -350,8 +403,6 @@ __global__ __launch_bounds__(NTH) void solve_kernel(Tiles T, double *B, int64_t 
     const bool second = FWD ? wave >= WAVES / 2 : wave < WAVES / 2;
     // the rows solved first go first: what they wait for is on the chain
     if (!second) __builtin_amdgcn_s_setprio(2);
-    Sum<ONE> acc;
-    acc.zero();
     const int first = FWD ? 0 : 2 * nblk - 1, count = 2 * seq;  // blocks before this workgroup's own
     // the tile holding step k's block; its class is read once per tile, as a read of
     // it waits for the pieces sent for before
@@ -369,7 +420,7 @@ __global__ __launch_bounds__(NTH) void solve_kernel(Tiles T, double *B, int64_t 
     auto fetch_step = [&](int k, const TileRef &R, Raw<!FWD> &r) {
         const int64_t q0 = (int64_t)(FWD ? k : first - k) * HB;
         const int lq = (int)(q0 % b);
-        if constexpr (FWD) fetch(R, lr + wave * 16 + gi + (lq + gg) * b, 4 * b, r);
+        if constexpr (FWD) fetch(R, lr + wave * 16 + gi + (lq + (ONE ? 16 : 1) * gg) * b, (ONE ? 1 : 4) * b, r);
         else fetch(R, lq + 2 * gg + (lr + wave * 16 + gi) * b, r);
     };
     auto product = [&](const Raw<!FWD> &r, const TileRef &R, const double *x) {
@@ -377,7 +428,7 @@ __global__ __launch_bounds__(NTH) void solve_kernel(Tiles T, double *B, int64_t 
         double a[STEPS], xk[STEPS];
 #pragma unroll
         for (int s = 0; s < STEPS; ++s) {
-            const int k = FWD ? 4 * s + gg : 8 * (s >> 1) + 2 * gg + (s & 1);
+            const int k = Sum<FWD, ONE>::place(s, gg);
             xk[s] = x[ONE ? k : k * LDX + gi];
         }
         switch (R.cls) {
@@ -386,8 +437,7 @@ __global__ __launch_bounds__(NTH) void solve_kernel(Tiles T, double *B, int64_t 
         case P16: widen<P16>(r, gi, gg, T.lo16, R.t, a); break;
         default: widen<P8>(r, gi, gg, T.lo16, R.t, a); break;
         }
-#pragma unroll
-        for (int s = 0; s < STEPS; ++s) acc.add(s, a[s], xk[s]);
+        acc.add(a, xk);
     };
     auto give_up = [&]() {
         for (int e = tid; e < 128 * nr; e += NTH) {
@@ -453,7 +503,7 @@ __global__ __launch_bounds__(NTH) void solve_kernel(Tiles T, double *B, int64_t 
     // the block between the halves, in flight while the first is solved
     Raw<!FWD> mid;
     if constexpr (FWD) {
-        if (second) fetch(D, lr + wave * 16 + gi + (lr + gg) * b, 4 * b, mid);
+        if (second) fetch(D, lr + wave * 16 + gi + (lr + (ONE ? 16 : 1) * gg) * b, (ONE ? 1 : 4) * b, mid);
     } else {
         if (second) fetch(D, lr + HB + 2 * gg + (lr + wave * 16 + gi) * b, mid);
     }
@@ -466,13 +516,10 @@ __global__ __launch_bounds__(NTH) void solve_kernel(Tiles T, double *B, int64_t 
         if (mine) {
             const int w = wave - (FWD ? half : 1 - half) * (WAVES / 2);
             if (ONE) {
-                double s = acc.sum(0);
-                s += __shfl_xor(s, 16);
-                s += __shfl_xor(s, 32);
-                if (gg == 0) rs[0][w * 16 + gi] = rb[0] - s;
+                if (gg == 0) rs[0][w * 16 + gi] = 0.0 - acc.t[0];
             } else {
 #pragma unroll
-                for (int v = 0; v < 4; ++v) rs[gi][w * 16 + gg + 4 * v] = rb[v] - acc.sum(v);
+                for (int v = 0; v < 4; ++v) rs[gi][w * 16 + gg + 4 * v] = 0.0 - acc.t[v];
             }
         }
         __syncthreads();

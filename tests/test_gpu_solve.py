@@ -184,3 +184,44 @@ def test_threads_with_streams_of_their_own():
     finally:
         mod.mpchol_destroy(h)
     assert all(torch.equal(B[i], want) and torch.equal(Y[i], Yw) for i in range(rounds))
+
+
+def _substitute(L, B):
+    """L L^T X = B column by column, in the type of B: terms taken in their natural order."""
+    X = B.copy()
+    for k in range(len(L)):
+        X[k] /= L[k, k]
+        X[k + 1:] -= L[k + 1:, k:k + 1] * X[k:k + 1]
+    for k in range(len(L) - 1, -1, -1):
+        X[k] /= L[k, k]
+        X[:k] -= L[k, :k][:, None] * X[k:k + 1]
+    return X
+
+
+@pytest.mark.parametrize("rho", [2.0, 20.0])
+@pytest.mark.parametrize("band,tile,nrhs", [(38, 128, 16), (38, 128, 1), (38, 512, 16), (30, 256, 2)])
+def test_solve_error_of_neighbours_that_cancel(band, tile, nrhs, rho):
+    """Neighbouring terms of a solve with a correlation nearly cancel, so the order
+    of the sums decides the error: at most twice that of substitution in natural
+    order in FP64 (two draws of rounding errors differ by less), both against long
+    double with the GPU's own factor.  Sums over every other term take 4 to 6 times at
+    a correlation length of 20."""
+    torch = torch_cuda()
+    mod = M()
+    n = band * band
+    h = mod.mpchol_create(n, tile)
+    try:
+        mod.mpchol_set_generator(h, *synth.workload(band), rho, 1e-8)
+        mod.mpchol_precision_map(h, mod.RULE_FP64)
+        assert mod.mpchol_factor(h) == 0
+        L = factor_dense(h, n)
+        B = synth.rhs(n, nrhs)
+        Bt = torch.tensor(np.ascontiguousarray(B.T), device="cuda")
+        mod.mpchol_solve(h, Bt.T, n)
+        X = Bt.cpu().numpy().T
+    finally:
+        mod.mpchol_destroy(h)
+    exact = _substitute(L.astype(np.longdouble), B.astype(np.longdouble))
+    err, ref = (float(np.sqrt((((v - exact) / np.abs(exact).max()) ** 2).sum())) for v in (X, _substitute(L, B)))
+    log(f"  n={n} tile={tile} nrhs={nrhs} rho={rho}: {err:.2e}, in natural order {ref:.2e}")
+    assert err <= 2.0 * ref
