@@ -153,7 +153,8 @@ void mpchol_default_opts(mpchol_opts *o);
  * of 128, 128..2048).  n need not be a multiple of tile: the last tile row and
  * column are padded with an identity block, which changes neither the factor
  * nor the log-determinant.  Allocates the tile storage (about
- * NT(NT+1)/2 * tile^2 * 8 bytes) and the panel buffers on o->device.
+ * NT(NT+1)/2 * tile^2 * 8 bytes) and the panel buffers on o->device, and
+ * 22 NT^2 bytes + 256 KB of pinned host memory.
  * o may be NULL (defaults).  On error *h is NULL. */
 int mpchol_create(mpchol_t *h, int64_t n, int32_t tile, const mpchol_opts *o);
 
@@ -181,9 +182,14 @@ int mpchol_set_generator(mpchol_t h, const double *sigma, const double *x, doubl
  * host memory (or device memory if on_device); e.g. scale = 1/(R(T-P)).
  * Computed on the GPU by a tall-skinny FP64 MFMA SYRK into the kept FP64
  * copy, which maps, factor and residuals then read as after set_matrix.  The
- * caller keeps ownership of Xi.  Temporary device memory: (NT*b) x
- * roundup(m, 16) doubles, plus n x m for host input.  Synchronizes; the
- * product's time goes to stats.t_samples_ms.  EINVAL for null pointers,
+ * caller keeps ownership of Xi.  Scratch: at most 1,023 blocks of 128 x 128
+ * doubles, and copies of the samples -- of the last, partial block of 128 rows and
+ * of the last, partial run of 32 samples; of all of them, padded to multiples of 128
+ * and 32, if Xi is not aligned to 16 bytes or ldxi is odd or above 2^25.  It lies in
+ * the tile storage (the factor is void from this call on) if it fits there, else in
+ * temporary device memory; a host Xi takes another ldxi x m doubles.  Synchronizes;
+ * the product's time goes to stats.t_samples_ms.  After MPCHOL_EHIP the handle has
+ * no matrix.  EINVAL for null pointers,
  * ldxi < n, m < 1, scale <= 0 or nugget < 0. */
 int mpchol_set_samples(mpchol_t h, const double *xi, int64_t ldxi, int64_t m, double scale, double nugget,
                        int32_t on_device);
@@ -268,7 +274,7 @@ int mpchol_backward_error(mpchol_t h, double *berr, double *tile_res2);
  * on_device, else host memory (copied to a temporary device buffer).  The
  * stored factor is exactly widened to FP64; FP64 accumulation; ||A||_F is
  * computed from A's lower part.  tile_res2 as in mpchol_backward_error.
- * Temporary device memory: 2 NT^2 doubles, plus the copy of a host A.
+ * Temporary device memory: the copy of a host A.
  * Synchronizes.  MPCHOL_EINVAL for null pointers, lda < n or A = 0. */
 int mpchol_backward_error_matrix(mpchol_t h, const double *A, int64_t lda, int32_t on_device, double *berr,
                                  double *tile_res2);

@@ -55,7 +55,7 @@ struct mpchol_handle {
     bool x_sorted = false;  // generator coordinates nondecreasing
     hipStream_t st2 = nullptr;           // the rest of a pair's update, beside the next pair's panel work
     hipEvent_t ev_next = nullptr, ev_panel = nullptr;
-    // panel copies, four sets (column mod 4: the pair being applied and the pair being factored)
+    // panel copies, NSET sets (column mod NSET)
     double *p64 = nullptr;
     float *p32 = nullptr;
     uint16_t *p32s = nullptr;  // three BF16 parts of the FP32 copies (lo32 = BF16x3)
@@ -64,7 +64,7 @@ struct mpchol_handle {
     uint8_t *p8x = nullptr;      // lo8 MX: E8M0 block scales of the FP8 copies
     unsigned long long *pmax = nullptr;
     int32_t *pscale = nullptr;
-    int8_t *poz = nullptr;       // lo64 INT8: residue planes of the FP64 copies, four sets
+    int8_t *poz = nullptr;       // lo64 INT8: residue planes of the FP64 copies, NSET sets
     int32_t *pexp = nullptr;     // lo64 INT8: their row exponents
     OzakiConst *d_ozc = nullptr; // lo64 INT8: moduli and reconstruction constants (device)
     // per-tile metadata
