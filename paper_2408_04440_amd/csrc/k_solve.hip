@@ -14,7 +14,7 @@
 // is waited for, so the streaming hides behind the chain or the chain behind it
 // (N = 16,384: 16 right-hand sides 2.16 -> 1.80 ms, 7.0 us per 128 rows and
 // direction, where counts handed the blocks on and eight waves broadcast each
-// solved value; mixed classes 2.42 -> 1.80; one right-hand side 1.50 -> 1.38).
+// solved value; mixed classes 2.42 -> 1.78; one right-hand side 1.50 -> 1.36).
 //
 // Order and progress: a workgroup takes its place in the chain from a ticket
 // counter, so it only ever waits for workgroups that started before it: however
@@ -284,8 +284,8 @@ __device__ inline double sum_rows(double v)
 // summed from zero, in runs of neighbours, and added once: the terms of such a sum
 // nearly cancel from one to the next (a solve undoes what the correlation of
 // neighbours did), and sums over every other term, or every other four, lose what
-// cancels (N = 1,444, correlation length 20: 9 times the error, and 2% of the time
-// saved, 5% with one right-hand side).
+// cancels (N = 1,444, correlation length 20: 9 times the error, and 1% of the time
+// saved, 3% with one right-hand side).
 template <bool FWD, bool ONE> struct Sum {
     double4_t t;
     // column (row) of the block that a[s] belongs to
@@ -431,8 +431,14 @@ __global__ __launch_bounds__(NTH) void solve_kernel(Tiles T, double *B, int64_t 
             const int k = Sum<FWD, ONE>::place(s, gg);
             xk[s] = x[ONE ? k : k * LDX + gi];
         }
+        // FP64 by itself: joined with the other classes its values are moved, and the
+        // move waits for the pieces sent for meanwhile as well
+        if (R.cls == P64) {
+            widen<P64>(r, gi, gg, T.lo16, R.t, a);
+            acc.add(a, xk);
+            return;
+        }
         switch (R.cls) {
-        case P64: widen<P64>(r, gi, gg, T.lo16, R.t, a); break;
         case P32: widen<P32>(r, gi, gg, T.lo16, R.t, a); break;
         case P16: widen<P16>(r, gi, gg, T.lo16, R.t, a); break;
         default: widen<P8>(r, gi, gg, T.lo16, R.t, a); break;
